@@ -341,7 +341,9 @@ struct sg_ctx {
     DevBuf<int64_t> d_best, d_acc_count, d_mom, d_trace;
     DevBuf<int32_t> d_acc_out;
     DevBuf<QuadDesc> d_desc;
-    DevBuf<uint4> d_rowA, d_rowB, d_rowC;
+    DevBuf<uint4> d_rowA, d_rowB, d_rowC, d_rowP;
+    bool small = false;        // every instance has planes == 2
+    int quad_threads = kQuadThreads;   // work-group size of the replica kernel
     int n_blocks = 0;
     size_t quad_lds = 0;
     // two launch groups (a launch configuration): the graph's replica kernels of group 1 run
@@ -419,15 +421,17 @@ void init_stream(sg_ctx *c, void *s)
 // LDS of one APT work-group (see apt_quad_kernel): tile, four threshold tables,
 // reduction scratch, cluster-search row bitmaps, and for the queue search (rows longer
 // than 32 sites) the visited bits and the queue.
-size_t apt_lds_bytes(int npad, int n_rows, int ni, bool queue)
+size_t apt_lds_bytes(const InstDev &I, int ni)
 {
     // tile, threshold rows, reduction scratch; then the row scratch of the row-bitset cluster
     // search, or in its place the visited bits and the queue of the breadth-first search
-    size_t words = (size_t)(npad + 4 + 4 * ni + 32) + (queue ? 0 : (size_t)6 * n_rows);
+    const bool queue = I.row_off < 0;
+    size_t words = (size_t)(I.npad + 4 + 4 * ni + 32 + (I.planes == 2 ? kMaxQuadThreads / 16 : 0));
+    if (!queue) words += (I.planes == 2 ? 3 : 6) * (size_t)I.n_rows;
     size_t bytes = 16;
     if (queue) {
-        words += (size_t)((npad + 31) / 32 + 1);
-        bytes += sizeof(uint16_t) * (size_t)npad;
+        words += (size_t)((I.npad + 31) / 32 + 1);
+        bytes += sizeof(uint16_t) * (size_t)I.npad;
     }
     return sizeof(uint32_t) * words + bytes;
 }
@@ -523,7 +527,7 @@ void sqa_records(const Lat &L, int M, std::vector<uint4> &rec, std::vector<uint4
 
 // Row tables for the cluster search (see sg_internal.h); rows of lx <= 32.
 void apt_rows(const Lat &L, std::vector<uint4> &rowA, std::vector<uint4> &rowB,
-              std::vector<uint4> &rowC, InstDev &I)
+              std::vector<uint4> &rowC, std::vector<uint4> &rowP, bool small, InstDev &I)
 {
     I.lx = L.Lx;
     I.ly = L.Ly;
@@ -538,7 +542,8 @@ void apt_rows(const Lat &L, std::vector<uint4> &rowA, std::vector<uint4> &rowB,
         const int ppw = 64 / L.Ly;
         I.planes = (L.Lz + ppw - 1) / ppw <= kQuadThreads / 64 ? 1 : 0;
     }
-    I.row_off = (int32_t)rowA.size();
+    if (small) I.planes = 2;
+    I.row_off = (int32_t)(I.planes == 2 ? rowP.size() : rowA.size());
     for (int r = 0; r < I.n_rows; ++r) {
         uint32_t m[6] = {0, 0, 0, 0, 0, 0};
         uint32_t nbrow[4] = {(uint32_t)r, (uint32_t)r, (uint32_t)r, (uint32_t)r};
@@ -557,6 +562,11 @@ void apt_rows(const Lat &L, std::vector<uint4> &rowA, std::vector<uint4> &rowB,
         for (int x = 0; x < L.Lx; ++x)
             for (int a = 0; a < 3; ++a)
                 if (L.coupling(r * L.Lx + x, a, +1) < 0) neg[a] |= 1u << x;
+        if (I.planes == 2) {
+            rowP.push_back(make_uint4(m[0] | (m[2] << 16), m[3] | (m[4] << 16), m[5] | (neg[0] << 16),
+                                      neg[1] | (neg[2] << 16)));
+            continue;
+        }
         rowA.push_back(make_uint4(m[0], m[1], m[2], m[3]));
         rowB.push_back(make_uint4(m[4], m[5], nbrow[0] | (nbrow[1] << 16), nbrow[2] | (nbrow[3] << 16)));
         rowC.push_back(make_uint4(neg[0], neg[1], neg[2], 0u));
@@ -675,6 +685,23 @@ void build_common(sg_ctx *c, const sg_config *cfg, const int8_t *const *colour =
     set_key(c, cfg->seed);
 }
 
+// Work-group size of the replica kernel: 256 threads, doubled while the largest colour class has
+// more sites than threads (a phase takes several passes) and the context's work-groups together
+// stay within four waves per SIMD (more waves share the SIMD's issue, which bounds large
+// batches).  32 instances of L = 8..15: 23.6 us per cycle with 256 threads, 19.3 us with 512; an
+// L = 12 batch of 2048 work-groups keeps 256.
+int quad_threads(const sg_ctx *c)
+{
+    if (!c->small) return kQuadThreads;
+    int cus = 0, phase = 0;
+    hip_check(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device), "device");
+    for (const InstDev &I : c->idev) phase = std::max(phase, *std::max_element(I.col_cnt, I.col_cnt + 4));
+    int nt = kQuadThreads;
+    while (nt < kMaxQuadThreads && phase > nt && (int64_t)c->n_inst * c->n_quads * (2 * nt / 64) <= 16LL * cus)
+        nt *= 2;
+    return nt;
+}
+
 // --------------------------------------------------------------------- APT
 void create_apt(sg_ctx *c, const sg_config *cfg, const int8_t *const *colour = nullptr)
 {
@@ -706,11 +733,13 @@ void create_apt(sg_ctx *c, const sg_config *cfg, const int8_t *const *colour = n
     // the instance's own tables, then joined in instance order.
     struct Tables {
         InstDev I{};
-        std::vector<uint4> rec, recj, rowA, rowB, rowC;
+        std::vector<uint4> rec, recj, rowA, rowB, rowC, rowP;
         std::vector<uint32_t> lut, tab;
         std::vector<int32_t> tab_off, tab_len;
     };
     std::vector<Tables> per((size_t)c->n_inst);
+    c->small = true;   // one wave searches the clusters (cluster_wave): 16 sites along every axis
+    for (const Lat &L : c->lat) c->small = c->small && L.Lx <= 16 && L.Ly <= 16 && L.Lz <= 16;
     parallel_for(c->n_inst, [&](int i) {
         const Lat &L = c->lat[i];
         Tables &T = per[i];
@@ -720,7 +749,7 @@ void create_apt(sg_ctx *c, const sg_config *cfg, const int8_t *const *colour = n
         I.n_slots = c->n_slots;
         apt_records(L, T.rec, T.recj, I);
         I.n_bonds = L.bonds();
-        apt_rows(L, T.rowA, T.rowB, T.rowC, I);
+        apt_rows(L, T.rowA, T.rowB, T.rowC, T.rowP, c->small, I);
         const double *bt = &c->beta[(size_t)i * c->n_beta];
         for (int b = 0; b < c->n_beta; ++b)
             for (int I2 = -c->imax; I2 <= c->imax; ++I2) T.lut.push_back(heat_bath_threshold(bt[b], I2));
@@ -738,7 +767,7 @@ void create_apt(sg_ctx *c, const sg_config *cfg, const int8_t *const *colour = n
             if (T.tab.size() > (size_t)1 << 30) fail(SG_ENOMEM, "swap tables too large");
         }
     });
-    std::vector<uint4> rec, recj, rowA, rowB, rowC;
+    std::vector<uint4> rec, recj, rowA, rowB, rowC, rowP;
     std::vector<int32_t> perm, slot_lut, tab_off, tab_len;
     std::vector<uint32_t> lut, tab;
     int64_t spin_bytes = 0;
@@ -747,12 +776,13 @@ void create_apt(sg_ctx *c, const sg_config *cfg, const int8_t *const *colour = n
         InstDev I = T.I;
         I.rec_off += (int64_t)rec.size();
         I.recj_off += (int64_t)recj.size();
-        if (I.row_off >= 0) I.row_off += (int32_t)rowA.size();
+        if (I.row_off >= 0) I.row_off += (int32_t)(I.planes == 2 ? rowP.size() : rowA.size());
         rec.insert(rec.end(), T.rec.begin(), T.rec.end());
         recj.insert(recj.end(), T.recj.begin(), T.recj.end());
         rowA.insert(rowA.end(), T.rowA.begin(), T.rowA.end());
         rowB.insert(rowB.end(), T.rowB.begin(), T.rowB.end());
         rowC.insert(rowC.end(), T.rowC.begin(), T.rowC.end());
+        rowP.insert(rowP.end(), T.rowP.begin(), T.rowP.end());
         I.spin_off = spin_bytes;
         spin_bytes += (int64_t)nb4 * I.npad;
         I.slot_off = i * nb4;
@@ -798,6 +828,7 @@ void create_apt(sg_ctx *c, const sg_config *cfg, const int8_t *const *colour = n
     c->d_rowA.upload(rowA, s, "row tables");
     c->d_rowB.upload(rowB, s, "row tables");
     c->d_rowC.upload(rowC, s, "row tables");
+    c->d_rowP.upload(rowP, s, "row tables");
     c->d_perm.upload(perm, s, "perm");
     c->d_slot_lut.upload(slot_lut, s, "slot tables");
     c->d_lut.upload(lut, s, "thresholds");
@@ -818,9 +849,10 @@ void create_apt(sg_ctx *c, const sg_config *cfg, const int8_t *const *colour = n
     std::vector<QuadDesc> desc = make_quad_descs(c->lat, c->n_quads, c->beta, c->n_beta, c->reps, 0);
     c->n_blocks = (int)desc.size();
     c->d_desc.upload(desc, s, "tasks");
+    c->quad_threads = quad_threads(c);
     c->quad_lds = 0;
     for (auto &I : c->idev) {
-        const size_t need = apt_lds_bytes(I.npad, I.n_rows, c->ni, I.row_off < 0);
+        const size_t need = apt_lds_bytes(I, c->ni);
         c->quad_lds = std::max(c->quad_lds, need);
     }
     if (c->quad_lds + 64 * sizeof(uint32_t) > kMaxLds)   // + the kernel's static threshold tables
@@ -839,6 +871,7 @@ void create_apt(sg_ctx *c, const sg_config *cfg, const int8_t *const *colour = n
     a.spins = c->d_spins.p; a.perm = c->d_perm.p; a.lut = c->d_lut.p; a.slot_lut = c->d_slot_lut.p;
     a.icm_on = c->d_icm_on.p; a.E = c->d_E.p; a.mom = c->d_mom.p; a.icm_info = c->d_icm_info.p;
     a.rowA = c->d_rowA.p; a.rowB = c->d_rowB.p; a.rowC = c->d_rowC.p;
+    a.rowP = c->d_rowP.p;
     a.ctr = c->d_ctr.p; a.key0 = c->key0; a.key1 = c->key1; a.tag = TAG_APT_SWEEP;
     a.do_energy = 2; a.mom_from = -1; a.reps = c->reps; a.imax = c->imax; a.ni = c->ni;
     a.n_blocks = c->n_blocks;
@@ -863,6 +896,8 @@ AptArgs apt_args(sg_ctx *c, int n_sweeps, int do_icm)
     a.desc = c->d_desc.p;
     a.inst = c->d_inst.p;
     a.boff = c->d_recb.p != nullptr;
+    a.small = c->small;
+    a.threads = c->quad_threads;
     a.rec_col = a.boff ? c->d_recb.p : c->d_rec.p;
     a.rec_j = c->d_recj.p;
     a.spins = c->d_spins.p;
@@ -876,6 +911,7 @@ AptArgs apt_args(sg_ctx *c, int n_sweeps, int do_icm)
     a.rowA = c->d_rowA.p;
     a.rowB = c->d_rowB.p;
     a.rowC = c->d_rowC.p;
+    a.rowP = c->d_rowP.p;
     a.ctr = c->d_ctr.p;
     a.key0 = c->key0;
     a.key1 = c->key1;
@@ -1234,7 +1270,7 @@ void apply_apt_config(sg_ctx *c, int code)
             for (int i = 0; i < c->n_inst; ++i) {
                 if (!sel[(size_t)i]) continue;
                 const InstDev &I = c->idev[(size_t)i];
-                c->lds_g[g] = std::max(c->lds_g[g], apt_lds_bytes(I.npad, I.n_rows, c->ni, I.row_off < 0));
+                c->lds_g[g] = std::max(c->lds_g[g], apt_lds_bytes(I, c->ni));
             }
         }
     }

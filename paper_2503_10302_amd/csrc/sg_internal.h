@@ -26,6 +26,7 @@ constexpr int kMaxH = 31;      // |h| bound, so that h + 32 fits 6 bits of a sit
 constexpr int kMaxN = 32767;   // sites per instance (16-bit site and neighbour indices)
 constexpr int kMaxByteOffsetSites = 16383;   // neighbour byte offsets (4 x index) fit 16 bits
 constexpr int kQuadThreads = 256;
+constexpr int kMaxQuadThreads = 1024;   // of the variants for few work-groups
 constexpr int kSqaThreads = 512;
 constexpr int kSqaTabWords = 976;        // static LDS of the DT-SQA kernel (tables)
 constexpr size_t kMaxLds = 160 * 1024;   // LDS per CU on gfx950
@@ -65,8 +66,10 @@ struct InstDev {
     int32_t n_rows;      // Ly * Lz
     int32_t row_off;     // first entry of the row tables, -1 when lx > 32
     int32_t ly, lz;      // y and z extents (rows are r = y + ly z)
-    int32_t planes;      // 1: every y-z plane's rows fit one per lane in one wave and all
-                         //    planes in the work-group's waves (wave-local cluster search)
+    int32_t planes;      // cluster search: 2: every lattice of the context has at most 16 sites
+                         //    along every axis (one wave, rowP);
+                         //    1: every y-z plane's rows fit one per lane in one wave and all
+                         //    planes in the work-group's waves (wave-local); 0: other
     int32_t n_bonds;     // bonds with J != 0 (each counted once)
 };
 
@@ -75,6 +78,9 @@ struct InstDev {
 //   rowB[r] = {bond to +z, bond to -z, row(+y) | row(-y) << 16, row(+z) | row(-z) << 16}
 //   rowC[r] = {J = -1 on the bond to +x, to +y, to +z, 0}
 // "present" means the neighbour exists and J != 0.
+// Instances with planes == 2 have one table instead, bits 0..15 and 16..31 of each word:
+//   rowP[r] = {bond to +x present, to +y; to -y, to +z; to -z, J = -1 to +x; J = -1 to +y, to +z}
+// and row_off counts its entries.
 
 // One work-group task of the APT replica kernel: instance and group of four
 // consecutive logical slots.  inst < 0 = idle filler.
@@ -115,6 +121,7 @@ struct AptArgs {
     const uint4 *rowA;
     const uint4 *rowB;
     const uint4 *rowC;
+    const uint4 *rowP;
     uint8_t *spins;            // physical replica buffers, bytes 0/1 (1 = spin up)
     const int32_t *perm;       // logical slot -> physical buffer (per instance)
     const uint32_t *lut;       // heat-bath thresholds, NI per table
@@ -141,6 +148,8 @@ struct AptArgs {
                                // call ctr[1] + cyc_k + 1; counters advance only between graphs
     int32_t waves;             // kernel variant: at least 8 or 7 (also for 0) waves per SIMD
     int32_t boff;              // 1: rec_col holds neighbour byte offsets (kernel variant)
+    int32_t threads;           // work-group size: 256, or 512 or 1024 with small
+    int32_t small;             // 1: every instance has planes == 2 (kernel variant)
     int32_t fused_swap;        // 1: first perform the replica exchange described by sw (the
                                //    previous cycle's attempt) for this work-group's slots,
                                //    reading sw.perm_in / sw.E_in and writing sw.perm and E

@@ -152,7 +152,8 @@ __device__ __forceinline__ int32_t wave_min(int32_t v)
     return v;
 }
 
-// Block-wide sum of four values (blockDim = 256).  red: >= 16 ints of LDS.
+// Block-wide sum of four values over NT threads.  red: >= NT / 16 ints of LDS.
+template <int NT>
 __device__ __forceinline__ void block_sum4(int32_t v[4], int32_t *red)
 {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -162,13 +163,18 @@ __device__ __forceinline__ void block_sum4(int32_t v[4], int32_t *red)
         for (int i = 0; i < 4; ++i) red[wv * 4 + i] = v[i];
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < 4; ++i) v[i] = red[i] + red[4 + i] + red[8 + i] + red[12 + i];
+    for (int i = 0; i < 4; ++i) {
+        v[i] = 0;
+#pragma unroll
+        for (int w = 0; w < NT / 64; ++w) v[i] += red[4 * w + i];
+    }
     __syncthreads();
 }
 
-// block_sum4 for the work-group's last use of red: the totals are read by threads 0..3
-// only (into v), and there is no trailing barrier.
-__device__ __forceinline__ void block_sum4_last(int32_t v[4], int32_t *red)
+// block_sum4 for the work-group's last use of red: the total of v[i] is returned to thread
+// i < 4 only, and there is no trailing barrier.
+template <int NT>
+__device__ __forceinline__ int32_t block_sum4_last(int32_t v[4], int32_t *red)
 {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
@@ -176,9 +182,11 @@ __device__ __forceinline__ void block_sum4_last(int32_t v[4], int32_t *red)
     if (lane == 0)
         for (int i = 0; i < 4; ++i) red[wv * 4 + i] = v[i];
     __syncthreads();
+    int32_t t = 0;
     if (threadIdx.x < 4)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = red[i] + red[4 + i] + red[8 + i] + red[12 + i];
+        for (int w = 0; w < NT / 64; ++w) t += red[4 * w + threadIdx.x];
+    return t;
 }
 
 // Exclusive prefix of v over the block in thread order; returns it and the total.
@@ -204,13 +212,14 @@ __device__ __forceinline__ int32_t block_exclusive_scan(int32_t v, int32_t *red,
 }
 
 // Energies (Eq. 8) of the four slots held in sp: E = -1/2 sum_j s_j (I_j + h_j).
+template <int NT>
 __device__ void quad_energy(const uint32_t *sp, const uint4 *recj, int n, int32_t *red, int32_t e[4])
 {
     int32_t acc[4] = {0, 0, 0, 0};
     uint4 rnext = ((int)threadIdx.x < n) ? recj[threadIdx.x] : make_uint4(0u, 0u, 0u, 0u);
-    for (int j = threadIdx.x; j < n; j += kQuadThreads) {
+    for (int j = threadIdx.x; j < n; j += NT) {
         const uint4 r = rnext;
-        if (j + kQuadThreads < n) rnext = recj[j + kQuadThreads];   // prefetch
+        if (j + NT < n) rnext = recj[j + NT];   // prefetch
         const uint32_t k = aligned_count(sp, r);
         const int32_t d = (int32_t)((r.x >> 16) & 7u);
         const int32_t hh = (int32_t)((r.x >> 25) & 63u) - 32;
@@ -221,7 +230,7 @@ __device__ void quad_energy(const uint32_t *sp, const uint4 *recj, int n, int32_
             acc[i] += ((w >> (8 * i)) & 1u) ? v : -v;
         }
     }
-    block_sum4(acc, red);
+    block_sum4<NT>(acc, red);
 #pragma unroll
     for (int i = 0; i < 4; ++i) e[i] = -acc[i] / 2;
 }
@@ -375,6 +384,53 @@ __device__ __forceinline__ RowFold fold_row(const uint32_t *row, int lx)
     return f;
 }
 
+// fold_row for rows of at most 16 sites.  The reads run past the row's end (up to 15 words, inside
+// the work-group's LDS), so that all are in flight at once: bits lx .. 15 hold no spins.
+__device__ __forceinline__ uint2 fold_row16(const uint32_t *row, int lx)
+{
+    uint32_t w[16];
+#pragma unroll
+    for (int x = 0; x < 8; ++x) w[x] = row[x];
+    uint2 f;
+    f.x = (w[0] | (w[1] << 1)) | ((w[2] | (w[3] << 1)) << 2);
+    f.x |= ((w[4] | (w[5] << 1)) | ((w[6] | (w[7] << 1)) << 2)) << 4;
+    f.y = 0u;
+    if (lx > 8) {
+#pragma unroll
+        for (int x = 8; x < 16; ++x) w[x] = row[x];
+        f.y = (w[8] | (w[9] << 1)) | ((w[10] | (w[11] << 1)) << 2);
+        f.y |= ((w[12] | (w[13] << 1)) | ((w[14] | (w[15] << 1)) << 2)) << 4;
+    }
+    return f;
+}
+
+// Bits 0..15: the spins of the slot in a row folded by fold_row16.
+__device__ __forceinline__ uint32_t slot_row16(const uint2 f, uint32_t slot)
+{
+    return __builtin_amdgcn_perm(f.y, f.x, slot | ((slot + 4u) << 8) | 0x0C0C0000u);
+}
+
+// flip_row for rows of at most 16 sites, reads past the end as in fold_row16.
+__device__ __forceinline__ void flip_row16(uint32_t *row, int lx, uint32_t F0, uint32_t X0, uint32_t F1,
+                                           uint32_t X1)
+{
+#pragma unroll
+    for (int x0 = 0; x0 < 16; x0 += 8) {
+        if (x0 >= lx) break;
+        uint32_t w[8];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) w[t] = row[x0 + t];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            const uint32_t f0 = 0u - ((F0 >> (x0 + t)) & 1u), f1 = 0u - ((F1 >> (x0 + t)) & 1u);
+            w[t] ^= (f0 & X0) ^ (f1 & X1);
+        }
+#pragma unroll
+        for (int t = 0; t < 8; ++t)
+            if (x0 + t < lx) row[x0 + t] = w[t];
+    }
+}
+
 // Bit x: the spin (1 = up) of the slot at site x of the folded row.
 __device__ __forceinline__ uint32_t slot_row(const RowFold &f, uint32_t slot)
 {
@@ -519,7 +575,7 @@ __device__ void icm_pairs_rows(uint32_t *sp, const uint4 *rowA, const uint4 *row
                           __popc(X2 & ~N2) - __popc(X2 & N2);
         }
     }
-    block_sum4(tot, red);
+    block_sum4<kQuadThreads>(tot, red);
     // cluster flip of the first replica: crossing bonds change sign -> dE = 2 * sum
     dE01[0] = (m0 > 0 && 2 * tot[0] <= n) ? 2 * tot[2] : 0;
     dE01[1] = (np > 1 && m1 > 0 && 2 * tot[1] <= n) ? 2 * tot[3] : 0;
@@ -757,7 +813,7 @@ __device__ void icm_pairs_planes(uint32_t *sp, const uint4 *rowA, const uint4 *r
                           __popc(X1b & N1b) + __popc(X2b & ~N2b) - __popc(X2b & N2b);
         }
     }
-    block_sum4(tot, red);
+    block_sum4<kQuadThreads>(tot, red);
     // cluster flip of the first replica: crossing bonds change sign -> dE = 2 * sum
     dE01[0] = (m0 > 0 && 2 * tot[0] <= n) ? 2 * tot[2] : 0;
     dE01[1] = (np > 1 && m1 > 0 && 2 * tot[1] <= n) ? 2 * tot[3] : 0;
@@ -790,6 +846,301 @@ __device__ void icm_pairs_planes(uint32_t *sp, const uint4 *rowA, const uint4 *r
     }
     if (own && (F[0] | F[1])) flip_row(sp + r * lx, lx, F[0], Xf[0], F[1], Xf[1]);
     __syncthreads();
+}
+
+// The moves of icm_pairs_planes for lattices of at most 16 sites along every axis, with the
+// whole cluster search in one wave: lane (g, y) of wave 0 holds row y of the K planes
+// z = g K .. g K + K - 1 (g = lane / 16, K = ceil(lz / 4)), both pairs in one word (pair 1 in
+// the upper half), so that a step of the fill takes the wrap bond along x and closes every row
+// between its ends (xfill_linear), carries the cluster up to three rows along y inside the 16 lanes of a plane (lane moves on the vector
+// unit, no LDS), and closes it along z inside the lane; only the two planes at a lane's ends and
+// the wrap along y go through lane exchanges.  What bounds it is the chain of dependent steps of
+// one wave.  On equilibrated states a step of this kind needs 4.9 / 5.2 / 6.6 rounds at L = 8 /
+// 12 / 15 (0.2 more without a second pass for the wrap along x), against 9.5 / 19.5 / 26.5 rounds of one move per axis and 1 / 2.6 / 3.5 exchanges
+// between waves with planes spread over the waves.
+//
+// Measured, with the spread-plane search before: a cycle of one L = 8 instance 12.4 us -> 10.3 us, of
+// 256 instances of L = 6..15 44.3 -> 35 us (a third of that because the kernel without the
+// other searches no longer spills).
+//
+// A plane past lz in the last lanes is transparent: it takes and gives every site along z, so
+// the wrap bond between the planes lz - 1 and 0 works through it.
+
+// Lane i takes lane i - n (shr) or i + n (shl) of its row of 16 lanes, 0 past the end.
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp16(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
+}
+constexpr int kShl = 0x100, kShr = 0x110, kBcast15 = 0x15F;
+constexpr int kYReach = 3;   // rows that a round carries the cluster along y
+
+template <int K>
+__device__ __forceinline__ void cluster_wave(const uint4 *t, int lx, int ly, int lz, uint32_t wp0,
+                                             uint32_t wp1, const uint32_t *Qr, uint32_t *Vr,
+                                             int32_t *red)
+{
+    const int lane = threadIdx.x & 63, y = lane & 15, g = lane >> 4;
+    const uint32_t hi = (uint32_t)(lx - 1);
+    uint32_t W[K], Q[K];
+    uint32_t cnt[K], pre[K];   // q = -1 sites of the row and before it in the plane, per pair
+    uint32_t S = 0u;           // of the lane's planes
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int z = g * K + k;
+        Q[k] = (y < ly && z < lz) ? Qr[z * ly + y] : 0u;
+        W[k] = 0u;
+        cnt[k] = (uint32_t)__popc(Q[k] & 0xFFFFu) | ((uint32_t)__popc(Q[k] >> 16) << 16);
+    }
+    // seeds: the k-th site with q = -1 in ascending site order = (plane, row, x) order
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        uint32_t c = cnt[k];
+        c += dpp16<kShr + 1>(c);
+        c += dpp16<kShr + 2>(c);
+        c += dpp16<kShr + 4>(c);
+        c += dpp16<kShr + 8>(c);
+        pre[k] = S + c - cnt[k];
+        S += dpp16<kBcast15>(c);
+    }
+    const uint32_t s0 = (uint32_t)__builtin_amdgcn_readlane((int)S, 0);
+    const uint32_t s1 = s0 + (uint32_t)__builtin_amdgcn_readlane((int)S, 16);
+    const uint32_t s2 = s1 + (uint32_t)__builtin_amdgcn_readlane((int)S, 32);
+    const uint32_t m = s2 + (uint32_t)__builtin_amdgcn_readlane((int)S, 48);
+    const uint32_t base = g == 0 ? 0u : (g == 1 ? s0 : (g == 2 ? s1 : s2));
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        const uint32_t mp = p ? m >> 16 : m & 0xFFFFu;
+        const uint32_t kth = __umulhi(p ? wp1 : wp0, mp);
+        uint32_t qs = 0u, nth = 0u;
+        int ks = -1;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const uint32_t f = base + pre[k];
+            const uint32_t d = kth - (p ? f >> 16 : f & 0xFFFFu);
+            const uint32_t c = p ? cnt[k] >> 16 : cnt[k] & 0xFFFFu;
+            if (d < c) {
+                ks = k;
+                nth = d;
+                qs = p ? Q[k] >> 16 : Q[k] & 0xFFFFu;
+            }
+        }
+        if (ks >= 0) {   // one lane (none when the pair has no such site)
+            uint32_t x = 0u;
+#pragma unroll
+            for (uint32_t h = 8; h >= 1; h >>= 1) {
+                const uint32_t c = (uint32_t)__popc(qs & ((1u << h) - 1u));
+                if (nth >= c) {
+                    nth -= c;
+                    qs >>= h;
+                    x += h;
+                }
+            }
+            red[16 + p] = ((g * K + ks) * ly + y) * lx + (int)x;
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+                if (k == ks) W[k] |= 1u << (x + 16u * p);
+        }
+    }
+    if (lane == 0) red[18] = (int32_t)m;
+    // masks of the sites that can take the cluster from each side (U, D: from y - 1, y + 1, the
+    // wrap included: a move inside the 16 lanes brings 0 into the edge rows)
+    XMasks xm[K];
+    uint32_t U[K], D[K], Zu[K], Zd[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int z = g * K + k;
+        const uint4 r = t[k];
+        auto both = [](uint32_t h) { return h | (h << 16); };
+        xm[k] = x_masks(Q[k], both(r.x & 0xFFFFu), hi, 0x00010001u);
+        D[k] = both(r.x >> 16) & Q[k];
+        U[k] = both(r.y & 0xFFFFu) & Q[k];
+        Zd[k] = z < lz ? both(r.y >> 16) & Q[k] : 0xFFFFFFFFu;
+        Zu[k] = z < lz ? both(r.z & 0xFFFFu) & Q[k] : 0xFFFFFFFFu;
+    }
+    // lanes that hold the row across the wrap along y (rows inside: their own, no effect), and
+    // the next planes along z
+    const int aw = 4 * (y == 0 ? lane + ly - 1 : (y == ly - 1 ? lane - y : lane));
+    const uint32_t first = y == 0 ? 0xFFFFFFFFu : 0u;
+    const int ab = 4 * ((lane + 48) & 63), at = 4 * ((lane + 16) & 63);
+    while (true) {
+        uint32_t W0[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            W0[k] = W[k];
+            const uint32_t w = W[k] | ((W[k] >> hi) & xm[k].w0) | ((W[k] << hi) & xm[k].whi);
+            const uint32_t v = xfill_linear(w, xm[k]);
+            W[k] = v;
+        }
+#pragma unroll
+        for (int h = 0; h < kYReach; ++h)
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                // (opaque, so that each lane move is part of its AND)
+                uint32_t u = dpp16<kShr + 1>(W[k]) & U[k], d = dpp16<kShl + 1>(W[k]) & D[k];
+                asm("" : "+v"(u), "+v"(d));
+                W[k] |= u | d;
+            }
+        const uint32_t below = (uint32_t)__builtin_amdgcn_ds_bpermute(ab, (int)W[K - 1]);
+        const uint32_t above = (uint32_t)__builtin_amdgcn_ds_bpermute(at, (int)W[0]);
+        uint32_t yw[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) yw[k] = (uint32_t)__builtin_amdgcn_ds_bpermute(aw, (int)W[k]);
+#pragma unroll
+        for (int k = 0; k < K; ++k) W[k] |= yw[k] & ((U[k] & first) | (D[k] & ~first));
+        W[0] |= below & Zu[0];
+        W[K - 1] |= above & Zd[K - 1];
+#pragma unroll
+        for (int k = 1; k < K; ++k) W[k] |= W[k - 1] & Zu[k];
+#pragma unroll
+        for (int k = K - 2; k >= 0; --k) W[k] |= W[k + 1] & Zd[k];
+        uint32_t grew = 0u;
+#pragma unroll
+        for (int k = 0; k < K; ++k) grew |= W[k] ^ W0[k];
+        if (!__any(grew != 0u)) break;
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int z = g * K + k;
+        if (y < ly && z < lz) Vr[z * ly + y] = W[k];
+    }
+}
+
+// Thread (z, y) = (tid / 16, tid mod 16) of the first four waves holds row y of plane z for the
+// overlap, the sums over the cluster's boundary and the flips.  LDS: Qr, Vr, Sr [ly lz] each;
+// red[16..28], sums [NT / 16].  e4: this thread's energy changes of the four slots so far; the
+// return value is slot tid's total over the work-group, the move included, in threads 0..3.
+template <int NT>
+__device__ int32_t icm_pairs_wave(uint32_t *sp, const uint4 *rowP, int n, int lx, int ly, int lz, int np,
+                               uint32_t pa, uint32_t pb, uint32_t pidx0, uint32_t pidx1, uint32_t call,
+                               uint32_t c3p, uint32_t key0, uint32_t key1, uint32_t *Qr, int32_t *red,
+                                  int32_t *sums, int32_t *info0, int32_t *info1, int32_t e4[4])
+{
+    uint32_t *Vr = Qr + ly * lz, *Sr = Vr + ly * lz;   // cluster; spins of each pair's first replica
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));   // (what follows from it is not kept from or for other parts)
+    const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int y = tid & 15, z = tid >> 4;
+    const bool own = y < ly && z < lz;
+    const int r = z * ly + y;
+    const int K = (lz + 3) >> 2;
+    // wave 0: the bond masks of its rows, and both pairs' random words (lane 1: pair 1)
+    uint4 t[4];
+    uint4 uw = make_uint4(0u, 0u, 0u, 0u);
+    if (wv == 0) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            t[k] = make_uint4(0u, 0u, 0u, 0u);
+            const int zz = (lane >> 4) * K + k;
+            if (k < K && y < ly && zz < lz) t[k] = rowP[zz * ly + y];
+        }
+        uw = philox10(lane == 1 ? pidx1 : pidx0, call, 0u, c3p, key0, key1);
+    }
+    if (own) {
+        const uint2 f = fold_row16(sp + r * lx, lx);
+        uint32_t s = slot_row16(f, pa & 3u), q = s ^ slot_row16(f, pb & 3u);
+        if (np > 1) {
+            const uint32_t s1 = slot_row16(f, (pa >> 8) & 3u);
+            q |= (s1 ^ slot_row16(f, (pb >> 8) & 3u)) << 16;
+            s |= s1 << 16;
+        }
+        const uint32_t all2 = ((1u << lx) - 1u) * 0x00010001u;
+        Qr[r] = q & all2;
+        Sr[r] = s & all2;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int32_t v = wave_sum(e4[i]);
+        if (lane == 0) sums[4 * wv + i] = v;
+        e4[i] = 0;
+    }
+    __syncthreads();
+    if (wv == 0) {
+        const uint32_t w0 = (uint32_t)__builtin_amdgcn_readlane((int)uw.x, 0);
+        const uint32_t w1 = (uint32_t)__builtin_amdgcn_readlane((int)uw.x, 1);
+        if (lane == 0) red[19] = (int32_t)(uw.y >> 31);
+        if (lane == 1) red[28] = (int32_t)(uw.y >> 31);
+        if (K == 4) cluster_wave<4>(t, lx, ly, lz, w0, w1, Qr, Vr, red);
+        else if (K == 3) cluster_wave<3>(t, lx, ly, lz, w0, w1, Qr, Vr, red);
+        else if (K == 2) cluster_wave<2>(t, lx, ly, lz, w0, w1, Qr, Vr, red);
+        else cluster_wave<1>(t, lx, ly, lz, w0, w1, Qr, Vr, red);
+    }
+    // this thread's row again (not held across the search: it would cost registers there)
+    uint4 rp = make_uint4(0u, 0u, 0u, 0u);
+    if (own) rp = rowP[r];
+    __syncthreads();
+    // cluster sizes and, for each pair, the sum of J s_i s_j of the first replica over bonds
+    // that cross the cluster boundary (counted once, along +x, +y, +z), both pairs of a row in
+    // one word, their counts in the halves of one integer
+    const uint32_t hi = (uint32_t)(lx - 1), top = 0x00010001u << hi;
+    uint32_t V = 0u;
+    int32_t sz = 0, db = 0;
+    if (own) {
+        const int iy = y + 1 < ly ? r + 1 : r + 1 - ly, iz = z + 1 < lz ? r + ly : y;
+        V = Vr[r];
+        const uint32_t s = Sr[r];
+        auto both = [](uint32_t h) { return h | (h << 16); };
+        const uint32_t Vx = ((V >> 1) & ~top) | ((V << hi) & top), Sx = ((s >> 1) & ~top) | ((s << hi) & top);
+        const uint32_t X0 = (V ^ Vx) & both(rp.x & 0xFFFFu), N0 = X0 & (s ^ Sx ^ both(rp.z >> 16));
+        const uint32_t X1 = (V ^ Vr[iy]) & both(rp.x >> 16), N1 = X1 & (s ^ Sr[iy] ^ both(rp.w & 0xFFFFu));
+        const uint32_t X2 = (V ^ Vr[iz]) & both(rp.y >> 16), N2 = X2 & (s ^ Sr[iz] ^ both(rp.w >> 16));
+        auto lo = [](uint32_t v) { return (int32_t)__popc(v & 0xFFFFu); };
+        auto up = [](uint32_t v) { return (int32_t)__popc(v >> 16); };
+        sz = lo(V) + (up(V) << 16);
+        db = lo(X0) + lo(X1) + lo(X2) - 2 * (lo(N0) + lo(N1) + lo(N2)) +
+             (int32_t)((uint32_t)(up(X0) + up(X1) + up(X2) - 2 * (up(N0) + up(N1) + up(N2))) << 16);
+    }
+    if (wv < 4) {
+        sz = wave_sum(sz);
+        db = wave_sum(db);
+        if (lane == 0) {
+            red[20 + 2 * wv] = sz;
+            red[21 + 2 * wv] = db;
+        }
+    }
+    __syncthreads();
+    sz = red[20] + red[22] + red[24] + red[26];
+    db = red[21] + red[23] + red[25] + red[27];
+    const int32_t m = red[18];
+    const int32_t m0 = m & 0xFFFF, m1 = (int32_t)((uint32_t)m >> 16);
+    const int32_t z0 = sz & 0xFFFF, z1 = (int32_t)((uint32_t)sz >> 16);
+    const int32_t d0 = (int32_t)(int16_t)db, d1 = (db - d0) >> 16;
+    const bool big0 = 2 * z0 > n, big1 = 2 * z1 > n;
+    const int32_t br0 = red[19], br1 = red[28];
+    const uint32_t mA0 = 1u << (8 * (pa & 3u)), mB0 = 1u << (8 * (pb & 3u));
+    const uint32_t mA1 = 1u << (8 * ((pa >> 8) & 3u)), mB1 = 1u << (8 * ((pb >> 8) & 3u));
+    int32_t v = 0;
+    if (tid < 4) {
+        // isoenergetic move (crossing bonds change sign, the partner's energy by the opposite
+        // amount); a cluster of more than half the lattice flips one whole replica instead
+#pragma unroll
+        for (int w = 0; w < NT / 64; ++w) v += sums[4 * w + tid];
+        const int32_t c0 = m0 > 0 && !big0 ? 2 * d0 : 0, c1 = m1 > 0 && !big1 ? 2 * d1 : 0;
+        if (tid == (int)(pa & 3u)) v += c0;
+        if (tid == (int)(pb & 3u)) v -= c0;
+        if (np > 1) {
+            if (tid == (int)((pa >> 8) & 3u)) v += c1;
+            if (tid == (int)((pb >> 8) & 3u)) v -= c1;
+        }
+        int32_t *o = tid == 0 ? info0 : info1;
+        if (tid < np) {
+            const int32_t mp = tid ? m1 : m0;
+            const bool big = tid ? big1 : big0;
+            o[0] = mp;
+            o[1] = mp > 0 ? red[16 + tid] : -1;
+            o[2] = mp > 0 ? (tid ? z1 : z0) : 0;
+            o[3] = mp > 0 && big ? 1 + (tid ? br1 : br0) : 0;
+        }
+    }
+    if (own) {
+        const uint32_t all = (1u << lx) - 1u;
+        const uint32_t X0 = big0 ? (br0 == 0 ? mA0 : mB0) : (mA0 | mB0);
+        const uint32_t X1 = big1 ? (br1 == 0 ? mA1 : mB1) : (mA1 | mB1);
+        const uint32_t F0 = big0 ? all : V & 0xFFFFu, F1 = np > 1 ? (big1 ? all : V >> 16) : 0u;
+        flip_row16(sp + r * lx, lx, F0, X0, F1, X1);
+    }
+    __syncthreads();
+    return v;
 }
 
 // Replica exchange (Eq. 4): the decision for temperature pair (b, b + 1), label l, at
@@ -1072,8 +1423,12 @@ __device__ __forceinline__ void apt_site(const AptArgs &A, uint32_t *sp, const u
 // W: at least W waves per SIMD (the register budget: 64 VGPRs for W = 8, 72 for W = 7), a
 // launch-configuration choice of the autotuner; results do not depend on it.  BOFF: the
 // colour-sorted records carry byte offsets (every instance of at most 16383 sites).
-template <bool SCALED, int W, bool BOFF>
-__global__ __launch_bounds__(kQuadThreads) __attribute__((amdgpu_waves_per_eu(W, 8)))
+// SMALL: every instance has planes == 2 (the searches of larger lattices are left out, which
+// spares the registers they would cost the rest of the kernel).
+// NT: threads of the work-group (256; more, with W = 4, where few work-groups leave the chip
+// idle: see quad_threads in sg_api.cpp).
+template <bool SCALED, int W, bool BOFF, bool SMALL, int NT>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(W, 8)))
 void apt_quad_kernel(AptArgs A)
 {
     // SCALED (at most 16 threshold entries per slot): the four tables sit in static LDS at
@@ -1088,7 +1443,8 @@ void apt_quad_kernel(AptArgs A)
         uint32_t *sp = lds;                              // npad + 4 words
         uint32_t *lut = SCALED ? lut_static : sp + npad + 4;   // 4 * ni
         int32_t *red = (int32_t *)(sp + npad + 4 + 4 * ni);    // 32
-        uint32_t *Qr = (uint32_t *)(red + 32);           // 2 * n_rows
+        int32_t *sums = SMALL ? red + 32 : red;                // SMALL: kMaxQuadThreads / 16
+        uint32_t *Qr = (uint32_t *)(red + 32 + (SMALL ? kMaxQuadThreads / 16 : 0));          // 2 * n_rows (planes == 2: 3 * n_rows in all)
         uint32_t *Vr = Qr + 2 * I.n_rows;                // 2 * n_rows, then S rows 2 * n_rows
         // queue search only (no row tables: rows longer than 32 sites, or too many rows): in
         // place of the row scratch, allocated when some instance needs it
@@ -1099,7 +1455,7 @@ void apt_quad_kernel(AptArgs A)
         // The threshold rows are loaded by waves 1..3 while wave 0 makes the exchange, so that
         // the two chains of dependent loads overlap (the exchange ends with a barrier; without
         // it the gather's barrier orders the rows before the sweep).
-        for (int e = tid - 64; e >= 0 && e < 4 * ni; e += kQuadThreads - 64) {
+        for (int e = tid - 64; e >= 0 && e < 4 * ni; e += NT - 64) {
             const int i = e / ni;
             lut[e] = A.lut[(int64_t)A.slot_lut[slot_off + 4 * q + i] * ni + (e - i * ni)];
         }
@@ -1107,7 +1463,7 @@ void apt_quad_kernel(AptArgs A)
         int32_t pq[4];
         if (A.fused_swap) {
             fused_swap_quad(A.sw, slot_off, D.inst, q, red + 24, red + 28);
-            for (int i = 0; i < 4; ++i) pq[i] = red[24 + i];
+            for (int i = 0; i < 4; ++i) pq[i] = __builtin_amdgcn_readfirstlane(red[24 + i]);
             if (tid < 4) e_in = red[28 + tid];
         } else {
             for (int i = 0; i < 4; ++i) pq[i] = A.perm[slot_off + 4 * q + i];
@@ -1118,8 +1474,8 @@ void apt_quad_kernel(AptArgs A)
         // gather + transpose: word j holds byte i = spin of slot 4q+i at site j; two groups of
         // four sites per thread and pass, all eight loads issued before either is transposed
         const int ng4 = npad >> 2;
-        for (int g0 = tid; g0 < ng4; g0 += 2 * kQuadThreads) {
-            const int g1 = g0 + kQuadThreads;
+        for (int g0 = tid; g0 < ng4; g0 += 2 * NT) {
+            const int g1 = g0 + NT;
             const bool two = g1 < ng4;
             uint32_t v[2][4];
 #pragma unroll
@@ -1155,6 +1511,8 @@ void apt_quad_kernel(AptArgs A)
         uint32_t V02 = 0u, V13 = 0u, C4 = 0u;
         const uint32_t rev4 = 2u * (uint32_t)A.imax * 0x01010101u;
         bool full_energy = A.do_energy == 2;
+        bool summed = false;   // e_sum of thread i < 4 already holds slot i's total change
+        int32_t e_sum = 0;
         // threshold offsets: table of slot b at b * ni; with ni <= 16 the four byte offsets
         // of one site fit one word (index bytes + table starts, times 4)
         const uint32_t soff4 = (uint32_t)ni * 0x03020100u;
@@ -1170,13 +1528,13 @@ void apt_quad_kernel(AptArgs A)
                 // two sites per pass, each with its own record register, so that the record
                 // of the next site loads while this one is updated
                 uint4 ra = (tid < cnt) ? rc[tid] : make_uint4(0u, 0u, 0u, 0u);
-                for (int i = tid; i < cnt; i += 2 * kQuadThreads) {
-                    const bool has_b = i + kQuadThreads < cnt;
+                for (int i = tid; i < cnt; i += 2 * NT) {
+                    const bool has_b = i + NT < cnt;
                     uint4 rb = make_uint4(0u, 0u, 0u, 0u);
-                    if (has_b) rb = rc[i + kQuadThreads];
+                    if (has_b) rb = rc[i + NT];
                     apt_site<SCALED, BOFF>(A, sp, lut, ra, uq, c3, soff4, rev4, V02, V13, C4);
                     if (!has_b) break;
-                    if (i + 2 * kQuadThreads < cnt) ra = rc[i + 2 * kQuadThreads];
+                    if (i + 2 * NT < cnt) ra = rc[i + 2 * NT];
                     apt_site<SCALED, BOFF>(A, sp, lut, rb, uq, c3, soff4, rev4, V02, V13, C4);
                 }
                 __syncthreads();
@@ -1188,7 +1546,7 @@ void apt_quad_kernel(AptArgs A)
             V02 = V13 = C4 = 0u;
             if (A.mom_from >= 0 && sw >= A.mom_from) {
                 int32_t e[4] = {dE[0], dE[1], dE[2], dE[3]};
-                block_sum4(e, red);
+                block_sum4<NT>(e, sums);
                 if (tid < 4) {
                     const int s = 4 * q + tid;
                     if (s < I.n_slots) {
@@ -1247,56 +1605,63 @@ void apt_quad_kernel(AptArgs A)
             }
             if (np > 0) {
                 const uint32_t c3p = ((uint32_t)D.inst << 4) | TAG_ICM_PICK;
-                const uint4 u0 = philox10((uint32_t)pidx0, a, 0u, c3p, A.key0, A.key1);
-                const uint4 u1 = philox10((uint32_t)pidx1, a, 0u, c3p, A.key0, A.key1);
                 int32_t *info0 = A.icm_info + ((int64_t)I.info_off + pidx0) * 4;
                 int32_t *info1 = A.icm_info + ((int64_t)I.info_off + pidx1) * 4;
-                if (I.row_off >= 0) {
-                    int32_t d01[2];
-                    if (I.planes)
-                        icm_pairs_planes(sp, A.rowA + I.row_off, A.rowB + I.row_off,
-                                         A.rowC + I.row_off, n, I.lx, I.ly, I.lz, np, pa, pb,
-                                         make_uint4(u0.x, u0.y, u1.x, u1.y), Qr, Vr, red, info0,
-                                         info1, d01);
-                    else
-                        icm_pairs_rows(sp, A.rowA + I.row_off, A.rowB + I.row_off,
-                                       A.rowC + I.row_off, n, I.lx, I.n_rows, np, pa, pb,
-                                       make_uint4(u0.x, u0.y, u1.x, u1.y), Qr, Vr, red, info0,
-                                       info1, d01);
-                    if (tid == 0) {
-                        // isoenergetic move: the partner's energy changes by the opposite amount
-                        dE[pa & 3u] += d01[0];
-                        dE[pb & 3u] -= d01[0];
-                        if (np > 1) {
-                            dE[(pa >> 8) & 3u] += d01[1];
-                            dE[(pb >> 8) & 3u] -= d01[1];
-                        }
-                    }
+                if constexpr (SMALL) {
+                    e_sum = icm_pairs_wave<NT>(sp, A.rowP + I.row_off, n, I.lx, I.ly, I.lz, np, pa, pb,
+                                               (uint32_t)pidx0, (uint32_t)pidx1, a, c3p, A.key0,
+                                               A.key1, Qr, red, sums, info0, info1, dE);
                 } else {
-                    full_energy = true;
-                    icm_pair(sp, recj, n, (int)(pa & 3u), (int)(pb & 3u), u0.x, u0.y, queue, vis,
-                             red, info0);
-                    if (np > 1)
-                        icm_pair(sp, recj, n, (int)((pa >> 8) & 3u), (int)((pb >> 8) & 3u), u1.x,
-                                 u1.y, queue, vis, red, info1);
+                    const uint4 u0 = philox10((uint32_t)pidx0, a, 0u, c3p, A.key0, A.key1);
+                    const uint4 u1 = philox10((uint32_t)pidx1, a, 0u, c3p, A.key0, A.key1);
+                    if (I.row_off >= 0) {
+                        int32_t d01[2];
+                        if (I.planes)
+                            icm_pairs_planes(sp, A.rowA + I.row_off, A.rowB + I.row_off,
+                                             A.rowC + I.row_off, n, I.lx, I.ly, I.lz, np, pa, pb,
+                                             make_uint4(u0.x, u0.y, u1.x, u1.y), Qr, Vr, red, info0,
+                                             info1, d01);
+                        else
+                            icm_pairs_rows(sp, A.rowA + I.row_off, A.rowB + I.row_off,
+                                           A.rowC + I.row_off, n, I.lx, I.n_rows, np, pa, pb,
+                                           make_uint4(u0.x, u0.y, u1.x, u1.y), Qr, Vr, red, info0,
+                                           info1, d01);
+                        if (tid == 0) {
+                            // isoenergetic move: the partner's energy changes by the opposite amount
+                            dE[pa & 3u] += d01[0];
+                            dE[pb & 3u] -= d01[0];
+                            if (np > 1) {
+                                dE[(pa >> 8) & 3u] += d01[1];
+                                dE[(pb >> 8) & 3u] -= d01[1];
+                            }
+                        }
+                    } else {
+                        full_energy = true;
+                        icm_pair(sp, recj, n, (int)(pa & 3u), (int)(pb & 3u), u0.x, u0.y, queue, vis,
+                                 red, info0);
+                        if (np > 1)
+                            icm_pair(sp, recj, n, (int)((pa >> 8) & 3u), (int)((pb >> 8) & 3u), u1.x,
+                                     u1.y, queue, vis, red, info1);
+                    }
                 }
+                if (SMALL) summed = true;
             }
         }
 
         if (A.do_energy && full_energy) {
             int32_t e[4];
-            quad_energy(sp, A.rec_j + I.recj_off, n, red, e);
+            quad_energy<NT>(sp, A.rec_j + I.recj_off, n, sums, e);
             if (tid < 4) {
                 const int s = 4 * q + tid;
                 if (s < I.n_slots) A.E[I.slot_off + s] = e[tid];
             }
         } else if (A.do_energy) {
-            block_sum4_last(dE, red);
+            if (!summed) e_sum = block_sum4_last<NT>(dE, sums);
             if (tid < 4) {
                 const int s = 4 * q + tid;
                 if (s < I.n_slots) {
-                    if (A.fused_swap) A.E[I.slot_off + s] = e_in + dE[tid];
-                    else A.E[I.slot_off + s] += dE[tid];
+                    if (A.fused_swap) A.E[I.slot_off + s] = e_in + e_sum;
+                    else A.E[I.slot_off + s] += e_sum;
                 }
             }
         } else if (A.fused_swap && tid < 4 && 4 * q + tid < I.n_slots) {
@@ -1305,7 +1670,7 @@ void apt_quad_kernel(AptArgs A)
 
         if (A.n_sweeps > 0 || A.do_icm) {
             uint8_t *gw = A.spins + I.spin_off;
-            for (int g = tid; g < (npad >> 2); g += kQuadThreads) {
+            for (int g = tid; g < (npad >> 2); g += NT) {
                 uint32_t o[4];
                 transpose_bytes(sp[4 * g], sp[4 * g + 1], sp[4 * g + 2], sp[4 * g + 3], o);
                 *(uint32_t *)(gw + b0 + 4 * g) = o[0];
@@ -2189,30 +2554,38 @@ static hipError_t allow_lds(const void *fn, size_t bytes)
     return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
-template <bool SCALED, int W, bool BOFF>
+template <bool SCALED, int W, bool BOFF, bool SMALL, int NT>
 hipError_t launch_apt_quad_t(const AptArgs &a, size_t lds_bytes, hipStream_t s)
 {
-    hipError_t e = allow_lds((const void *)apt_quad_kernel<SCALED, W, BOFF>, lds_bytes);
+    const void *k = (const void *)apt_quad_kernel<SCALED, W, BOFF, SMALL, NT>;
+    hipError_t e = allow_lds(k, lds_bytes);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((apt_quad_kernel<SCALED, W, BOFF>), dim3(a.n_blocks), dim3(kQuadThreads),
+    hipLaunchKernelGGL((apt_quad_kernel<SCALED, W, BOFF, SMALL, NT>), dim3(a.n_blocks), dim3(NT),
                        lds_bytes, s, a);
     return hipGetLastError();
 }
 
-template <bool SCALED, bool BOFF>
+template <bool SCALED, bool BOFF, bool SMALL>
 hipError_t launch_apt_quad_w(const AptArgs &a, size_t lds_bytes, hipStream_t s)
 {
-    if (a.waves == 8) return launch_apt_quad_t<SCALED, 8, BOFF>(a, lds_bytes, s);
-    return launch_apt_quad_t<SCALED, 7, BOFF>(a, lds_bytes, s);
+    if constexpr (SMALL) {
+        if (a.threads == 512) return launch_apt_quad_t<SCALED, 4, BOFF, SMALL, 512>(a, lds_bytes, s);
+        if (a.threads == 1024) return launch_apt_quad_t<SCALED, 4, BOFF, SMALL, 1024>(a, lds_bytes, s);
+    }
+    if (a.waves == 8) return launch_apt_quad_t<SCALED, 8, BOFF, SMALL, 256>(a, lds_bytes, s);
+    return launch_apt_quad_t<SCALED, 7, BOFF, SMALL, 256>(a, lds_bytes, s);
 }
 
 hipError_t launch_apt_quad(const AptArgs &a, size_t lds_bytes, hipStream_t s)
 {
+    if (a.boff && a.small)
+        return a.ni <= 16 ? launch_apt_quad_w<true, true, true>(a, lds_bytes, s)
+                          : launch_apt_quad_w<false, true, true>(a, lds_bytes, s);
     if (a.boff)
-        return a.ni <= 16 ? launch_apt_quad_w<true, true>(a, lds_bytes, s)
-                          : launch_apt_quad_w<false, true>(a, lds_bytes, s);
-    return a.ni <= 16 ? launch_apt_quad_w<true, false>(a, lds_bytes, s)
-                      : launch_apt_quad_w<false, false>(a, lds_bytes, s);
+        return a.ni <= 16 ? launch_apt_quad_w<true, true, false>(a, lds_bytes, s)
+                          : launch_apt_quad_w<false, true, false>(a, lds_bytes, s);
+    return a.ni <= 16 ? launch_apt_quad_w<true, false, false>(a, lds_bytes, s)
+                      : launch_apt_quad_w<false, false, false>(a, lds_bytes, s);
 }
 
 hipError_t launch_apt_swap(const SwapArgs &a, hipStream_t s)

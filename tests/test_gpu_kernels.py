@@ -1,0 +1,55 @@
+"""GPU parity of single kernels at the edges of their tiles, bit for bit against the CPU oracle."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2503_10302_amd import sg
+from paper_2503_10302_amd.inputs import diluted_couplings, ej_couplings, geometric_ladder
+
+pytestmark = pytest.mark.gpu
+SEED = 0x0DD_5EED
+
+
+def _apt_cycles_match(insts, reps, cycles, cutoff, sweeps=1, n_beta=4):
+    """run_apt and one further cluster move with its records, spins and energies compared."""
+    beta = geometric_ladder(n_beta, 0.2, 3.0)
+    ctx = sg.apt(insts, beta, SEED, reps_per_beta=reps)
+    trace = ctx.run_apt(cycles, sweeps, cutoff, record_every=1)
+    icm = np.isfinite(cutoff)
+    info = ctx.icm(cutoff, want_info=True) if icm else None
+    spins, E = ctx.spins(), ctx.energy()
+    for i, inst in enumerate(insts):
+        lat = oracle.Lattice(*inst)
+        sp = oracle.apt_init(lat, i, n_beta * reps, SEED)
+        ctr, oE = np.zeros(3, np.uint32), np.zeros(n_beta * reps, np.int64)
+        best = np.array([np.iinfo(np.int64).max], np.int64)
+        rc, otr, _ = oracle.apt_run(lat, i, beta, reps, SEED, cycles, sweeps, cutoff, 1, ctr, sp, oE, best)
+        assert rc == 0 and np.array_equal(trace[i], otr), f"trace, instance {i}"
+        if icm:
+            rc, oinfo = oracle.apt_icm(lat, i, beta, reps, cutoff, SEED, cycles + 1, sp)
+            assert rc == 0 and np.array_equal(info[i], oinfo), f"records, instance {i}"
+        assert np.array_equal(spins[i, :, :lat.n], sp), f"spins, instance {i}"
+        assert E[i].tolist() == [oracle.energy(lat, s) for s in sp], f"energies, instance {i}"
+
+
+@pytest.mark.parametrize("reps", [2, 4])
+def test_one_wave_cluster_search_shapes(reps):
+    """Every number of planes per lane (lz 1..16), rows at both halves' ends, axes of one and two
+    sites, open axes and missing bonds, in one context of lattices of at most 16 sites an axis."""
+    shapes = [(16, 16, 16), (2, 16, 5), (16, 1, 13), (5, 2, 4), (3, 3, 9), (1, 7, 16), (15, 15, 12),
+              (8, 8, 1), (9, 16, 8), (4, 5, 2), (1, 1, 3)]
+    insts = [(ej_couplings(s, p, 40 + i)[0], p, None)
+             for i, s in enumerate(shapes) for p in ((7,) if i % 2 else (7, 5))]
+    insts += [(diluted_couplings(s, 7, 80 + i, 0.25), 7, None) for i, s in enumerate(shapes[:4])]
+    _apt_cycles_match(insts, reps, 3, 0.3)
+
+
+@pytest.mark.parametrize("shape,n_inst,h_max", [((10, 10, 10), 1, 0), ((13, 13, 13), 1, 0), ((15, 15, 15), 70, 0),
+                                                ((16, 16, 9), 2, 3)])
+def test_larger_work_groups(shape, n_inst, h_max):
+    """The replica kernel's 512- and 1024-thread forms (few work-groups, phases of several passes):
+    a graph of cycles and single ones, with cluster moves or with fields."""
+    insts = [ej_couplings(shape, 7, 60 + i, h_max=h_max) for i in range(n_inst)]
+    insts = [(J, 7, h) for J, h in insts]
+    _apt_cycles_match(insts[:3] if n_inst < 4 else insts, 2, 34 if n_inst < 4 else 2,
+                      float("inf") if h_max else 0.5)
