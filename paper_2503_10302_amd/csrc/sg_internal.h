@@ -233,11 +233,25 @@ hipError_t launch_advance(uint32_t *ctr, uint32_t d0, uint32_t d1, uint32_t d2, 
                           hipStream_t s);
 
 // MLP kernels (sg_mlp.hip).  Parameters: 6625 floats, then mean[4], std[4].
-hipError_t launch_mlp_pass(const float *P, const float *x, const float *y, const int *idx,
-                           int batch, int nblk, float *grad_acc, float *loss_acc, float *out,
-                           float *grad, hipStream_t s);
-hipError_t launch_mlp_adam2(float *P, const float *g, float *m, float *v, float lr, float b1,
-                            float b2, float eps, int step, hipStream_t s);
+hipError_t launch_mlp_forward(const float *P, const float *x, int n, float *out, hipStream_t s);
+// Loss and gradient over a batch, summed in kMlpGroups groups of consecutive samples (loss: one
+// value per group; grad nullable), then with adam a step on P.  Workspace: records of up to
+// chunk samples and the sums carried between chunks.
+constexpr int kMlpGroups = 64;
+constexpr int kMlpRecFloats = 344;
+constexpr int kMlpChunk = 8192;
+struct MlpWork {
+    float *rec;   // [chunk][kMlpRecFloats]
+    float *acc;   // [2][6625]
+    int chunk;
+};
+struct MlpAdam {
+    float *m, *v;
+    float lr, b1, b2, eps;
+    int step;
+};
+hipError_t launch_mlp_grad(float *P, const float *x, const float *y, const int *idx, int batch,
+                           const MlpWork &w, float *loss, float *grad, const MlpAdam *adam, hipStream_t s);
 // Allocation-free prediction: at most kPredictMax instances per call; the staging area
 // (raw features [kPredictMax][4], then outputs [kPredictMax][33]) is a static device array
 // of the library, one per GPU.  mlp_scratch gives its address on the current device

@@ -22,7 +22,6 @@ using namespace sg;
 namespace {
 constexpr int NP = SG_MLP_NPARAM;
 constexpr int NPX = NP + 8;   // + feature mean[4], std[4]
-constexpr int NBLK = 64;
 
 struct Err {
     sg_status code;
@@ -108,16 +107,33 @@ void features_of(const sg_lattice &L, double *f)
 
 }  // namespace
 
+namespace {
+
+// Room for a batch's records (the stream is idle when it grows).
+void mlp_reserve(MlpWork &w, int batch)
+{
+    const int want = std::min(batch, kMlpChunk);
+    if (w.chunk >= want) return;
+    if (w.rec) (void)hipFree(w.rec);
+    w.rec = nullptr;
+    w.chunk = 0;
+    w.rec = dalloc<float>((size_t)want * kMlpRecFloats);
+    w.chunk = want;
+}
+
+}  // namespace
+
 struct sg_mlp {
     hipStream_t stream = nullptr;
     bool own = false;
-    float *P = nullptr, *m = nullptr, *v = nullptr, *grad = nullptr, *gacc = nullptr, *loss = nullptr;
+    float *P = nullptr, *m = nullptr, *v = nullptr, *grad = nullptr, *loss = nullptr;
+    MlpWork work{nullptr, nullptr, 0};   // grown to the batches seen, at most kMlpChunk records
     int step = 0;
     uint64_t seed = 0;
     float *scratch = nullptr;   // the library's static staging area on this network's GPU
     ~sg_mlp()
     {
-        for (float *p : {P, m, v, grad, gacc, loss})
+        for (float *p : {P, m, v, grad, loss, work.rec, work.acc})
             if (p) (void)hipFree(p);
         if (own && stream) (void)hipStreamDestroy(stream);
     }
@@ -182,8 +198,8 @@ sg_status sg_mlp_create(const float *params, uint64_t seed, void *hip_stream, sg
         m->m = dalloc<float>(NP);
         m->v = dalloc<float>(NP);
         m->grad = dalloc<float>(NP);
-        m->gacc = dalloc<float>((size_t)NBLK * NP);
-        m->loss = dalloc<float>(NBLK);
+        m->loss = dalloc<float>(kMlpGroups);
+        m->work.acc = dalloc<float>((size_t)2 * NP);
         chk(hipMemcpyAsync(m->P, h.data(), sizeof(float) * NPX, hipMemcpyHostToDevice, m->stream));
         chk(hipMemsetAsync(m->m, 0, sizeof(float) * NP, m->stream));
         chk(hipMemsetAsync(m->v, 0, sizeof(float) * NP, m->stream));
@@ -242,10 +258,10 @@ sg_status sg_mlp_loss_grad(sg_mlp *m, const float *x, const float *y, int32_t ba
         dy = dalloc<float>((size_t)batch * 33);
         chk(hipMemcpyAsync(dx, x, sizeof(float) * 4 * batch, hipMemcpyHostToDevice, m->stream));
         chk(hipMemcpyAsync(dy, y, sizeof(float) * 33 * batch, hipMemcpyHostToDevice, m->stream));
-        const int nblk = std::min(NBLK, (int)batch);
-        chk(launch_mlp_pass(m->P, dx, dy, nullptr, batch, nblk, m->gacc, m->loss, nullptr, m->grad,
-                            m->stream));
+        const int nblk = std::min(kMlpGroups, (int)batch);
+        mlp_reserve(m->work, batch);
         std::vector<float> l(nblk);
+        chk(launch_mlp_grad(m->P, dx, dy, nullptr, batch, m->work, m->loss, m->grad, nullptr, m->stream));
         chk(hipMemcpyAsync(l.data(), m->loss, sizeof(float) * nblk, hipMemcpyDeviceToHost, m->stream));
         if (grad) chk(hipMemcpyAsync(grad, m->grad, sizeof(float) * NP, hipMemcpyDeviceToHost, m->stream));
         chk(hipStreamSynchronize(m->stream));
@@ -266,43 +282,73 @@ sg_status sg_mlp_train(sg_mlp *m, const float *x, const float *y, int32_t n, int
                        int32_t epochs, float lr, float *loss_per_epoch)
 {
     if (!m || !x || !y || n < 1 || batch < 1 || epochs < 0 || !(lr > 0.f)) return SG_EINVAL;
-    float *dx = nullptr, *dy = nullptr;
+    float *dx = nullptr, *dy = nullptr, *dloss = nullptr;
     int *didx = nullptr;
+    hipEvent_t ev[2] = {nullptr, nullptr};
+    auto release = [&] {
+        (void)hipFree(dx); (void)hipFree(dy); (void)hipFree(didx); (void)hipFree(dloss);
+        for (hipEvent_t e : ev)
+            if (e) (void)hipEventDestroy(e);
+    };
     try {
+        const int nb = (int)(((int64_t)n + batch - 1) / batch);   // minibatches per epoch
+        const int grp = std::min(kMlpGroups, std::min(batch, n));
+        // losses stay on the device for a run of epochs (64 MB of them at most, or one epoch)
+        const int64_t per_epoch = (int64_t)nb * grp;
+        const int run = (int)std::max<int64_t>(1, std::min<int64_t>(epochs, (16 << 20) / per_epoch));
         dx = dalloc<float>((size_t)n * 4);
         dy = dalloc<float>((size_t)n * 33);
-        didx = dalloc<int>((size_t)n);
+        didx = dalloc<int>((size_t)2 * n);
+        dloss = dalloc<float>((size_t)run * per_epoch);
+        for (hipEvent_t &e : ev) chk(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+        mlp_reserve(m->work, std::min(batch, n));
         chk(hipMemcpyAsync(dx, x, sizeof(float) * 4 * (size_t)n, hipMemcpyHostToDevice, m->stream));
         chk(hipMemcpyAsync(dy, y, sizeof(float) * 33 * (size_t)n, hipMemcpyHostToDevice, m->stream));
-        std::vector<int> order(n);
+        std::vector<int> order(n), sent[2];
         std::iota(order.begin(), order.end(), 0);
         std::mt19937_64 rng(m->seed ^ 0x9E3779B97F4A7C15ull);
-        std::vector<float> l(NBLK);
+        std::vector<float> l;
+        // The host prepares the next epoch (order, launches) while the GPU runs the present one.
         for (int ep = 0; ep < epochs; ++ep) {
             std::shuffle(order.begin(), order.end(), rng);
-            chk(hipStreamSynchronize(m->stream));
-            chk(hipMemcpyAsync(didx, order.data(), sizeof(int) * (size_t)n, hipMemcpyHostToDevice,
+            if (ep >= 2) chk(hipEventSynchronize(ev[ep & 1]));   // that copy has left its buffer
+            sent[ep & 1] = order;
+            int *di = didx + (size_t)(ep & 1) * n;
+            chk(hipMemcpyAsync(di, sent[ep & 1].data(), sizeof(int) * (size_t)n, hipMemcpyHostToDevice,
                                m->stream));
-            double lsum = 0.0;
-            for (int s0 = 0; s0 < n; s0 += batch) {
-                const int b = std::min(batch, n - s0);
-                const int nblk = std::min(NBLK, b);
-                chk(launch_mlp_pass(m->P, dx, dy, didx + s0, b, nblk, m->gacc, m->loss, nullptr,
-                                    m->grad, m->stream));
-                chk(launch_mlp_adam2(m->P, m->grad, m->m, m->v, lr, 0.9f, 0.999f, 1e-8f, ++m->step,
-                                     m->stream));
-                chk(hipMemcpyAsync(l.data(), m->loss, sizeof(float) * nblk, hipMemcpyDeviceToHost,
-                                   m->stream));
-                chk(hipStreamSynchronize(m->stream));
-                for (int k = 0; k < nblk; ++k) lsum += l[k];
+            chk(hipEventRecord(ev[ep & 1], m->stream));
+            const int at = ep % run;
+            for (int k = 0; k < nb; ++k) {
+                const int s0 = k * batch, b = std::min(batch, n - s0);
+                const MlpAdam ad{m->m, m->v, lr, 0.9f, 0.999f, 1e-8f, ++m->step};
+                chk(launch_mlp_grad(m->P, dx, dy, di + s0, b, m->work, dloss + at * per_epoch + (size_t)k * grp,
+                                    nullptr, &ad, m->stream));
             }
-            if (loss_per_epoch) loss_per_epoch[ep] = (float)(lsum / ((double)n * 33.0));
+            if (at + 1 < run && ep + 1 < epochs) continue;
+            // the losses of epochs ep - at .. ep: the groups' sums of their minibatches, in order
+            l.resize((size_t)(at + 1) * per_epoch);
+            chk(hipMemcpyAsync(l.data(), dloss, sizeof(float) * l.size(), hipMemcpyDeviceToHost, m->stream));
+            chk(hipStreamSynchronize(m->stream));
+            for (int e = 0; loss_per_epoch && e <= at; ++e) {
+                double lsum = 0.0;
+                for (int k = 0; k < nb; ++k) {
+                    const int b = std::min(batch, n - k * batch);
+                    for (int q = 0; q < std::min(kMlpGroups, b); ++q) lsum += l[e * per_epoch + (size_t)k * grp + q];
+                }
+                loss_per_epoch[ep - at + e] = (float)(lsum / ((double)n * 33.0));
+            }
         }
+        chk(hipStreamSynchronize(m->stream));
     } catch (const Err &e) {
-        (void)hipFree(dx); (void)hipFree(dy); (void)hipFree(didx);
+        (void)hipStreamSynchronize(m->stream);
+        release();
         return e.code;
+    } catch (const std::bad_alloc &) {
+        (void)hipStreamSynchronize(m->stream);
+        release();
+        return SG_ENOMEM;
     }
-    (void)hipFree(dx); (void)hipFree(dy); (void)hipFree(didx);
+    release();
     return SG_OK;
 }
 
@@ -319,8 +365,7 @@ sg_status sg_ladder_predict(sg_mlp *m, const sg_lattice *inst, int32_t n_inst, d
         dx = dalloc<float>((size_t)n_inst * 4);
         dout = dalloc<float>((size_t)n_inst * 33);
         chk(hipMemcpyAsync(dx, xf.data(), sizeof(float) * xf.size(), hipMemcpyHostToDevice, m->stream));
-        chk(launch_mlp_pass(m->P, dx, nullptr, nullptr, n_inst, std::min(NBLK, (int)n_inst), nullptr,
-                            nullptr, dout, nullptr, m->stream));
+        chk(launch_mlp_forward(m->P, dx, n_inst, dout, m->stream));
         chk(hipMemcpyAsync(out.data(), dout, sizeof(float) * out.size(), hipMemcpyDeviceToHost, m->stream));
         chk(hipStreamSynchronize(m->stream));
     } catch (const Err &e) {
@@ -631,8 +676,7 @@ sg_status sg_ladder_predict_noalloc(sg_mlp *m, const sg_lattice *inst, int32_t n
     float *dx = m->scratch, *dout = m->scratch + (size_t)kPredictMax * 4;
     try {
         chk(hipMemcpyAsync(dx, hx, sizeof(float) * 4 * n, hipMemcpyHostToDevice, m->stream));
-        chk(launch_mlp_pass(m->P, dx, nullptr, nullptr, n_inst, std::min(NBLK, (int)n_inst), nullptr,
-                            nullptr, dout, nullptr, m->stream));
+        chk(launch_mlp_forward(m->P, dx, n_inst, dout, m->stream));
         chk(hipMemcpyAsync(hout, dout, sizeof(float) * 33 * n, hipMemcpyDeviceToHost, m->stream));
         chk(hipStreamSynchronize(m->stream));
     } catch (const Err &e) {

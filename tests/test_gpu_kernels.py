@@ -53,3 +53,24 @@ def test_larger_work_groups(shape, n_inst, h_max):
     insts = [(J, 7, h) for J, h in insts]
     _apt_cycles_match(insts[:3] if n_inst < 4 else insts, 2, 34 if n_inst < 4 else 2,
                       float("inf") if h_max else 0.5)
+
+
+@pytest.mark.parametrize("batch", [1, 63, 64, 65, 130, 8192, 8193])
+def test_mlp_gradient_batch_edges(batch):
+    """Loss and gradient at the edges of the summation groups and of the record chunks against the
+    FP64 oracle.  FP32 sums of n terms are off by at most about n 2^-24 of their absolute sum (in
+    practice by its square root); 2e-5 of the largest entry leaves a factor of some ten."""
+    import ctypes as C
+    from paper_2503_10302_amd import ladder
+    rng = np.random.default_rng(batch)
+    net = ladder.Predictor(seed=3)
+    p = net.params()
+    x = rng.standard_normal((batch, 4)).astype(np.float32)
+    y = rng.standard_normal((batch, 33)).astype(np.float32)
+    loss, grad = C.c_float(0), np.zeros(sg.MLP_NPARAM, np.float32)
+    rc = net.lib.sg_mlp_loss_grad(net.h, x.ctypes.data_as(C.c_void_p), y.ctypes.data_as(C.c_void_p), batch,
+                                  C.byref(loss), grad.ctypes.data_as(C.c_void_p))
+    assert rc == 0
+    oloss, ograd, _ = oracle.mlp_loss_grad(p[:sg.MLP_NPARAM].astype(np.float64), x, y)
+    assert abs(loss.value - oloss) <= 1e-5 * abs(oloss)
+    assert np.abs(grad - ograd).max() <= 2e-5 * np.abs(ograd).max()
