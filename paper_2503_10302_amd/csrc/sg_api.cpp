@@ -2341,7 +2341,47 @@ double sigma_of_moments(int64_t S1, int64_t S2, int64_t N)
 
 }  // namespace
 
-// The adaptive stage with 32 chains per word (adapt_kernel), for instances without
+// Work-group size of adapt_kernel: 1024 threads where no CU gets a second work-group and a phase
+// has more sites than kAdaptThreads (64 instances of L = 15 with 100 chains: 82 -> 75 ms), else
+// kAdaptThreads.
+int adaptive_threads(int64_t work_groups, int phase, int cus)
+{
+    return work_groups <= cus && phase > kAdaptThreads ? 1024 : kAdaptThreads;
+}
+
+// Chain words per instance in adapt_kernel, 0 for the chains as APT slots (a group of four per
+// work-group).  A site costs a work-group about 60 vector instructions and 50 per group, as a
+// tile of APT slots about 110 (its energies included).  A phase takes the longer of its
+// instructions' issue on the CU with the most work-groups and one thread's passes, whose dependent
+// instructions come about 2.5 times slower than they could issue; the cheapest split wins, so few
+// instances are cut into more, shorter words.  Measured against words of 32 chains (and APT slots
+// where those would not give every CU one): 64 instances of L = 15 with 100 chains (words of 7, 6,
+// 6, 6 groups, before 8, 8, 8, 1) 90 -> 75 ms; 4, 16 and 32 instances 1.56, 1.22 and 1.28 times
+// faster; 256 instances the same.
+int adaptive_words(int n_inst, int groups, int phase, int cus, int slot_threads)
+{
+    auto cost = [&](int words, double per_site_max, double per_site, int threads) {
+        const double on_cu = (double)(((int64_t)n_inst * words + cus - 1) / cus);
+        return std::max(on_cu * std::max(phase, 256) / 256.0 * per_site,
+                        2.5 * ((phase + threads - 1) / threads) * per_site_max);
+    };
+    int best = 0;
+    double best_cost = cost(groups, 110.0, 110.0, slot_threads);
+    for (int ng = 8; ng >= 2; --ng) {
+        const int nw = (groups + ng - 1) / ng;
+        const int top = (groups + nw - 1) / nw;   // groups of the fullest word
+        if (top < 2) continue;
+        const double c = cost(nw, 60.0 + 50.0 * top, 60.0 + 50.0 * groups / nw,
+                              adaptive_threads((int64_t)n_inst * nw, phase, cus));
+        if (c < best_cost) {
+            best_cost = c;
+            best = nw;
+        }
+    }
+    return best;
+}
+
+// The adaptive stage with up to 32 chains per word (adapt_kernel), for instances without
 // fields.  Returns false, having done nothing, when it does not apply; the caller then
 // runs the chains as APT slots.
 bool adaptive_packed(sg_ctx *c, const sg_adaptive_params *p, double *beta_out,
@@ -2353,21 +2393,22 @@ bool adaptive_packed(sg_ctx *c, const sg_adaptive_params *p, double *beta_out,
         max_npad = std::max(max_npad, I.npad);
         max_n = std::max(max_n, I.n);
     }
-    const int per_thread = 3 * ((max_n + kAdaptThreads - 1) / kAdaptThreads);
+    const int n_inst = c->n_inst, nc = p->n_chains, groups = (nc + 3) / 4;
+    int dev = 0, cus = 0;
+    hip_check(hipGetDevice(&dev), "device");
+    hip_check(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev), "device");
+    int phase = 0;   // sites of the largest colour class
+    for (const InstDev &I : c->idev) phase = std::max(phase, *std::max_element(I.col_cnt, I.col_cnt + 4));
+    const int nw = adaptive_words(n_inst, groups, phase, cus, c->quad_threads);
+    if (nw == 0) return false;
+    const int nt = adaptive_threads((int64_t)n_inst * nw, phase, cus);
+    const int per_thread = 3 * ((max_n + nt - 1) / nt);
     int planes = 1;
     while ((1 << planes) <= per_thread) ++planes;
     const size_t lds = sizeof(uint32_t) * (size_t)(max_npad + 1);
     // + the kernel's static LDS: tables, energy counters, reduction scratch
-    const size_t lds_static =
-        sizeof(uint32_t) * (kAdaptTabWords + kAdaptPlanes * kAdaptThreads + kAdaptRedWords + 64);
+    const size_t lds_static = sizeof(uint32_t) * (kAdaptTabWords + kAdaptPlanes * nt + nt / 2 + 1 + 64);
     if (planes > kAdaptPlanes || lds + lds_static > kMaxLds) return false;
-    const int n_inst = c->n_inst, nc = p->n_chains, nw = (nc + 31) / 32;
-    // one work-group per (instance, chain word): with fewer work-groups than CUs the
-    // chains spread wider as APT slots (four per work-group)
-    int dev = 0, cus = 0;
-    hip_check(hipGetDevice(&dev), "device");
-    hip_check(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev), "device");
-    if ((int64_t)n_inst * nw < cus) return false;
     hipStream_t s = c->stream;
     AdaptArgs a{};
     a.inst = c->d_inst.p;
@@ -2384,6 +2425,9 @@ bool adaptive_packed(sg_ctx *c, const sg_adaptive_params *p, double *beta_out,
     a.n_inst = n_inst;
     a.n_chains = nc;
     a.nw = nw;
+    a.threads = nt;
+    a.ng = (groups + nw - 1) / nw;
+    a.n_full = groups - nw * (a.ng - 1);
     a.imax = c->imax;
     a.ni = c->ni;
     a.planes = planes;

@@ -182,13 +182,12 @@ struct SqaArgs {
 
 constexpr int kSqaPlanes = 10;   // bits of the readout's per-thread unsatisfied-bond counters
 
-// Adaptive-ladder stage with the chains bit-packed: word w of a site holds chains
-// 32 w .. 32 w + 31 of its instance (bit b = chain 32 w + b; 1 = up), all at the
-// instance's current beta.  Fields must be zero (energies count unsatisfied bonds).
+// Adaptive-ladder stage with the chains bit-packed: a word of a site holds consecutive chains
+// of its instance, in up to eight groups of four (bit b = the word's chain b; 1 = up), all at
+// the instance's current beta.  Fields must be zero (energies count unsatisfied bonds).
 constexpr int kAdaptThreads = 512;
 constexpr int kAdaptPlanes = 10;   // bits of the per-thread unsatisfied-bond counters
 constexpr int kAdaptTabWords = 256 + 16 + 64;            // static tables of adapt_kernel
-constexpr int kAdaptRedWords = kAdaptThreads / 64 * 32 + 1;   // its reduction scratch
 struct AdaptArgs {
     const InstDev *inst;
     const uint4 *rec_col;      // colour-sorted site records
@@ -198,6 +197,8 @@ struct AdaptArgs {
     int64_t *mom;              // [inst][n_chains][2]: sum of E, sum of E^2 over the tail
     int64_t wstride;           // words per (instance, word) block, >= npad + 1
     uint32_t t0;               // sweep counter of the launch's first sweep
+    int32_t threads;           // work-group size: kAdaptThreads or 1024
+    int32_t ng, n_full;        // groups of the first n_full words; the others hold ng - 1
     int32_t n_inst, n_chains, nw, n_sweeps, mom_from, imax, ni, planes;
     uint32_t key0, key1;
 };

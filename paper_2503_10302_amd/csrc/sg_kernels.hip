@@ -2283,33 +2283,31 @@ __global__ void best_key_energy_kernel(const uint64_t *key, int n, int64_t *out)
 // Adaptive-ladder stage (Methods, APT details): all chains of an instance run at the
 // instance's current beta, so 32 of them share one word per site and one threshold
 // row, and the aligned-neighbour count is summed bit-sliced as in the DT-SQA kernel.
-// One work-group per (instance, word of 32 chains); the words stay in LDS for all
-// sweeps of a launch.  Chain c = 32 w + 4 g + i takes word i of the Philox block
-// (site, sweep, 8 w + g, instance) -- the counter of slot c in the APT sweep.
+// One work-group per (instance, word of up to 32 chains); the words stay in LDS for all
+// sweeps of a launch.  The chains come in groups of four, chain c = 4 q + i in group q; an
+// instance's groups are split evenly over its words (adapt_word).  Chain c takes word i of the
+// Philox block (site, sweep, q, instance) -- the counter of slot c in the APT sweep.
 // ---------------------------------------------------------------------------
 // New states of the chains of one word at one site (heat-bath rule of Eq. 6 at the
-// instance's beta): chain 4 g + i takes word i of the Philox block (j, t, 8 w + g,
-// instance) of group g (rounds 0-1 split as in sqa_slices: D, C, E of the site, ug[g] of the
+// instance's beta): chain 4 g + i takes word i of the Philox block (j, t, first + g,
+// instance) of the word's group g (rounds 0-1 split as in sqa_slices: D, C, E of the site, ug[g] of the
 // group and sweep); its threshold index is a byte of the sum of a pair-table read
 // (planes c0, c1) and a 16-entry table read (plane c2), relative to lsite, the row moved
 // by the site's field and degree.  Groups run from the highest to the lowest so that the
 // borrow chain leaves chain b at bit b; the table reads of group g - 1 and the threshold
-// reads of group g are issued before group g's Philox block.  NG > 0: NG groups,
-// unrolled; NG == 0: ngrp groups, not unrolled.
+// reads of group g are issued before group g's Philox block.  NG groups, unrolled.
 template <int NG>
 __device__ __forceinline__ uint32_t adapt_groups(const uint32_t *lsite, const uint32_t *tab01,
                                                  const uint32_t *tab2, uint32_t e01, uint32_t o01,
                                                  uint32_t c2, uint32_t D, uint32_t C, uint32_t E,
-                                                 const uint4 *ug, uint32_t k0, uint32_t k1,
-                                                 int ngrp)
+                                                 const uint4 *ug, uint32_t k0, uint32_t k1)
 {
-    const int ng = NG > 0 ? NG : ngrp;
     uint32_t res = 0u;
-    uint32_t s0v = lds_word(tab01, pair_off(e01, o01, ng - 1));
-    uint32_t s1v = lds_word(tab2, nib_off(c2, ng - 1));
-    uint4 U = ug[ng - 1];
+    uint32_t s0v = lds_word(tab01, pair_off(e01, o01, NG - 1));
+    uint32_t s1v = lds_word(tab2, nib_off(c2, NG - 1));
+    uint4 U = ug[NG - 1];
 #pragma unroll
-    for (int g = ng - 1; g >= 0; --g) {
+    for (int g = NG - 1; g >= 0; --g) {
         const uint32_t idx4 = s0v + s1v;
         const uint32_t T3 = lds_word(lsite, idx4 >> 24);
         const uint32_t T2 = lds_word(lsite, (idx4 >> 16) & 0xFFu);
@@ -2340,13 +2338,13 @@ __device__ __forceinline__ uint32_t adapt_groups(const uint32_t *lsite, const ui
 
 // One colour phase of the adaptive stage's sweep: the sites of the phase are split over
 // the work-group's threads; each updates all chains of the word at its sites.
-template <int NG>
+template <int NG, int NT>
 __device__ __forceinline__ void adapt_phase(const AdaptArgs &A, const uint4 *rc, int cnt,
                                             uint32_t *sp, const uint32_t *tab01,
                                             const uint32_t *tab2, const uint32_t *lut,
-                                            const uint4 *ug, uint32_t c3, int ng, uint32_t vmask)
+                                            const uint4 *ug, uint32_t c3, uint32_t vmask)
 {
-    for (int i = threadIdx.x; i < cnt; i += kAdaptThreads) {
+    for (int i = threadIdx.x; i < cnt; i += NT) {
         const uint4 r = rc[i];
         const uint32_t j = r.x & 0xFFFFu, jn = r.x >> 19;
         // aligned words: bit b = 1 when J s_neighbour = +1 for chain b
@@ -2371,44 +2369,52 @@ __device__ __forceinline__ void adapt_phase(const AdaptArgs &A, const uint4 *rc,
         const uint64_t pb = (uint64_t)0xCD9E8D57u * B;
         const uint32_t res = adapt_groups<NG>(lsite, tab01, tab2, e01, o01, c2,
                                               (uint32_t)(pb >> 32), (uint32_t)pj, (uint32_t)pb, ug,
-                                              A.key0, A.key1, ng);
+                                              A.key0, A.key1);
         sp[j] = res & vmask;
     }
 }
 
-// Work-group -> (instance, chain word).  When the last word of each instance holds fewer
-// than 32 chains (one to seven Philox groups against eight), the full words come first
-// and the short ones last: work-groups are handed to the eight XCDs in turn, so with the
-// natural order (instance-major) every short word of a four-word instance would land on
-// two of the eight XCDs and the full ones on the other six.
-__device__ __forceinline__ void adapt_block(const AdaptArgs &A, int b, int &inst, int &w)
+// Work-group -> (instance, chain word) and the word's groups: the first n_full words of an
+// instance hold ng groups, the others ng - 1 (so that all work-groups take about the same time).
+// The fuller words come first: work-groups are handed to the eight XCDs in turn, and with the
+// natural order (instance-major) the fuller words of an instance would land on few of them.
+struct AdaptWord {
+    int inst, w, first, ng, nch;   // first group, groups and chains of the word
+};
+
+__device__ __forceinline__ AdaptWord adapt_word(const AdaptArgs &A, int b)
 {
-    const int nf = A.nw - 1;
-    if ((A.n_chains & 31) == 0 || nf == 0) {
-        inst = b / A.nw;
-        w = b - inst * A.nw;
-    } else if (b < A.n_inst * nf) {
-        inst = b / nf;
-        w = b - inst * nf;
+    AdaptWord W;
+    const int nf = A.n_full, nr = A.nw - nf;
+    if (b < A.n_inst * nf) {
+        W.inst = b / nf;
+        W.w = b - W.inst * nf;
+        W.ng = A.ng;
+        W.first = W.w * A.ng;
     } else {
-        inst = b - A.n_inst * nf;
-        w = nf;
+        b -= A.n_inst * nf;
+        W.inst = b / nr;
+        const int r = b - W.inst * nr;
+        W.w = nf + r;
+        W.ng = A.ng - 1;
+        W.first = nf * A.ng + r * (A.ng - 1);
     }
+    W.nch = min(4 * W.ng, A.n_chains - 4 * W.first);
+    return W;
 }
 
 __global__ __launch_bounds__(kAdaptThreads) void adapt_init_kernel(AdaptArgs A)
 {
-    int inst, w;
-    adapt_block(A, blockIdx.x, inst, w);
-    const InstDev I = A.inst[inst];
-    const int nch = min(32, A.n_chains - 32 * w), ng = (nch + 3) >> 2;
-    const uint32_t c3 = ((uint32_t)inst << 4) | TAG_ADAPT_INIT;
-    uint32_t *g = A.words + ((int64_t)inst * A.nw + w) * A.wstride;
+    const AdaptWord W = adapt_word(A, blockIdx.x);
+    const InstDev I = A.inst[W.inst];
+    const int nch = W.nch;
+    const uint32_t c3 = ((uint32_t)W.inst << 4) | TAG_ADAPT_INIT;
+    uint32_t *g = A.words + ((int64_t)W.inst * A.nw + W.w) * A.wstride;
     for (int j = threadIdx.x; j < (int)A.wstride; j += kAdaptThreads) {
         uint32_t wd = 0u;
         if (j < I.n)
-            for (int gq = 0; gq < ng; ++gq) {
-                const uint4 u = philox10((uint32_t)j, 0u, (uint32_t)(8 * w + gq), c3, A.key0, A.key1);
+            for (int gq = 0; gq < W.ng; ++gq) {
+                const uint4 u = philox10((uint32_t)j, 0u, (uint32_t)(W.first + gq), c3, A.key0, A.key1);
                 const uint32_t us[4] = {u.x, u.y, u.z, u.w};
                 for (int i = 0; i < 4; ++i)
                     if (4 * gq + i < nch && us[i] < 0x80000000u) wd |= 1u << (4 * gq + i);
@@ -2417,27 +2423,29 @@ __global__ __launch_bounds__(kAdaptThreads) void adapt_init_kernel(AdaptArgs A)
     }
 }
 
-__global__ __launch_bounds__(kAdaptThreads) void adapt_kernel(AdaptArgs A)
+// NG: groups of the fuller words.  NT: 512 threads, or 1024 where every CU has one work-group at
+// most and a phase more sites than threads.
+template <int NG, int NT>
+__global__ __launch_bounds__(NT) void adapt_kernel(AdaptArgs A)
 {
     // Static LDS: pair spread table of planes c0, c1 (256), spread table of c2 (16),
     // threshold row (<= 64), per-thread counters for the energies, reduction scratch.
     __shared__ uint32_t tabs[kAdaptTabWords];
-    __shared__ uint32_t vc[kAdaptPlanes * kAdaptThreads];
-    constexpr int kWaves = kAdaptThreads / 64;
-    __shared__ int32_t red[kAdaptRedWords];
+    __shared__ uint32_t vc[kAdaptPlanes * NT];
+    constexpr int kWaves = NT / 64;
+    __shared__ int32_t red[kWaves * 32 + 1];
     // group words of Philox rounds 0-1 (sqa_group_words) by sweep parity and group
     __shared__ __align__(16) uint4 ugrp[2 * 8];
     extern __shared__ uint32_t sp[];   // npad + 1 words, the last one the zero dummy
-    int inst, w;
-    adapt_block(A, blockIdx.x, inst, w);
+    const AdaptWord W = adapt_word(A, blockIdx.x);
+    const int inst = W.inst, nch = W.nch, ng = W.ng;
     const InstDev I = A.inst[inst];
     const int tid = threadIdx.x, n = I.n, npad = I.npad;
-    const int nch = min(32, A.n_chains - 32 * w), ng = (nch + 3) >> 2;
     const uint32_t vmask = nch >= 32 ? 0xFFFFFFFFu : ((1u << nch) - 1u);
-    uint32_t *gw = A.words + ((int64_t)inst * A.nw + w) * A.wstride;
-    for (int i = tid; i <= npad; i += kAdaptThreads) sp[i] = i < npad ? gw[i] : 0u;
+    uint32_t *gw = A.words + ((int64_t)inst * A.nw + W.w) * A.wstride;
+    for (int i = tid; i <= npad; i += NT) sp[i] = i < npad ? gw[i] : 0u;
     uint32_t *tab01 = tabs, *tab2 = tabs + 256, *lut = tabs + 272;
-    for (int e = tid; e < 272; e += kAdaptThreads) {
+    for (int e = tid; e < 272; e += NT) {
         // bit i of a nibble -> byte i; table index = I + imax = 2 k + (h - d + imax), k =
         // c0 + 2 c1 + 4 c2, stored times 4 (byte offsets into the threshold row)
         auto spread = [](uint32_t nib) {
@@ -2446,23 +2454,23 @@ __global__ __launch_bounds__(kAdaptThreads) void adapt_kernel(AdaptArgs A)
         const uint32_t lo = (uint32_t)e & 15u, hi = ((uint32_t)e >> 4) & 15u;
         tabs[e] = e < 256 ? 8u * spread(lo) + 16u * spread(hi) : 32u * spread(lo);
     }
-    for (int i = tid; i < A.ni; i += kAdaptThreads) lut[i] = A.lut[(int64_t)inst * A.ni + i];
+    for (int i = tid; i < A.ni; i += NT) lut[i] = A.lut[(int64_t)inst * A.ni + i];
     // bonds along +x, +y, +z present (J != 0): E = 2 (unsatisfied) - bonds
     if (tid == 0) red[kWaves * 32] = 0;
     __syncthreads();
     int32_t nbc = 0;
-    for (int j = tid; j < n; j += kAdaptThreads) {
+    for (int j = tid; j < n; j += NT) {
         const uint4 r = A.rec_j[I.recj_off + j];
         nbc += ((r.y & 0xFFFFu) != (uint32_t)n) + ((r.z & 0xFFFFu) != (uint32_t)n) +
                ((r.w & 0xFFFFu) != (uint32_t)n);
     }
     if (A.n_sweeps > 0 && tid < ng)
-        ugrp[tid] = sqa_group_words(A.t0, 8u * (uint32_t)w + (uint32_t)tid, A.key0, A.key1);
+        ugrp[tid] = sqa_group_words(A.t0, (uint32_t)(W.first + tid), A.key0, A.key1);
     atomicAdd(&red[kWaves * 32], nbc);
     __syncthreads();
     const int32_t bonds = red[kWaves * 32];
     const uint32_t c3 = ((uint32_t)inst << 4) | TAG_ADAPT_SWEEP;
-    int64_t S1 = 0, S2 = 0;   // moments of chain 32 w + tid (threads < nch)
+    int64_t S1 = 0, S2 = 0;   // moments of the word's chain tid (threads < nch)
     for (int sw = 0; sw < A.n_sweeps; ++sw) {
         const uint32_t t = A.t0 + (uint32_t)sw;
         const uint4 *ug = ugrp + 8 * (sw & 1);
@@ -2471,13 +2479,11 @@ __global__ __launch_bounds__(kAdaptThreads) void adapt_kernel(AdaptArgs A)
             // sweep's phases, are past a barrier)
             if (c == 0 && sw + 1 < A.n_sweeps && tid < ng)
                 ugrp[8 * ((sw + 1) & 1) + tid] =
-                    sqa_group_words(t + 1u, 8u * (uint32_t)w + (uint32_t)tid, A.key0, A.key1);
+                    sqa_group_words(t + 1u, (uint32_t)(W.first + tid), A.key0, A.key1);
             const uint4 *rc = A.rec_col + I.rec_off + A.inst[inst].col_off[c];
             const int cnt = A.inst[inst].col_cnt[c];
-            if (ng == 8)
-                adapt_phase<8>(A, rc, cnt, sp, tab01, tab2, lut, ug, c3, ng, vmask);
-            else
-                adapt_phase<0>(A, rc, cnt, sp, tab01, tab2, lut, ug, c3, ng, vmask);
+            if (ng == NG) adapt_phase<NG, NT>(A, rc, cnt, sp, tab01, tab2, lut, ug, c3, vmask);
+            else adapt_phase<NG - 1, NT>(A, rc, cnt, sp, tab01, tab2, lut, ug, c3, vmask);
             __syncthreads();
         }
         if (sw >= A.mom_from) {
@@ -2486,7 +2492,7 @@ __global__ __launch_bounds__(kAdaptThreads) void adapt_kernel(AdaptArgs A)
             uint32_t v[kAdaptPlanes];
 #pragma unroll
             for (int p = 0; p < kAdaptPlanes; ++p) v[p] = 0u;
-            for (int j = tid; j < n; j += kAdaptThreads) {
+            for (int j = tid; j < n; j += NT) {
                 const uint4 r = A.rec_j[I.recj_off + j];
                 const uint32_t jn = r.x >> 19, wj = sp[j];
                 const uint32_t nbf[3] = {r.y & 0xFFFFu, r.z & 0xFFFFu, r.w & 0xFFFFu};
@@ -2505,7 +2511,7 @@ __global__ __launch_bounds__(kAdaptThreads) void adapt_kernel(AdaptArgs A)
             }
 #pragma unroll
             for (int p = 0; p < kAdaptPlanes; ++p)
-                if (p < A.planes) vc[p * kAdaptThreads + tid] = v[p];
+                if (p < A.planes) vc[p * NT + tid] = v[p];
             __syncthreads();
             // chain cc, sources part * 32 .. part * 32 + 31
             const int cc = tid & 31, part = tid >> 5;
@@ -2513,7 +2519,7 @@ __global__ __launch_bounds__(kAdaptThreads) void adapt_kernel(AdaptArgs A)
             for (int src = part * 32; src < part * 32 + 32; ++src)
 #pragma unroll
                 for (int p = 0; p < kAdaptPlanes; ++p)
-                    if (p < A.planes) cntu += (int32_t)(((vc[p * kAdaptThreads + src] >> cc) & 1u) << p);
+                    if (p < A.planes) cntu += (int32_t)(((vc[p * NT + src] >> cc) & 1u) << p);
             cntu += __shfl_xor(cntu, 32, 64);
             if ((tid & 63) < 32) red[(tid >> 6) * 32 + cc] = cntu;
             __syncthreads();
@@ -2528,9 +2534,9 @@ __global__ __launch_bounds__(kAdaptThreads) void adapt_kernel(AdaptArgs A)
             __syncthreads();
         }
     }
-    for (int i = tid; i < npad; i += kAdaptThreads) gw[i] = sp[i];
+    for (int i = tid; i < npad; i += NT) gw[i] = sp[i];
     if (tid < nch) {
-        int64_t *m = A.mom + ((int64_t)inst * A.n_chains + 32 * w + tid) * 2;
+        int64_t *m = A.mom + ((int64_t)inst * A.n_chains + 4 * W.first + tid) * 2;
         m[0] = S1;
         m[1] = S2;
     }
@@ -2681,12 +2687,34 @@ hipError_t launch_adapt_init(const AdaptArgs &a, int n_inst, hipStream_t s)
     return hipGetLastError();
 }
 
+template <int NG, int NT>
+hipError_t launch_adapt_t(const AdaptArgs &a, int n_inst, size_t lds_bytes, hipStream_t s)
+{
+    hipError_t e = allow_lds((const void *)adapt_kernel<NG, NT>, lds_bytes);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((adapt_kernel<NG, NT>), dim3(n_inst * a.nw), dim3(NT), lds_bytes, s, a);
+    return hipGetLastError();
+}
+
+template <int NG>
+hipError_t launch_adapt_g(const AdaptArgs &a, int n_inst, size_t lds_bytes, hipStream_t s)
+{
+    return a.threads == 1024 ? launch_adapt_t<NG, 1024>(a, n_inst, lds_bytes, s)
+                             : launch_adapt_t<NG, kAdaptThreads>(a, n_inst, lds_bytes, s);
+}
+
 hipError_t launch_adapt(const AdaptArgs &a, int n_inst, size_t lds_bytes, hipStream_t s)
 {
-    hipError_t e = allow_lds((const void *)adapt_kernel, lds_bytes);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(adapt_kernel, dim3(n_inst * a.nw), dim3(kAdaptThreads), lds_bytes, s, a);
-    return hipGetLastError();
+    switch (a.ng) {
+    case 2: return launch_adapt_g<2>(a, n_inst, lds_bytes, s);
+    case 3: return launch_adapt_g<3>(a, n_inst, lds_bytes, s);
+    case 4: return launch_adapt_g<4>(a, n_inst, lds_bytes, s);
+    case 5: return launch_adapt_g<5>(a, n_inst, lds_bytes, s);
+    case 6: return launch_adapt_g<6>(a, n_inst, lds_bytes, s);
+    case 7: return launch_adapt_g<7>(a, n_inst, lds_bytes, s);
+    case 8: return launch_adapt_g<8>(a, n_inst, lds_bytes, s);
+    }
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_advance(uint32_t *ctr, uint32_t d0, uint32_t d1, uint32_t d2, uint32_t d3,

@@ -74,3 +74,18 @@ def test_mlp_gradient_batch_edges(batch):
     oloss, ograd, _ = oracle.mlp_loss_grad(p[:sg.MLP_NPARAM].astype(np.float64), x, y)
     assert abs(loss.value - oloss) <= 1e-5 * abs(oloss)
     assert np.abs(grad - ograd).max() <= 2e-5 * np.abs(ograd).max()
+
+
+@pytest.mark.parametrize("shape,n_inst,n_chains", [((3, 4, 2), 520, 8), ((3, 4, 2), 520, 11), ((4, 3, 3), 520, 16),
+                                                   ((2, 3, 4), 520, 20), ((3, 4, 2), 520, 24), ((3, 3, 2), 520, 25),
+                                                   ((3, 4, 2), 520, 32), ((3, 2, 2), 300, 100),
+                                                   ((12, 12, 12), 12, 100)])
+def test_adaptive_word_splits(shape, n_inst, n_chains):
+    """Every number of groups per chain word of the adaptive kernel (2 to 8, words with one group
+    less beside them, a last group that is not full) and its 1024-thread form."""
+    insts = [(ej_couplings(shape, 7, 300 + i)[0], 7, None) for i in range(n_inst)]
+    kw = dict(beta0=0.4, alpha=1.25, tol=0.01, n_chains=n_chains, sweeps=5, tail=3, max_steps=2)
+    got = sg.adaptive_ladder(insts, 21, **kw)
+    for i in range(0, n_inst, max(1, n_inst // 40)):
+        beta, sigma = oracle.adaptive_ladder(oracle.Lattice(*insts[i]), i, 21, **kw)[:2]
+        assert np.array_equal(got[i][0], beta) and np.array_equal(got[i][1], sigma), f"instance {i}"
