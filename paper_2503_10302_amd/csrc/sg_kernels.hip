@@ -1766,26 +1766,25 @@ __device__ __forceinline__ uint32_t pair_off(uint32_t ev, uint32_t od, int g)
 // and step, U = {U1, U2, U3} from ug[g] (sqa_group_words), after which the state of round 2
 // is (D ^ U1, E, C ^ U2, .) and round 2's second XOR pair takes U3.  SCALED: table indices
 // are stored pre-multiplied by 4 (byte offsets), possible when the table has <= 64 rows.
-// NG > 0: NG groups, unrolled; NG == 0: ngrp groups, not unrolled.
-template <int NG, bool SCALED>
+// Groups G0 .. NG - 1, unrolled; bits below 4 G0 of the result are 0.
+template <int NG, bool SCALED, int G0 = 0>
 __device__ __forceinline__ uint32_t sqa_slices(const uint32_t *lut, const uint32_t *tab01,
                                                const uint32_t *tab2t, const uint32_t *tab1,
                                                uint32_t e01, uint32_t o01, uint32_t e2t,
                                                uint32_t o2t, uint32_t t1b, uint32_t D,
                                                uint32_t C, uint32_t E, const uint4 *ug,
-                                               uint32_t k0, uint32_t k1, int ngrp)
+                                               uint32_t k0, uint32_t k1)
 {
     uint32_t res = 0u;
-    const int ng = NG > 0 ? NG : ngrp;
     // Software pipeline: the spread-table reads of group g - 1 and the threshold reads
     // of group g are issued before group g's Philox block, whose arithmetic covers
     // their LDS latency.
-    uint32_t s0 = lds_word(tab01, pair_off(e01, o01, ng - 1));
-    uint32_t s1 = lds_word(tab2t, pair_off(e2t, o2t, ng - 1));
-    uint32_t s2 = lds_word(tab1, nib_off(t1b, ng - 1));
-    uint4 U = ug[ng - 1];
+    uint32_t s0 = lds_word(tab01, pair_off(e01, o01, NG - 1));
+    uint32_t s1 = lds_word(tab2t, pair_off(e2t, o2t, NG - 1));
+    uint32_t s2 = lds_word(tab1, nib_off(t1b, NG - 1));
+    uint4 U = ug[NG - 1];
 #pragma unroll
-    for (int g = ng - 1; g >= 0; --g) {
+    for (int g = NG - 1; g >= G0; --g) {
         const uint32_t idx4 = s0 + s1 + s2;
         uint32_t o0, o1, o2, o3;
         if (SCALED) {
@@ -1802,7 +1801,7 @@ __device__ __forceinline__ uint32_t sqa_slices(const uint32_t *lut, const uint32
         const uint32_t T3 = lds_word(lut, o3), T2 = lds_word(lut, o2);
         const uint32_t T1 = lds_word(lut, o1), T0 = lds_word(lut, o0);
         const uint4 Ug = U;
-        if (g > 0) {
+        if (g > G0) {
             s0 = lds_word(tab01, pair_off(e01, o01, g - 1));
             s1 = lds_word(tab2t, pair_off(e2t, o2t, g - 1));
             s2 = lds_word(tab1, nib_off(t1b, g - 1));
@@ -1822,7 +1821,7 @@ __device__ __forceinline__ uint32_t sqa_slices(const uint32_t *lut, const uint32
         res = shift_in_lt(res, x[1], T1);
         res = shift_in_lt(res, x[0], T0);
     }
-    return res;
+    return G0 > 0 ? res << (4 * G0) : res;
 }
 
 // The group-and-step part of the first two Philox rounds of sqa_slices for counter
@@ -1843,14 +1842,15 @@ __device__ __forceinline__ uint4 sqa_group_words(uint32_t t, uint32_t x2, uint32
 // six spatial neighbours, the number of up Trotter neighbours from the other parity's word,
 // then sqa_slices.  ODD (an odd number M of slices, H = (M + 1) / 2): word 0 holds H slices and
 // word 1 H - 1; the ring closes between slice M - 1 (bit H - 1 of word 0) and slice 0 (bit 0),
-// so word 0's Trotter neighbours come partly from word 0 itself, and only the bits in umask
-// are written (the rest keep their values: they belong to other phases).
-template <int NG, bool SCALED, int P, bool ODD = false>
+// so word 0's Trotter neighbours come partly from word 0 itself, and only the bits in umask,
+// all in groups G0 .. NG - 1, are written (the rest keep their values: they belong to other
+// phases).
+template <int NG, bool SCALED, int P, bool ODD = false, int G0 = 0>
 __device__ __forceinline__ void sqa_site(const SqaArgs &A, const uint4 rr, uint32_t *sp,
                                          const uint32_t *lrow, const uint32_t *tab01,
                                          const uint32_t *tab2t, const uint32_t *tab1,
                                          uint32_t mask, int H, const uint4 *ug, uint32_t c3,
-                                         int ngrp, uint32_t umask = 0u)
+                                         uint32_t umask = 0u)
 {
     const uint32_t j = rr.x & 0xFFFFu;
     const uint32_t jn = rr.x >> 19;
@@ -1902,9 +1902,9 @@ __device__ __forceinline__ void sqa_site(const SqaArgs &A, const uint4 rr, uint3
     const uint64_t pj = (uint64_t)0xD2511F53u * ((j << 1) | (uint32_t)P);
     const uint32_t B = (uint32_t)(pj >> 32) ^ c3 ^ A.key1;
     const uint64_t pb = (uint64_t)0xCD9E8D57u * B;
-    const uint32_t res = sqa_slices<NG, SCALED>(lsite, tab01, tab2t, tab1, e01, o01, e2t, o2t,
-                                                t1b, (uint32_t)(pb >> 32), (uint32_t)pj,
-                                                (uint32_t)pb, ug, A.key0, A.key1, ngrp);
+    const uint32_t res = sqa_slices<NG, SCALED, G0>(lsite, tab01, tab2t, tab1, e01, o01, e2t, o2t,
+                                                    t1b, (uint32_t)(pb >> 32), (uint32_t)pj,
+                                                    (uint32_t)pb, ug, A.key0, A.key1);
     if constexpr (ODD)
         sp[2 * j + P] = (sp[2 * j + P] & ~umask) | (res & umask);
     else
@@ -1990,8 +1990,11 @@ __device__ __forceinline__ int32_t sqa_disagree_counts(const uint32_t *g, int n,
 }
 
 // The work-group size is a launch-time choice (a multiple of 64, at most 1024);
-// waves are limited to 64 VGPRs (8 waves per SIMD).
-template <int NG, bool SCALED>
+// waves are limited to 64 VGPRs (8 per SIMD).  NG: groups of four slices per word, unrolled for
+// every number of slices (against a loop over the groups: eight 15 x 15 x 12 instances with fields,
+// M = 48, 3.1 -> 2.85 ms for 40 steps; eight L = 10 ones, M = 63, 2.5 -> 1.7 ms);
+// ODD: an odd number of slices.
+template <int NG, bool SCALED, bool ODD>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8)))
 void sqa_kernel(SqaArgs A)
 {
@@ -2034,8 +2037,7 @@ void sqa_kernel(SqaArgs A)
         tabs[256 + e] = (SCALED ? 4u : 1u) * v;
     }
     const uint32_t c3 = ((uint32_t)inst << 4) | TAG_SQA_SWEEP;
-    const int ngrp = (H + 3) >> 2;
-    if (A.n_steps > 0 && tid < ngrp)
+    if (A.n_steps > 0 && tid < NG)
         ugrp[tid] = sqa_group_words((uint32_t)A.t0, ((uint32_t)r << 16) | (uint32_t)tid, A.key0,
                                     A.key1);
     // Threshold rows: a table of <= 128 entries is double-buffered, the next step's
@@ -2061,7 +2063,7 @@ void sqa_kernel(SqaArgs A)
             if (dbuf && c == 0 && st + 1 < A.n_steps)
                 for (int i = tid; i < A.nl; i += THREADS)
                     lut[128 * ((st + 1) & 1) + i] = A.lut[(int64_t)(A.lut_step0 + st + 1) * A.nl + i];
-            if (c == 0 && st + 1 < A.n_steps && tid < ngrp)
+            if (c == 0 && st + 1 < A.n_steps && tid < NG)
                 ugrp[8 * ((st + 1) & 1) + tid] = sqa_group_words(
                     t + 1u, ((uint32_t)r << 16) | (uint32_t)tid, A.key0, A.key1);
             const uint4 *rc = A.rec + I.rec_off + A.inst[inst].col_off[c];
@@ -2070,30 +2072,25 @@ void sqa_kernel(SqaArgs A)
             // the boundary, so only the wave that straddles it runs both bodies)
             const int n0 = A.inst[inst].col_p1[c];
             int i = tid;
-            if constexpr (NG == 0) {
-                if (A.M & 1) {
-                    // odd M: word 0 but its last slice, word 1, then the last slice alone
-                    const int n2 = A.inst[inst].col_p2[c];
-                    const uint32_t last = 1u << (H - 1);
-                    for (; i < n0; i += THREADS)
-                        sqa_site<0, SCALED, 0, true>(A, rc[i], sp, lrow, tab01, tab2t, tab1, mask,
-                                                     H, ug, c3, ngrp, mask & ~last);
-                    for (; i < n2; i += THREADS)
-                        sqa_site<0, SCALED, 1, true>(A, rc[i], sp, lrow, tab01, tab2t, tab1, mask,
-                                                     H, ug, c3, ngrp, mask >> 1);
-                    for (; i < cnt; i += THREADS)
-                        sqa_site<0, SCALED, 0, true>(A, rc[i], sp, lrow, tab01, tab2t, tab1, mask,
-                                                     H, ug, c3, ngrp, last);
-                    __syncthreads();
-                    continue;
-                }
+            if constexpr (ODD) {
+                // word 0 but its last slice, word 1, then the last slice alone (in the last group)
+                const int n2 = A.inst[inst].col_p2[c];
+                const uint32_t last = 1u << (H - 1);
+                for (; i < n0; i += THREADS)
+                    sqa_site<NG, SCALED, 0, true>(A, rc[i], sp, lrow, tab01, tab2t, tab1, mask, H, ug,
+                                                  c3, mask & ~last);
+                for (; i < n2; i += THREADS)
+                    sqa_site<NG, SCALED, 1, true>(A, rc[i], sp, lrow, tab01, tab2t, tab1, mask, H, ug,
+                                                  c3, mask >> 1);
+                for (; i < cnt; i += THREADS)
+                    sqa_site<NG, SCALED, 0, true, NG - 1>(A, rc[i], sp, lrow, tab01, tab2t, tab1, mask,
+                                                          H, ug, c3, last);
+            } else {
+                for (; i < n0; i += THREADS)
+                    sqa_site<NG, SCALED, 0>(A, rc[i], sp, lrow, tab01, tab2t, tab1, mask, H, ug, c3);
+                for (; i < cnt; i += THREADS)
+                    sqa_site<NG, SCALED, 1>(A, rc[i], sp, lrow, tab01, tab2t, tab1, mask, H, ug, c3);
             }
-            for (; i < n0; i += THREADS)
-                sqa_site<NG, SCALED, 0>(A, rc[i], sp, lrow, tab01, tab2t, tab1, mask, H, ug, c3,
-                                        ngrp);
-            for (; i < cnt; i += THREADS)
-                sqa_site<NG, SCALED, 1>(A, rc[i], sp, lrow, tab01, tab2t, tab1, mask, H, ug, c3,
-                                        ngrp);
             __syncthreads();
         }
     }
@@ -2606,14 +2603,25 @@ hipError_t launch_sqa_init(const SqaArgs &a, int n_inst, hipStream_t s)
     return hipGetLastError();
 }
 
-template <int NG, bool SCALED>
+template <int NG, bool SCALED, bool ODD>
 hipError_t launch_sqa_t(const SqaArgs &a, int n_inst, size_t lds_bytes, int threads, hipStream_t s)
 {
-    const void *k = (const void *)sqa_kernel<NG, SCALED>;
+    const void *k = (const void *)sqa_kernel<NG, SCALED, ODD>;
     hipError_t e = allow_lds(k, lds_bytes);   // the dynamic part (the tables are static)
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((sqa_kernel<NG, SCALED>), dim3(n_inst * a.R), dim3(threads), lds_bytes, s, a);
+    hipLaunchKernelGGL((sqa_kernel<NG, SCALED, ODD>), dim3(n_inst * a.R), dim3(threads), lds_bytes, s, a);
     return hipGetLastError();
+}
+
+template <int NG>
+hipError_t launch_sqa_g(const SqaArgs &a, int n_inst, size_t lds_bytes, int threads, hipStream_t s)
+{
+    const bool scaled = a.nl <= 64;
+    if (a.M & 1)
+        return scaled ? launch_sqa_t<NG, true, true>(a, n_inst, lds_bytes, threads, s)
+                      : launch_sqa_t<NG, false, true>(a, n_inst, lds_bytes, threads, s);
+    return scaled ? launch_sqa_t<NG, true, false>(a, n_inst, lds_bytes, threads, s)
+                  : launch_sqa_t<NG, false, false>(a, n_inst, lds_bytes, threads, s);
 }
 
 bool sqa_config_valid(int threads) { return threads >= 128 && threads <= 1024 && threads % 64 == 0; }
@@ -2621,19 +2629,17 @@ bool sqa_config_valid(int threads) { return threads >= 128 && threads <= 1024 &&
 hipError_t launch_sqa(const SqaArgs &a, int n_inst, size_t lds_bytes, int threads, hipStream_t s)
 {
     if (!sqa_config_valid(threads)) return hipErrorInvalidValue;
-    const bool scaled = a.nl <= 64;
-    const int ngrp = (a.H + 3) >> 2;
-    if (a.M & 1)   // odd M: the general kernel, which holds the three-part phases
-        return scaled ? launch_sqa_t<0, true>(a, n_inst, lds_bytes, threads, s)
-                      : launch_sqa_t<0, false>(a, n_inst, lds_bytes, threads, s);
-    if (ngrp == 8)
-        return scaled ? launch_sqa_t<8, true>(a, n_inst, lds_bytes, threads, s)
-                      : launch_sqa_t<8, false>(a, n_inst, lds_bytes, threads, s);
-    // M = 32 and M = 16 with pre-scaled tables also run unrolled
-    if (ngrp == 4 && scaled) return launch_sqa_t<4, true>(a, n_inst, lds_bytes, threads, s);
-    if (ngrp == 2 && scaled) return launch_sqa_t<2, true>(a, n_inst, lds_bytes, threads, s);
-    return scaled ? launch_sqa_t<0, true>(a, n_inst, lds_bytes, threads, s)
-                  : launch_sqa_t<0, false>(a, n_inst, lds_bytes, threads, s);
+    switch ((a.H + 3) >> 2) {
+    case 1: return launch_sqa_g<1>(a, n_inst, lds_bytes, threads, s);
+    case 2: return launch_sqa_g<2>(a, n_inst, lds_bytes, threads, s);
+    case 3: return launch_sqa_g<3>(a, n_inst, lds_bytes, threads, s);
+    case 4: return launch_sqa_g<4>(a, n_inst, lds_bytes, threads, s);
+    case 5: return launch_sqa_g<5>(a, n_inst, lds_bytes, threads, s);
+    case 6: return launch_sqa_g<6>(a, n_inst, lds_bytes, threads, s);
+    case 7: return launch_sqa_g<7>(a, n_inst, lds_bytes, threads, s);
+    case 8: return launch_sqa_g<8>(a, n_inst, lds_bytes, threads, s);
+    }
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_widen_rows(const int32_t *src, int src_stride, int64_t *dst, int rows, int cols,

@@ -89,3 +89,25 @@ def test_adaptive_word_splits(shape, n_inst, n_chains):
     for i in range(0, n_inst, max(1, n_inst // 40)):
         beta, sigma = oracle.adaptive_ladder(oracle.Lattice(*insts[i]), i, 21, **kw)[:2]
         assert np.array_equal(got[i][0], beta) and np.array_equal(got[i][1], sigma), f"instance {i}"
+
+
+@pytest.mark.parametrize("h_max", [0, 12])
+@pytest.mark.parametrize("M", [4, 9, 12, 17, 20, 25, 28, 36, 41, 44, 49, 52, 57, 60, 61])
+def test_sqa_group_counts(M, h_max):
+    """Every number of slice groups per word, even and odd M (with the last slice alone in its
+    group at M = 9, 17, ...), in the scaled (no fields) and the unscaled table form."""
+    inst = []
+    for i, (shape, periodic) in enumerate([((4, 3, 2), 7), ((3, 3, 3), 5)]):
+        J, h = ej_couplings(shape, periodic, 500 + i, h_max=h_max)
+        inst.append((J, periodic, h))
+    gam = np.linspace(3.0, 0.1, 5)
+    ctx = sg.sqa(inst, M, 2, 3.0, SEED)
+    bE, bs = ctx.sqa_anneal(gam)
+    spins, E = ctx.spins(), ctx.energy()
+    for i, x in enumerate(inst):
+        lat = oracle.Lattice(*x)
+        sp = oracle.sqa_init(lat, i, M, 2, SEED)
+        oE, ostate, _ = oracle.sqa_anneal(lat, i, M, 2, 3.0, gam, SEED, 0, sp)
+        assert np.array_equal(spins[i, :, :, :lat.n], sp) and bE[i] == oE, f"instance {i}"
+        assert np.array_equal(bs[i, :lat.n], ostate)
+        assert E[i].min() == oE
