@@ -373,6 +373,7 @@ struct sg_ctx {
     DevBuf<int32_t> d_slice_E;
     DevBuf<int64_t> d_best_key;   // per instance: (E + 2^30) << 32 | (r M + k) of the lowest slice
     DevBuf<int8_t> d_best_state;  // per instance: that slice, +1/-1 [n_max]
+    DevBuf<int8_t> d_stage;   // spins on their way to or from the host (at most 32 MB, or one row)
     size_t sqa_lds = 0;
     uint32_t sqa_steps = 0;
     int sqa_threads = 0;   // work-group size; 0: chosen by the autotuner on the next anneal
@@ -1926,6 +1927,116 @@ void run_sqa_anneal(sg_ctx *c, const double *gamma, int32_t n_steps)
     }
 }
 
+// Spins of rows [row0, row0 + rows) (APT: logical slots, DT-SQA: replicas, over all instances) as
+// +1/-1 bytes, `stride` per site row, to device memory.
+void spins_out(sg_ctx *c, int64_t row0, int64_t rows, int stride, int8_t *out)
+{
+    if (c->mode == SG_APT)
+        hip_check(launch_apt_spins_out(c->d_spins.p, c->d_perm.p, c->d_inst.p, 4 * c->n_quads, c->n_slots, row0,
+                                       rows, stride, out, c->stream),
+                  "spins");
+    else
+        hip_check(launch_sqa_spins_out(c->d_sqa.p, c->d_inst.p, c->R, c->M, row0, rows, stride, out, c->stream),
+                  "spins");
+}
+
+// Rows of spins cross to the host through a staging buffer on the device, at most 32 MB at a
+// time (or one row; less where the device has no room for that), kept with the context.  The bytes are made and read by the GPU: four L = 15
+// instances with 64 replicas of 32 slices (28 MB of spins) leave in 1.7 ms; a loop over them on
+// the host took 36 ms.
+int64_t stage_rows(sg_ctx *c, int64_t rows, int64_t row_bytes)
+{
+    int64_t n = std::min(rows, std::max<int64_t>(1, (32 << 20) / row_bytes));
+    while (c->d_stage.n < (size_t)(n * row_bytes)) {
+        try {
+            c->d_stage.alloc((size_t)(n * row_bytes), "spin staging");
+        } catch (const Failure &) {
+            if (n == 1) throw;
+            n = (n + 1) / 2;
+        }
+    }
+    return n;
+}
+
+void spins_to_host(sg_ctx *c, int64_t row0, int64_t rows, int stride, int8_t *out)
+{
+    const int64_t row_bytes = (int64_t)stride * (c->mode == SG_APT ? 1 : c->M);
+    const int64_t n = stage_rows(c, rows, row_bytes);
+    for (int64_t q = 0; q < rows; q += n) {
+        const int64_t m = std::min(n, rows - q);
+        spins_out(c, row0 + q, m, stride, c->d_stage.p);
+        c->d_stage.download(out + q * row_bytes, (size_t)(m * row_bytes), c->stream, "spins");
+        hip_check(hipStreamSynchronize(c->stream), "spins");
+    }
+}
+
+// sg_set_spins; the caller waits for the stream before `in` may go.
+void put_spins(sg_ctx *c, const int8_t *in)
+{
+    // The new state is built beside the present one and checked on the way; it takes its place
+    // only when every site's byte was +1 or -1.  A small state (up to 256 KB of spins: the
+    // check takes less than the buffer and the trip of the flag), or one that finds no room on
+    // the device, is checked here first and goes in at once.
+    const bool apt = c->mode == SG_APT;
+    hipStream_t s = c->stream;
+    const int64_t rows = (int64_t)c->n_inst * (apt ? c->n_slots : c->R);
+    const int64_t row_bytes = (int64_t)c->n_max * (apt ? 1 : c->M);
+    const int64_t n = stage_rows(c, rows, row_bytes);
+    DevBuf<uint32_t> next;
+    const size_t words = apt ? c->d_spins.n / 4 : c->d_sqa.n;   // (replica buffers of 16 k bytes)
+    uint32_t *state = apt ? (uint32_t *)c->d_spins.p : c->d_sqa.p, *to = state;
+    int32_t *bad = (int32_t *)(c->d_ctr.p + 7);   // (a spare counter)
+    if (rows * row_bytes > 1 << 18) {
+        try {
+            next.alloc(words, "spins");
+            to = next.p;
+            hip_check(launch_fill_u32((uint32_t *)bad, 0u, 1, s), "spins");
+        } catch (const Failure &e) {
+            if (e.code != SG_ENOMEM) throw;
+        }
+    }
+    if (to == state) {
+        const int64_t per_inst = row_bytes / c->n_max * (apt ? c->n_slots : c->R);   // site rows
+        for (int64_t q = 0; q < per_inst * c->n_inst; ++q) {
+            const int8_t *v = in + q * c->n_max;
+            const int sites = c->idev[(size_t)(q / per_inst)].n;
+            int wrong = 0;
+            for (int j = 0; j < sites; ++j) wrong |= (v[j] != 1) & (v[j] != -1);
+            if (wrong) fail(SG_EINVAL, "spins must be +1 or -1");
+        }
+    }
+    // every site of every row is written; an APT ladder that does not fill its last tile
+    // leaves buffers that no slot names
+    if (apt && c->n_slots != 4 * c->n_quads) hip_check(launch_fill_u32(to, 0u, (int64_t)words, s), "spins");
+    for (int64_t q = 0; q < rows; q += n) {
+        const int64_t m = std::min(n, rows - q);
+        c->d_stage.upload(in + q * row_bytes, (size_t)(m * row_bytes), s, "spins");
+        hip_check(apt ? launch_apt_spins_in((uint8_t *)to, c->d_inst.p, c->n_slots, q, m, c->n_max,
+                                            c->d_stage.p, bad, s)
+                      : launch_sqa_spins_in(to, c->d_inst.p, c->R, c->M, q, m, c->n_max, c->d_stage.p,
+                                            bad, s),
+                  "spins");
+    }
+    if (to != state) {
+        int32_t wrong = 0;
+        hip_check(hipMemcpyAsync(&wrong, bad, sizeof wrong, hipMemcpyDeviceToHost, s), "spins");
+        hip_check(hipStreamSynchronize(s), "spins");
+        if (wrong) fail(SG_EINVAL, "spins must be +1 or -1");
+        hip_check(hipMemcpyAsync(state, to, words * 4, hipMemcpyDeviceToDevice, s), "spins");
+    }
+    if (apt) {
+        const int nb4 = 4 * c->n_quads;
+        std::vector<int32_t> perm((size_t)c->n_inst * nb4);
+        for (size_t i = 0; i < perm.size(); ++i) perm[i] = (int32_t)(i % nb4);
+        c->d_perm.upload(perm.data(), perm.size(), s, "perm");
+        hip_check(hipStreamSynchronize(s), "perm");   // the vector ends here
+        // energies of the new state
+        AptArgs a = apt_args(c, 0, 0);
+        a.do_energy = 2;
+        hip_check(launch_apt_quad(a, c->quad_lds, s), "energy");
+    }
+}
+
 // A device pointer for a device-output call: memory of the context's device (SG_EINVAL
 // otherwise, so that a host pointer is refused instead of being written by a kernel).
 void check_device_ptr(const sg_ctx *c, const void *p, const char *what)
@@ -2032,13 +2143,9 @@ sg_status sg_get_spins_dev(sg_ctx *c, int8_t *spins_dev)
         if (!c) fail(SG_EINVAL, "context is NULL");
         check_device_ptr(c, spins_dev, "spins_dev");
         if (c->mode == SG_APT)
-            hip_check(launch_apt_spins_out(c->d_spins.p, c->d_perm.p, c->d_inst.p, c->n_inst,
-                                           4 * c->n_quads, c->n_slots, c->n_max, spins_dev, c->stream),
-                      "spins");
+            spins_out(c, 0, (int64_t)c->n_inst * c->n_slots, c->n_max, spins_dev);
         else
-            hip_check(launch_sqa_spins_out(c->d_sqa.p, c->d_inst.p, c->n_inst, c->R, c->M, c->n_max,
-                                           spins_dev, c->stream),
-                      "spins");
+            spins_out(c, 0, (int64_t)c->n_inst * c->R, c->n_max, spins_dev);
     });
 }
 
@@ -2047,12 +2154,18 @@ sg_status sg_sqa_trotter_agreement(sg_ctx *c, int32_t *agree_host)
     return guarded(c, [&] {
         require(c, SG_SQA);
         if (!agree_host) fail(SG_EINVAL, "agree_host is NULL");
-        DevBuf<int32_t> d;
-        d.alloc((size_t)c->n_inst * c->R * c->M, "correlation");
+        // counts of whole replicas through the staging buffer
+        const int64_t rows = (int64_t)c->n_inst * c->R;
+        const int64_t n = stage_rows(c, rows, 4 * c->M);
         SqaArgs a = sqa_args(c);
-        hip_check(launch_sqa_corr(a, c->n_inst, d.p, c->stream), "correlation");
-        d.download(agree_host, d.n, c->stream, "correlation");
-        hip_check(hipStreamSynchronize(c->stream), "correlation");
+        for (int64_t q = 0; q < rows; q += n) {
+            const int64_t m = std::min(n, rows - q);
+            hip_check(launch_sqa_corr(a, (int)q, (int)m, (int32_t *)c->d_stage.p, c->stream), "correlation");
+            hip_check(hipMemcpyAsync(agree_host + q * c->M, c->d_stage.p, (size_t)(4 * m * c->M),
+                                     hipMemcpyDeviceToHost, c->stream),
+                      "correlation");
+            hip_check(hipStreamSynchronize(c->stream), "correlation");
+        }
     });
 }
 
@@ -2060,38 +2173,7 @@ sg_status sg_get_spins(sg_ctx *c, int8_t *out)
 {
     return guarded(c, [&] {
         if (!c || !out) fail(SG_EINVAL, "NULL argument");
-        if (c->mode == SG_APT) {
-            const int nb4 = 4 * c->n_quads;
-            std::vector<uint8_t> raw(c->d_spins.n);
-            std::vector<int32_t> perm((size_t)c->n_inst * nb4);
-            c->d_spins.download(raw.data(), raw.size(), c->stream, "spins");
-            c->d_perm.download(perm.data(), perm.size(), c->stream, "spins");
-            hip_check(hipStreamSynchronize(c->stream), "spins");
-            for (int i = 0; i < c->n_inst; ++i) {
-                const InstDev &I = c->idev[i];
-                for (int s = 0; s < c->n_slots; ++s) {
-                    const uint8_t *src = raw.data() + I.spin_off + (int64_t)perm[(size_t)i * nb4 + s] * I.npad;
-                    int8_t *dst = out + ((size_t)i * c->n_slots + s) * c->n_max;
-                    std::memset(dst, 0, (size_t)c->n_max);
-                    for (int j = 0; j < I.n; ++j) dst[j] = src[j] ? 1 : -1;
-                }
-            }
-        } else {
-            std::vector<uint32_t> raw(c->d_sqa.n);
-            c->d_sqa.download(raw.data(), raw.size(), c->stream, "spins");
-            hip_check(hipStreamSynchronize(c->stream), "spins");
-            for (int i = 0; i < c->n_inst; ++i) {
-                const InstDev &I = c->idev[i];
-                for (int r = 0; r < c->R; ++r)
-                    for (int k = 0; k < c->M; ++k) {
-                        const uint32_t *w = raw.data() + I.spin_off + (int64_t)r * I.npad * 2;
-                        int8_t *dst = out + (((size_t)i * c->R + r) * c->M + k) * c->n_max;
-                        std::memset(dst, 0, (size_t)c->n_max);
-                        for (int j = 0; j < I.n; ++j)
-                            dst[j] = ((w[2 * j + (k & 1)] >> (k >> 1)) & 1u) ? 1 : -1;
-                    }
-            }
-        }
+        spins_to_host(c, 0, (int64_t)c->n_inst * (c->mode == SG_APT ? c->n_slots : c->R), c->n_max, out);
     });
 }
 
@@ -2103,36 +2185,8 @@ sg_status sg_get_spins_range(sg_ctx *c, int32_t inst, int32_t first, int32_t cou
         const int total = c->mode == SG_APT ? c->n_slots : c->R;
         if (first < 0 || count < 0 || (int64_t)first + count > total)
             fail(SG_EINVAL, "range outside the instance's %s", c->mode == SG_APT ? "slots" : "replicas");
-        const InstDev &I = c->idev[inst];
         if (count == 0) return;
-        if (c->mode == SG_APT) {
-            const int nb4 = 4 * c->n_quads;
-            std::vector<int32_t> perm((size_t)nb4);
-            hip_check(hipMemcpyAsync(perm.data(), c->d_perm.p + (size_t)inst * nb4, perm.size() * 4,
-                                     hipMemcpyDeviceToHost, c->stream),
-                      "spins");
-            hip_check(hipStreamSynchronize(c->stream), "spins");
-            std::vector<uint8_t> buf((size_t)I.npad);
-            for (int s = 0; s < count; ++s) {
-                hip_check(hipMemcpyAsync(buf.data(),
-                                         c->d_spins.p + I.spin_off + (int64_t)perm[first + s] * I.npad,
-                                         buf.size(), hipMemcpyDeviceToHost, c->stream),
-                          "spins");
-                hip_check(hipStreamSynchronize(c->stream), "spins");
-                for (int j = 0; j < I.n; ++j) out[(size_t)s * I.n + j] = buf[j] ? 1 : -1;
-            }
-        } else {
-            std::vector<uint32_t> w((size_t)count * I.npad * 2);
-            hip_check(hipMemcpyAsync(w.data(), c->d_sqa.p + I.spin_off + (int64_t)first * I.npad * 2,
-                                     w.size() * 4, hipMemcpyDeviceToHost, c->stream),
-                      "spins");
-            hip_check(hipStreamSynchronize(c->stream), "spins");
-            for (int r = 0; r < count; ++r)
-                for (int k = 0; k < c->M; ++k)
-                    for (int j = 0; j < I.n; ++j)
-                        out[((size_t)r * c->M + k) * I.n + j] =
-                            ((w[(size_t)r * I.npad * 2 + 2 * j + (k & 1)] >> (k >> 1)) & 1u) ? 1 : -1;
-        }
+        spins_to_host(c, (int64_t)inst * total + first, count, c->idev[inst].n, out);
     });
 }
 
@@ -2140,50 +2194,8 @@ sg_status sg_set_spins(sg_ctx *c, const int8_t *in)
 {
     return guarded(c, [&] {
         if (!c || !in) fail(SG_EINVAL, "NULL argument");
-        if (c->mode == SG_APT) {
-            const int nb4 = 4 * c->n_quads;
-            for (int i = 0; i < c->n_inst; ++i)
-                for (int s = 0; s < c->n_slots; ++s)
-                    for (int j = 0; j < c->idev[i].n; ++j) {
-                        const int8_t v = in[((size_t)i * c->n_slots + s) * c->n_max + j];
-                        if (v != 1 && v != -1) fail(SG_EINVAL, "spins must be +1 or -1");
-                    }
-            std::vector<uint8_t> raw(c->d_spins.n, 0);
-            std::vector<int32_t> perm((size_t)c->n_inst * nb4);
-            for (int i = 0; i < c->n_inst; ++i) {
-                const InstDev &I = c->idev[i];
-                for (int s = 0; s < nb4; ++s) {
-                    perm[(size_t)i * nb4 + s] = s;
-                    if (s >= c->n_slots) continue;
-                    uint8_t *dst = raw.data() + I.spin_off + (int64_t)s * I.npad;
-                    const int8_t *src = in + ((size_t)i * c->n_slots + s) * c->n_max;
-                    for (int j = 0; j < I.n; ++j) dst[j] = src[j] > 0 ? 1 : 0;
-                }
-            }
-            c->d_spins.upload(raw.data(), raw.size(), c->stream, "spins");
-            c->d_perm.upload(perm.data(), perm.size(), c->stream, "perm");
-            // energies of the new state
-            AptArgs a = apt_args(c, 0, 0);
-            a.do_energy = 2;
-            hip_check(launch_apt_quad(a, c->quad_lds, c->stream), "energy");
-            hip_check(hipStreamSynchronize(c->stream), "spins");
-        } else {
-            std::vector<uint32_t> raw(c->d_sqa.n, 0u);
-            for (int i = 0; i < c->n_inst; ++i) {
-                const InstDev &I = c->idev[i];
-                for (int r = 0; r < c->R; ++r)
-                    for (int k = 0; k < c->M; ++k) {
-                        const int8_t *src = in + (((size_t)i * c->R + r) * c->M + k) * c->n_max;
-                        uint32_t *w = raw.data() + I.spin_off + (int64_t)r * I.npad * 2;
-                        for (int j = 0; j < I.n; ++j) {
-                            if (src[j] != 1 && src[j] != -1) fail(SG_EINVAL, "spins must be +1 or -1");
-                            if (src[j] > 0) w[2 * j + (k & 1)] |= 1u << (k >> 1);
-                        }
-                    }
-            }
-            c->d_sqa.upload(raw.data(), raw.size(), c->stream, "spins");
-            hip_check(hipStreamSynchronize(c->stream), "spins");
-        }
+        put_spins(c, in);
+        hip_check(hipStreamSynchronize(c->stream), "spins");
     });
 }
 
@@ -2221,9 +2233,8 @@ sg_status sg_get_state(sg_ctx *c, void *blob, size_t *len)
         const uint32_t hdr[6] = {0x53474331u, (uint32_t)c->mode, (uint32_t)c->n_inst,
                                  (uint32_t)c->n_max, (uint32_t)c->n_slots, (uint32_t)(c->R * c->M)};
         std::memcpy(b, hdr, sizeof hdr);
-        uint32_t ctr[3];
-        if (sg_get_counters(c, ctr) != SG_OK) fail(SG_EHIP, "%s", c->err.c_str());
-        std::memcpy(b + 24, ctr, sizeof ctr);
+        uint32_t ctr[8];
+        c->d_ctr.download(ctr, 8, c->stream, "state");
         size_t off = 64;
         if (c->mode == SG_APT) {
             c->d_best.download((int64_t *)(b + off), (size_t)c->n_inst, c->stream, "state");
@@ -2231,11 +2242,14 @@ sg_status sg_get_state(sg_ctx *c, void *blob, size_t *len)
             const size_t na = (size_t)c->n_inst * (c->n_beta - 1) * c->reps;
             c->d_acc_count.download((int64_t *)(b + off), na, c->stream, "state");
             off += 8 * na;
-            hip_check(hipStreamSynchronize(c->stream), "state");
         } else {
             off += 8 * (size_t)c->n_inst;
         }
-        if (sg_get_spins(c, (int8_t *)(b + off)) != SG_OK) fail(SG_EHIP, "%s", c->err.c_str());
+        // (the spins' copies wait for the stream)
+        spins_to_host(c, 0, (int64_t)c->n_inst * (c->mode == SG_APT ? c->n_slots : c->R), c->n_max,
+                      (int8_t *)(b + off));
+        if (c->mode == SG_SQA) ctr[0] = c->sqa_steps;
+        std::memcpy(b + 24, ctr, 3 * sizeof *ctr);
         *len = need;
     });
 }
@@ -2254,17 +2268,13 @@ sg_status sg_set_state(sg_ctx *c, const void *blob, size_t len)
             fail(SG_EINVAL, "blob belongs to a different context shape");
         uint32_t ctr[3];
         std::memcpy(ctr, b + 24, sizeof ctr);
-        size_t off = 64;
+        const uint8_t *best = b + 64, *acc = best + 8 * (size_t)c->n_inst;
+        const size_t na = c->mode == SG_APT ? (size_t)c->n_inst * (c->n_beta - 1) * c->reps : 0;
+        put_spins(c, (const int8_t *)(acc + 8 * na));   // refuses a bad state before anything changes
         if (c->mode == SG_APT) {
-            c->d_best.upload((const int64_t *)(b + off), (size_t)c->n_inst, c->stream, "state");
-            off += 8 * (size_t)c->n_inst;
-            const size_t na = (size_t)c->n_inst * (c->n_beta - 1) * c->reps;
-            c->d_acc_count.upload((const int64_t *)(b + off), na, c->stream, "state");
-            off += 8 * na;
-        } else {
-            off += 8 * (size_t)c->n_inst;
+            c->d_best.upload((const int64_t *)best, (size_t)c->n_inst, c->stream, "state");
+            c->d_acc_count.upload((const int64_t *)acc, na, c->stream, "state");
         }
-        if (sg_set_spins(c, (const int8_t *)(b + off)) != SG_OK) fail(SG_EINVAL, "%s", c->err.c_str());
         uint32_t v[8] = {ctr[0], ctr[1], ctr[2], 0u, 0u, 0u, 0u, 0u};
         c->d_ctr.upload(v, 8, c->stream, "state");
         if (c->mode == SG_SQA) c->sqa_steps = ctr[0];

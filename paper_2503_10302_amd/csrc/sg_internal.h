@@ -216,15 +216,23 @@ hipError_t launch_sqa(const SqaArgs &a, int n_inst, size_t lds_bytes, int thread
 // The slice chosen by best_key[i] of every instance as +1/-1 bytes, out[i][n_max].
 hipError_t launch_sqa_best_state(const SqaArgs &a, int n_inst, int n_max, int8_t *out,
                                  hipStream_t s);
-// agree[inst][r][k]: sites where slice k of replica r agrees with its slice 0.
 hipError_t launch_widen_rows(const int32_t *src, int src_stride, int64_t *dst, int rows, int cols,
                              hipStream_t s);
-hipError_t launch_apt_spins_out(const uint8_t *spins, const int32_t *perm, const InstDev *inst,
-                                int n_inst, int nb4, int n_slots, int n_max, int8_t *out, hipStream_t s);
-hipError_t launch_sqa_spins_out(const uint32_t *words, const InstDev *inst, int n_inst, int R, int M,
-                                int n_max, int8_t *out, hipStream_t s);
+// Spins as +1/-1 bytes out of and into the replica buffers, `stride` bytes per site row.  Rows count
+// logical slots (APT; one site row each) or replicas (DT-SQA; M site rows each) over all instances.
+// The *_in launches set *bad when a site's byte is neither +1 nor -1.
+hipError_t launch_apt_spins_out(const uint8_t *spins, const int32_t *perm, const InstDev *inst, int nb4,
+                                int n_slots, int64_t row0, int64_t rows, int stride, int8_t *out, hipStream_t s);
+hipError_t launch_sqa_spins_out(const uint32_t *words, const InstDev *inst, int R, int M, int64_t row0,
+                                int64_t rows, int stride, int8_t *out, hipStream_t s);
+hipError_t launch_apt_spins_in(uint8_t *spins, const InstDev *inst, int n_slots, int64_t row0, int64_t rows,
+                               int stride, const int8_t *in, int32_t *bad, hipStream_t s);
+hipError_t launch_sqa_spins_in(uint32_t *words, const InstDev *inst, int R, int M, int64_t row0, int64_t rows,
+                               int stride, const int8_t *in, int32_t *bad, hipStream_t s);
 hipError_t launch_best_key_energy(const uint64_t *key, int n, int64_t *out, hipStream_t s);
-hipError_t launch_sqa_corr(const SqaArgs &a, int n_inst, int32_t *agree, hipStream_t s);
+// agree[q][k]: sites where slice k of replica row0 + q (counted over all instances) agrees with its
+// slice 0.
+hipError_t launch_sqa_corr(const SqaArgs &a, int row0, int rows, int32_t *agree, hipStream_t s);
 hipError_t launch_adapt_init(const AdaptArgs &a, int n_inst, hipStream_t s);
 hipError_t launch_adapt(const AdaptArgs &a, int n_inst, size_t lds_bytes, hipStream_t s);
 hipError_t launch_fill_i64(int64_t *p, int64_t v, int64_t n, hipStream_t s);

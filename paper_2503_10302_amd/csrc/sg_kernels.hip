@@ -2168,12 +2168,12 @@ void sqa_kernel(SqaArgs A)
 }
 
 // Correlation along the Trotter direction (C_k = (1/n) sum_i s_{i,0} s_{i,k}), exactly: the
-// number of sites where slice k agrees with slice 0, agree[inst][r][k], one work-group of 256
-// threads per replica.
-__global__ __launch_bounds__(256) void sqa_corr_kernel(SqaArgs A, int32_t *agree)
+// number of sites where slice k agrees with slice 0, agree[block][k], one work-group of 256
+// threads per replica, the replicas (of all instances in turn) from row0 on.
+__global__ __launch_bounds__(256) void sqa_corr_kernel(SqaArgs A, int row0, int32_t *agree)
 {
     __shared__ int32_t red[64];
-    const int inst = blockIdx.x / A.R, r = blockIdx.x - inst * A.R;
+    const int row = row0 + (int)blockIdx.x, inst = row / A.R, r = row - inst * A.R;
     const InstDev I = A.inst[inst];
     const uint32_t *g = A.spins + I.spin_off + (int64_t)r * I.npad * 2;
     const int H = A.H, n = I.n, M = A.M;
@@ -2186,7 +2186,7 @@ __global__ __launch_bounds__(256) void sqa_corr_kernel(SqaArgs A, int32_t *agree
     const int lane = threadIdx.x & 63;
     if (lane < M) atomicAdd(&red[lane], mine);
     __syncthreads();
-    if (threadIdx.x < M) agree[((int64_t)inst * A.R + r) * M + threadIdx.x] = n - red[threadIdx.x];
+    if (threadIdx.x < M) agree[(int64_t)blockIdx.x * M + threadIdx.x] = n - red[threadIdx.x];
 }
 
 // Spins of the slice that best_key[i] names (replica r, slice k = 2h + p: bit h of word p),
@@ -2242,31 +2242,135 @@ __global__ void widen_rows_kernel(const int32_t *src, int src_stride, int64_t *d
     }
 }
 
-// APT spins as +1/-1, [n_inst][n_slots][n_max] (0 past an instance's n): logical slot s of
-// instance i is physical buffer perm[i][s].  Grid (n_slots, n_inst).
-__global__ void apt_spins_out_kernel(const uint8_t *spins, const int32_t *perm, const InstDev *inst,
-                                     int nb4, int n_slots, int n_max, int8_t *out)
+// Four bytes of a caller's array, at any alignment.
+__device__ __forceinline__ uint32_t load4(const int8_t *p)
 {
-    const int s = blockIdx.x, i = blockIdx.y;
-    const InstDev I = inst[i];
-    const uint8_t *src = spins + I.spin_off + (int64_t)perm[(int64_t)i * nb4 + s] * I.npad;
-    int8_t *dst = out + ((int64_t)i * n_slots + s) * n_max;
-    for (int j = threadIdx.x; j < n_max; j += blockDim.x)
-        dst[j] = j < I.n ? (src[j] ? 1 : -1) : 0;
+    uint32_t v;
+    __builtin_memcpy(&v, p, 4);
+    return v;
+}
+// The first `valid` (at most four) bytes of v to p.
+__device__ __forceinline__ void store4(int8_t *p, uint32_t v, int valid)
+{
+    if (valid >= 4) {
+        __builtin_memcpy(p, &v, 4);
+    } else {
+        for (int t = 0; t < valid; ++t) p[t] = (int8_t)(v >> (8 * t));
+    }
+}
+// Bytes 0/1 -> -1/+1, the bytes of sites at or past `left` -> 0.
+__device__ __forceinline__ uint32_t signed_bytes(uint32_t bits, int left)
+{
+    const uint32_t v = 0xFFFFFFFFu ^ (bits * 0xFEu);
+    return left >= 4 ? v : (left <= 0 ? 0u : v & ((1u << (8 * left)) - 1u));
 }
 
-// DT-SQA spins as +1/-1, [n_inst][R][M][n_max]: slice k = 2 h + p is bit h of word p.
-// Grid (R * M, n_inst).
-__global__ void sqa_spins_out_kernel(const uint32_t *words, const InstDev *inst, int R, int M,
-                                     int n_max, int8_t *out)
+// APT spins of the rows (logical slots, all instances' in turn) row0 + blockIdx.y as +1/-1 bytes,
+// `stride` per row (0 past an instance's n): slot s of instance i is physical buffer perm[i][s].
+// Four sites per thread: the copy is bound by memory, a byte per thread by its instructions.
+__global__ __launch_bounds__(256) void apt_spins_out_kernel(const uint8_t *spins, const int32_t *perm,
+                                                            const InstDev *inst, int nb4, int n_slots,
+                                                            int64_t row0, int stride, int8_t *out)
 {
-    const int rk = blockIdx.x, i = blockIdx.y;
-    const int r = rk / M, k = rk - r * M;
+    const int64_t row = row0 + blockIdx.y;
+    const int i = (int)(row / n_slots), sl = (int)(row - (int64_t)i * n_slots);
     const InstDev I = inst[i];
-    const uint32_t *w = words + I.spin_off + (int64_t)r * I.npad * 2;
-    int8_t *dst = out + (((int64_t)i * R + r) * M + k) * n_max;
-    for (int j = threadIdx.x; j < n_max; j += blockDim.x)
-        dst[j] = j < I.n ? (((w[2 * j + (k & 1)] >> (k >> 1)) & 1u) ? 1 : -1) : 0;
+    const uint8_t *src = spins + I.spin_off + (int64_t)perm[(int64_t)i * nb4 + sl] * I.npad;
+    int8_t *dst = out + (int64_t)blockIdx.y * stride;
+    for (int j = 4 * (blockIdx.x * 256 + threadIdx.x); j < stride; j += 1024 * gridDim.x) {
+        const uint32_t w = j < I.npad ? *(const uint32_t *)(src + j) : 0u;
+        store4(dst + j, signed_bytes(w, I.n - j), stride - j);
+    }
+}
+
+// DT-SQA spins of the replicas (all instances' in turn) row0 + blockIdx.y as +1/-1 bytes, M rows
+// of `stride` per replica: slice k = 2 h + p is bit h of word p.  A thread holds the words of four
+// sites for all slices, so every word is read once (132 MB of spins: 110 -> 40 us, against a
+// byte per thread and a read of the words for every slice).
+__global__ __launch_bounds__(256) void sqa_spins_out_kernel(const uint32_t *words, const InstDev *inst,
+                                                            int R, int M, int64_t row0, int stride,
+                                                            int8_t *out)
+{
+    const int64_t row = row0 + blockIdx.y;
+    const int i = (int)(row / R), r = (int)(row - (int64_t)i * R);
+    const InstDev I = inst[i];
+    const uint32_t *g = words + I.spin_off + (int64_t)r * I.npad * 2;
+    int8_t *dst = out + (int64_t)blockIdx.y * M * stride;
+    for (int j = 4 * (blockIdx.x * 256 + threadIdx.x); j < stride; j += 1024 * gridDim.x) {
+        uint32_t w[2][4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const uint2 v = j < I.npad ? *(const uint2 *)(g + 2 * (j + t)) : make_uint2(0u, 0u);
+            w[0][t] = v.x;
+            w[1][t] = v.y;
+        }
+        for (int k = 0; k < M; ++k) {
+            const int h = k >> 1;
+            uint32_t bits = 0u;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) bits |= (((k & 1 ? w[1][t] : w[0][t]) >> h) & 1u) << (8 * t);
+            store4(dst + (int64_t)k * stride + j, signed_bytes(bits, I.n - j), stride - j);
+        }
+    }
+}
+
+// The other way: bytes +1/-1 of the rows row0 + blockIdx.y into a copy of the replica buffers
+// (logical slot s in buffer s).  *bad is set when a byte of a site is neither +1 nor -1.
+__device__ __forceinline__ uint32_t up_bytes(uint32_t v, int left, int32_t &wrong)
+{
+    const uint32_t neg = (v >> 7) & 0x01010101u;
+    const uint32_t live = left >= 4 ? 0xFFFFFFFFu : (left <= 0 ? 0u : (1u << (8 * left)) - 1u);
+    wrong |= ((v ^ 0x01010101u ^ (neg * 0xFEu)) & live) != 0u;
+    return (neg ^ 0x01010101u) & live;
+}
+
+__device__ __forceinline__ uint32_t load4_upto(const int8_t *p, int valid)
+{
+    if (valid >= 4) return load4(p);
+    uint32_t v = 0u;
+    for (int t = 0; t < valid; ++t) v |= (uint32_t)(uint8_t)p[t] << (8 * t);
+    return v;
+}
+
+__global__ __launch_bounds__(256) void apt_spins_in_kernel(uint8_t *spins, const InstDev *inst,
+                                                           int n_slots, int64_t row0, int stride,
+                                                           const int8_t *in, int32_t *bad)
+{
+    const int64_t row = row0 + blockIdx.y;
+    const int i = (int)(row / n_slots), sl = (int)(row - (int64_t)i * n_slots);
+    const InstDev I = inst[i];
+    uint8_t *dst = spins + I.spin_off + (int64_t)sl * I.npad;
+    const int8_t *src = in + (int64_t)blockIdx.y * stride;
+    int32_t wrong = 0;
+    for (int j = 4 * (blockIdx.x * 256 + threadIdx.x); j < I.npad; j += 1024 * gridDim.x)
+        *(uint32_t *)(dst + j) = up_bytes(load4_upto(src + j, I.n - j), I.n - j, wrong);
+    if (wrong) atomicOr(bad, 1);
+}
+
+__global__ __launch_bounds__(256) void sqa_spins_in_kernel(uint32_t *words, const InstDev *inst, int R,
+                                                           int M, int64_t row0, int stride,
+                                                           const int8_t *in, int32_t *bad)
+{
+    const int64_t row = row0 + blockIdx.y;
+    const int i = (int)(row / R), r = (int)(row - (int64_t)i * R);
+    const InstDev I = inst[i];
+    uint32_t *g = words + I.spin_off + (int64_t)r * I.npad * 2;
+    const int8_t *src = in + (int64_t)blockIdx.y * M * stride;
+    int32_t wrong = 0;
+    for (int j = 4 * (blockIdx.x * 256 + threadIdx.x); j < I.npad; j += 1024 * gridDim.x) {
+        uint32_t w[2][4] = {{0u, 0u, 0u, 0u}, {0u, 0u, 0u, 0u}};
+        for (int k = 0; k < M; ++k) {
+            const uint32_t up = up_bytes(load4_upto(src + (int64_t)k * stride + j, I.n - j), I.n - j, wrong);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const uint32_t bit = ((up >> (8 * t)) & 1u) << (k >> 1);
+                if (k & 1) w[1][t] |= bit; else w[0][t] |= bit;
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < 4; ++t) *(uint2 *)(g + 2 * (j + t)) = make_uint2(w[0][t], w[1][t]);
+    }
+    if (wrong) atomicOr(bad, 1);
 }
 
 // The lowest slice energy of every instance from its key ((E + 2^30) << 32 | (r M + k)).
@@ -2652,20 +2756,54 @@ hipError_t launch_widen_rows(const int32_t *src, int src_stride, int64_t *dst, i
     return hipGetLastError();
 }
 
-hipError_t launch_apt_spins_out(const uint8_t *spins, const int32_t *perm, const InstDev *inst,
-                                int n_inst, int nb4, int n_slots, int n_max, int8_t *out, hipStream_t s)
+namespace {
+// Calls f(first row, rows) over launches of at most 32768 rows (the grid's y extent).
+template <class F>
+hipError_t over_rows(int64_t rows, F f)
 {
-    hipLaunchKernelGGL(apt_spins_out_kernel, dim3(n_slots, n_inst), dim3(256), 0, s, spins, perm, inst,
-                       nb4, n_slots, n_max, out);
-    return hipGetLastError();
+    for (int64_t q = 0; q < rows; q += 32768) {
+        f(q, (int)std::min<int64_t>(32768, rows - q));
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+}  // namespace
+
+hipError_t launch_apt_spins_out(const uint8_t *spins, const int32_t *perm, const InstDev *inst, int nb4,
+                                int n_slots, int64_t row0, int64_t rows, int stride, int8_t *out, hipStream_t s)
+{
+    return over_rows(rows, [&](int64_t q, int n) {
+        hipLaunchKernelGGL(apt_spins_out_kernel, dim3((stride + 1023) / 1024, n), dim3(256), 0, s, spins, perm,
+                           inst, nb4, n_slots, row0 + q, stride, out + q * stride);
+    });
 }
 
-hipError_t launch_sqa_spins_out(const uint32_t *words, const InstDev *inst, int n_inst, int R, int M,
-                                int n_max, int8_t *out, hipStream_t s)
+hipError_t launch_sqa_spins_out(const uint32_t *words, const InstDev *inst, int R, int M, int64_t row0,
+                                int64_t rows, int stride, int8_t *out, hipStream_t s)
 {
-    hipLaunchKernelGGL(sqa_spins_out_kernel, dim3(R * M, n_inst), dim3(256), 0, s, words, inst, R, M,
-                       n_max, out);
-    return hipGetLastError();
+    return over_rows(rows, [&](int64_t q, int n) {
+        hipLaunchKernelGGL(sqa_spins_out_kernel, dim3((stride + 1023) / 1024, n), dim3(256), 0, s, words, inst,
+                           R, M, row0 + q, stride, out + q * M * stride);
+    });
+}
+
+hipError_t launch_apt_spins_in(uint8_t *spins, const InstDev *inst, int n_slots, int64_t row0, int64_t rows,
+                               int stride, const int8_t *in, int32_t *bad, hipStream_t s)
+{
+    return over_rows(rows, [&](int64_t q, int n) {
+        hipLaunchKernelGGL(apt_spins_in_kernel, dim3((stride + 1023) / 1024, n), dim3(256), 0, s, spins, inst,
+                           n_slots, row0 + q, stride, in + q * stride, bad);
+    });
+}
+
+hipError_t launch_sqa_spins_in(uint32_t *words, const InstDev *inst, int R, int M, int64_t row0, int64_t rows,
+                               int stride, const int8_t *in, int32_t *bad, hipStream_t s)
+{
+    return over_rows(rows, [&](int64_t q, int n) {
+        hipLaunchKernelGGL(sqa_spins_in_kernel, dim3((stride + 1023) / 1024, n), dim3(256), 0, s, words, inst,
+                           R, M, row0 + q, stride, in + q * M * stride, bad);
+    });
 }
 
 hipError_t launch_best_key_energy(const uint64_t *key, int n, int64_t *out, hipStream_t s)
@@ -2681,9 +2819,9 @@ hipError_t launch_sqa_best_state(const SqaArgs &a, int n_inst, int n_max, int8_t
     return hipGetLastError();
 }
 
-hipError_t launch_sqa_corr(const SqaArgs &a, int n_inst, int32_t *agree, hipStream_t s)
+hipError_t launch_sqa_corr(const SqaArgs &a, int row0, int rows, int32_t *agree, hipStream_t s)
 {
-    hipLaunchKernelGGL(sqa_corr_kernel, dim3(n_inst * a.R), dim3(256), 0, s, a, agree);
+    hipLaunchKernelGGL(sqa_corr_kernel, dim3(rows), dim3(256), 0, s, a, row0, agree);
     return hipGetLastError();
 }
 

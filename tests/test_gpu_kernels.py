@@ -111,3 +111,44 @@ def test_sqa_group_counts(M, h_max):
         assert np.array_equal(spins[i, :, :, :lat.n], sp) and bE[i] == oE, f"instance {i}"
         assert np.array_equal(bs[i, :lat.n], ostate)
         assert E[i].min() == oE
+
+
+@pytest.mark.parametrize("mode", ["apt", "sqa"])
+@pytest.mark.parametrize("shapes", [[(1, 1, 1)], [(3, 1, 1), (5, 7, 3)], [(15, 15, 15), (4, 4, 4), (11, 9, 13)]])
+def test_spins_in_and_out(mode, shapes):
+    """Spins written and read back through the device packing at odd row lengths: small states (checked
+    on the host) and large ones (checked on the device, several staging buffers), parts of an
+    instance, and a state with one bad byte refused unchanged."""
+    insts = [(ej_couplings(s, 7, 700 + i)[0], 7, None) for i, s in enumerate(shapes)]
+    n_max, big = max(int(np.prod(s)) for s in shapes), len(shapes) == 3
+    if mode == "apt":
+        ctx = sg.apt(insts, geometric_ladder(5, 0.2, 3.0), SEED, reps_per_beta=2)
+        lead = (10,)
+    else:
+        R = 310 if big else 3      # 3 x 310 x 33 x 3375 spins: 104 MB
+        ctx = sg.sqa(insts, 33, R, 2.0, SEED)
+        lead = (R, 33)
+    rng = np.random.default_rng(1)
+    s = np.zeros((len(insts), *lead, n_max), np.int8)
+    for i, shape in enumerate(shapes):
+        n = int(np.prod(shape))
+        s[i, ..., :n] = 2 * rng.integers(0, 2, (*lead, n), dtype=np.int8) - 1
+    ctx.set_spins(s)
+    assert np.array_equal(ctx.spins(), s)
+    last = len(insts) - 1
+    n = int(np.prod(shapes[last]))
+    assert np.array_equal(ctx.spins_range(last, 1, 2), s[last, 1:3, ..., :n])
+    if mode == "apt":
+        lat = oracle.Lattice(*insts[0])
+        assert ctx.energy()[0].tolist() == [oracle.energy(lat, v[:lat.n]) for v in s[0]]
+    for value in (0, 2, -2, 127, -128):
+        bad = s.copy()
+        bad[last, ..., n - 1].flat[-1] = value
+        with pytest.raises(sg.SGError):
+            ctx.set_spins(bad)
+    assert np.array_equal(ctx.spins(), s)
+    bad = s.copy()
+    if n < n_max:
+        bad[last, ..., n:] = 7     # bytes past an instance's sites are not looked at
+        ctx.set_spins(bad)
+        assert np.array_equal(ctx.spins(), s)
