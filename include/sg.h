@@ -226,7 +226,9 @@ sg_status sg_sqa_anneal_dev(sg_ctx *ctx, const double *gamma, int32_t n_steps, i
  * instances up to 65, 75 or 85 % of all sites, and the rest (one group if that leaves the
  * second empty).  The first sg_run_apt / sg_run_apt_ex of a context whose code is unset (0)
  * times all fifteen on its own shape (sweeps per swap, cluster moves) and keeps the fastest,
- * leaving the context's state as it was; other calls use code 1 until then.
+ * leaving the context's state as it was; other calls use code 1 until then.  Launches of several
+ * sweeps may run in a kernel of their own, to which no code applies: a first run whose cycles are
+ * such launches alone (no cluster moves) sets code 1.
  * Both tuners cache their pick per workload shape for the process and in the file named by
  * the environment variable SG_TUNE_CACHE (default ~/.cache/libsg_tune.txt; best effort).
  * get: 0 while unset.  set: 0 re-enables the autotuner; any other value outside the allowed

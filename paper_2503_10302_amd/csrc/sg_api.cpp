@@ -344,6 +344,10 @@ struct sg_ctx {
     DevBuf<uint4> d_rowA, d_rowB, d_rowC, d_rowP;
     bool small = false;        // every instance has planes == 2
     int quad_threads = kQuadThreads;   // work-group size of the replica kernel
+    // sweeps in words of up to 32 slots (apt_word_kernel): words per instance, 0: never
+    int word_nw = 0, word_threads = 0, word_planes = 0;
+    size_t word_lds = 0;
+    DevBuf<QuadDesc> d_word_desc;
     int n_blocks = 0;
     size_t quad_lds = 0;
     // two launch groups (a launch configuration): the graph's replica kernels of group 1 run
@@ -703,6 +707,76 @@ int quad_threads(const sg_ctx *c)
     return nt;
 }
 
+// Work-group size of adapt_kernel and apt_word_kernel: 1024 threads where no CU gets a second work-group and a phase
+// has more sites than kAdaptThreads (64 instances of L = 15 with 100 chains: 82 -> 75 ms), else
+// kAdaptThreads.
+int adaptive_threads(int64_t work_groups, int phase, int cus)
+{
+    return work_groups <= cus && phase > kAdaptThreads ? 1024 : kAdaptThreads;
+}
+
+// Chain words per instance in adapt_kernel, 0 for the chains as APT slots (a group of four per
+// work-group).  A site costs a work-group about 60 vector instructions and 50 per group, as a
+// tile of APT slots about 110 (its energies included).  A phase takes the longer of its
+// instructions' issue on the CU with the most work-groups and one thread's passes, whose dependent
+// instructions come about 2.5 times slower than they could issue; the cheapest split wins, so few
+// instances are cut into more, shorter words.  Measured against words of 32 chains (and APT slots
+// where those would not give every CU one): 64 instances of L = 15 with 100 chains (words of 7, 6,
+// 6, 6 groups, before 8, 8, 8, 1) 90 -> 75 ms; 4, 16 and 32 instances 1.56, 1.22 and 1.28 times
+// faster; 256 instances the same.
+int adaptive_words(int n_inst, int groups, int phase, int cus, int slot_threads)
+{
+    auto cost = [&](int words, double per_site_max, double per_site, int threads) {
+        const double on_cu = (double)(((int64_t)n_inst * words + cus - 1) / cus);
+        return std::max(on_cu * std::max(phase, 256) / 256.0 * per_site,
+                        2.5 * ((phase + threads - 1) / threads) * per_site_max);
+    };
+    int best = 0;
+    double best_cost = cost(groups, 110.0, 110.0, slot_threads);
+    for (int ng = 8; ng >= 2; --ng) {
+        const int nw = (groups + ng - 1) / ng;
+        const int top = (groups + nw - 1) / nw;   // groups of the fullest word
+        if (top < 2) continue;
+        const double c = cost(nw, 60.0 + 50.0 * top, 60.0 + 50.0 * groups / nw,
+                              adaptive_threads((int64_t)n_inst * nw, phase, cus));
+        if (c < best_cost) {
+            best_cost = c;
+            best = nw;
+        }
+    }
+    return best;
+}
+
+// The sweeps of apt_word_kernel for this context: words per instance by the rule of the adaptive
+// stage (which few work-groups or phases of few sites turn down: a four-slot tile then has more
+// parallel work) and the kernel's LDS.
+void plan_words(sg_ctx *c)
+{
+    c->word_nw = 0;
+    if (c->ni > 16 || c->hmax > 0) return;   // energies count bonds; rows of 16 thresholds
+    int phase = 0, npad = 0;
+    for (const InstDev &I : c->idev) {
+        phase = std::max(phase, *std::max_element(I.col_cnt, I.col_cnt + 4));
+        npad = std::max(npad, I.npad);
+    }
+    if ((int64_t)4 * c->n_quads * npad >= (int64_t)1 << 31) return;   // 32-bit offsets
+    int cus = 0;
+    hip_check(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device), "device");
+    const int nw = adaptive_words(c->n_inst, c->n_quads, phase, cus, c->quad_threads);
+    if (nw == 0) return;
+    const int nt = adaptive_threads((int64_t)c->n_inst * nw, phase, cus);
+    const int per_thread = 3 * ((c->n_max + nt - 1) / nt);
+    int planes = 1;
+    while ((1 << planes) <= per_thread) ++planes;
+    const size_t lds = sizeof(uint32_t) * (size_t)(npad + 4);
+    const size_t lds_static = sizeof(uint32_t) * (272 + 512 + nt / 2 + 64 + 64);
+    if (planes > kAdaptPlanes || lds + lds_static > kMaxLds) return;
+    c->word_nw = nw;
+    c->word_threads = nt;
+    c->word_planes = planes;
+    c->word_lds = lds;
+}
+
 // --------------------------------------------------------------------- APT
 void create_apt(sg_ctx *c, const sg_config *cfg, const int8_t *const *colour = nullptr)
 {
@@ -851,6 +925,7 @@ void create_apt(sg_ctx *c, const sg_config *cfg, const int8_t *const *colour = n
     c->n_blocks = (int)desc.size();
     c->d_desc.upload(desc, s, "tasks");
     c->quad_threads = quad_threads(c);
+    plan_words(c);
     c->quad_lds = 0;
     for (auto &I : c->idev) {
         const size_t need = apt_lds_bytes(I, c->ni);
@@ -929,8 +1004,49 @@ AptArgs apt_args(sg_ctx *c, int n_sweeps, int do_icm)
     a.n_blocks = c->n_blocks;
     a.nb4 = 4 * c->n_quads;
     a.fused_swap = 0;
+    a.sw.n_beta = c->n_beta;
     a.waves = c->apt_waves;
     return a;
+}
+
+// The arguments of apt_word_kernel for a launch that apt_quad_kernel would make with a.
+AptArgs word_args(sg_ctx *c, AptArgs a)
+{
+    a.desc = c->d_word_desc.p;
+    a.n_blocks = c->n_inst * c->word_nw;
+    a.rec_col = c->d_rec.p;
+    a.threads = c->word_threads;
+    a.word_ng = (c->n_quads + c->word_nw - 1) / c->word_nw;
+    a.word_full = c->n_quads - c->word_nw * (a.word_ng - 1);
+    a.planes = c->word_planes;
+    a.do_icm = 0;
+    return a;
+}
+
+// The task list of the words, made on their first use: the largest instances first, an instance's
+// words on one XCD (work-groups go to the eight XCDs in turn).
+void make_word_tasks(sg_ctx *c)
+{
+    if (c->d_word_desc.p) return;
+    std::vector<int> idx((size_t)c->n_inst);
+    for (int i = 0; i < c->n_inst; ++i) idx[(size_t)i] = i;
+    std::stable_sort(idx.begin(), idx.end(),
+                     [&](int a, int b) { return c->lat[(size_t)a].n > c->lat[(size_t)b].n; });
+    std::vector<QuadDesc> d;
+    for (int i = 0; i < c->n_inst; i += 8)
+        for (int w = 0; w < c->word_nw; ++w)
+            for (int k = i; k < std::min(i + 8, c->n_inst); ++k) d.push_back({idx[(size_t)k], w});
+    c->d_word_desc.upload(d, c->stream, "tasks");
+    hip_check(hipStreamSynchronize(c->stream), "tasks");   // the list ends here
+}
+
+// Whether a cycle of n_sweeps sweeps runs them in words.  A launch in words costs about 13 us
+// beside its sweeps against 3 us in tiles, a sweep 6.8 against 13.1 us (128 L = 12 instances): 1.11,
+// 1.27 and 1.33 times faster at 2, 3 and 10 sweeps.  Cluster moves then take a launch of their own:
+// at 4 sweeps 1.18 times faster on that batch, 0.99 on 256 instances of L = 6..15.
+bool sweep_in_words(const sg_ctx *c, int n_sweeps, bool icm)
+{
+    return c->word_nw > 0 && n_sweeps >= (icm ? 5 : 2);
 }
 
 SwapArgs swap_args(sg_ctx *c, int32_t *acc_out, int64_t *trace, int trace_cap, int record_every)
@@ -1561,8 +1677,12 @@ sg_status sg_sweep(sg_ctx *c, int32_t n_sweeps)
         require(c, SG_APT);
         if (n_sweeps < 0) fail(SG_EINVAL, "n_sweeps must be >= 0");
         if (n_sweeps == 0) return;
-        AptArgs a = apt_args(c, n_sweeps, 0);
-        hip_check(launch_apt_quad(a, c->quad_lds, c->stream), "sweep");
+        const AptArgs a = apt_args(c, n_sweeps, 0);
+        if (sweep_in_words(c, n_sweeps, false)) make_word_tasks(c);
+        hip_check(sweep_in_words(c, n_sweeps, false)
+                      ? launch_apt_words(word_args(c, a), c->word_lds, c->stream)
+                      : launch_apt_quad(a, c->quad_lds, c->stream),
+                  "sweep");
         hip_check(launch_advance(c->d_ctr.p, (uint32_t)n_sweeps, 0u, 0u, 0u, c->stream), "sweep");
     });
 }
@@ -1661,6 +1781,19 @@ sg_status sg_swap(sg_ctx *c, int32_t *accepted_host)
 
 namespace {
 
+// One cycle (a: exchange, sweeps, cluster moves) with the sweeps in words; cluster moves follow in
+// a launch of the tiles that have one.
+hipError_t launch_word_cycle(sg_ctx *c, const AptArgs &a, bool icm)
+{
+    hipError_t e = launch_apt_words(word_args(c, a), c->word_lds, c->stream);
+    if (e != hipSuccess || !icm) return e;
+    AptArgs b = a;
+    b.n_sweeps = 0;
+    b.fused_swap = 0;
+    b.perm = a.perm;
+    return launch_apt_quad(b, c->quad_lds, c->stream);
+}
+
 void run_apt(sg_ctx *c, int64_t n_cycles, int32_t sweeps_per_swap, const std::vector<double> &cut,
              int32_t icm_pairs, int32_t record_every, int64_t *best_trace)
 {
@@ -1674,7 +1807,12 @@ void run_apt(sg_ctx *c, int64_t n_cycles, int32_t sweeps_per_swap, const std::ve
         if (n_cycles == 0) return;
         upload_icm_flags(c, icm ? cut : std::vector<double>((size_t)c->n_inst,
                                                               std::numeric_limits<double>::infinity()));
-        if (c->apt_config == 0) apt_autotune(c, sweeps_per_swap, icm, icm_pairs);
+        // Sweeps in words leave the configurations their cluster moves alone (nothing to choose
+        // without any).
+        const bool words = sweep_in_words(c, sweeps_per_swap, icm);
+        if (words) make_word_tasks(c);
+        if (c->apt_config == 0 && words && !icm) c->apt_config = 1;
+        if (c->apt_config == 0) apt_autotune(c, words ? 0 : sweeps_per_swap, icm, icm_pairs);
         else apply_apt_config(c, c->apt_config);
         const int cap = best_trace ? (int)(n_cycles / record_every) : 0;
         if (best_trace) {
@@ -1703,28 +1841,36 @@ void run_apt(sg_ctx *c, int64_t n_cycles, int32_t sweeps_per_swap, const std::ve
             hip_check(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal), "capture");
             hipError_t e = hipSuccess;
             int32_t *pa = c->d_perm.p, *pb = c->d_perm2.p, *ea = c->d_E.p, *eb = c->d_E2.p;
-            e = apt_on_groups(c, [&](hipStream_t gs, const QuadDesc *desc, int nb, size_t lds) {
-                hipError_t r = hipSuccess;
-                for (int k = 0; k < K && r == hipSuccess; ++k) {
-                    AptArgs fa = qa;
-                    fa.desc = desc;
-                    fa.n_blocks = nb;
-                    fa.cyc_k = k;
-                    if (k > 0) {
-                        const bool odd = (k & 1) != 0;
-                        fa.fused_swap = 1;
-                        fa.sw = sa;
-                        fa.sw.cyc_k = k - 1;
-                        fa.sw.perm_in = odd ? pa : pb;
-                        fa.sw.E_in = odd ? ea : eb;
-                        fa.sw.perm = odd ? pb : pa;
-                        fa.sw.E = fa.E = odd ? eb : ea;
-                        fa.perm = fa.sw.perm;
-                    }
-                    r = launch_apt_quad(fa, lds, gs);
+            // cycle k's arguments: the exchange of cycle k - 1 first
+            auto cycle = [&](int k) {
+                AptArgs fa = qa;
+                fa.cyc_k = k;
+                if (k > 0) {
+                    const bool odd = (k & 1) != 0;
+                    fa.fused_swap = 1;
+                    fa.sw = sa;
+                    fa.sw.cyc_k = k - 1;
+                    fa.sw.perm_in = odd ? pa : pb;
+                    fa.sw.E_in = odd ? ea : eb;
+                    fa.sw.perm = odd ? pb : pa;
+                    fa.sw.E = fa.E = odd ? eb : ea;
+                    fa.perm = fa.sw.perm;
                 }
-                return r;
-            });
+                return fa;
+            };
+            if (words)
+                for (int k = 0; k < K && e == hipSuccess; ++k) e = launch_word_cycle(c, cycle(k), icm);
+            else
+                e = apt_on_groups(c, [&](hipStream_t gs, const QuadDesc *desc, int nb, size_t lds) {
+                    hipError_t r = hipSuccess;
+                    for (int k = 0; k < K && r == hipSuccess; ++k) {
+                        AptArgs fa = cycle(k);
+                        fa.desc = desc;
+                        fa.n_blocks = nb;
+                        r = launch_apt_quad(fa, lds, gs);
+                    }
+                    return r;
+                });
             static_assert(K % 2 == 0, "the last replica kernel must write the second buffers");
             SwapArgs last = sa;
             last.cyc_k = K - 1;
@@ -1754,7 +1900,8 @@ void run_apt(sg_ctx *c, int64_t n_cycles, int32_t sweeps_per_swap, const std::ve
         qa.cyc_k = 0;
         sa.cyc_k = 0;
         for (; done < n_cycles; ++done) {
-            hip_check(launch_apt_quad(qa, c->quad_lds, c->stream), "cycle");
+            hip_check(words ? launch_word_cycle(c, qa, icm) : launch_apt_quad(qa, c->quad_lds, c->stream),
+                      "cycle");
             hip_check(launch_apt_swap(sa, c->stream), "cycle");
             hip_check(launch_advance(c->d_ctr.p, S, 1u, 1u, 1u, c->stream), "cycle");
         }
@@ -2351,46 +2498,6 @@ double sigma_of_moments(int64_t S1, int64_t S2, int64_t N)
 
 }  // namespace
 
-// Work-group size of adapt_kernel: 1024 threads where no CU gets a second work-group and a phase
-// has more sites than kAdaptThreads (64 instances of L = 15 with 100 chains: 82 -> 75 ms), else
-// kAdaptThreads.
-int adaptive_threads(int64_t work_groups, int phase, int cus)
-{
-    return work_groups <= cus && phase > kAdaptThreads ? 1024 : kAdaptThreads;
-}
-
-// Chain words per instance in adapt_kernel, 0 for the chains as APT slots (a group of four per
-// work-group).  A site costs a work-group about 60 vector instructions and 50 per group, as a
-// tile of APT slots about 110 (its energies included).  A phase takes the longer of its
-// instructions' issue on the CU with the most work-groups and one thread's passes, whose dependent
-// instructions come about 2.5 times slower than they could issue; the cheapest split wins, so few
-// instances are cut into more, shorter words.  Measured against words of 32 chains (and APT slots
-// where those would not give every CU one): 64 instances of L = 15 with 100 chains (words of 7, 6,
-// 6, 6 groups, before 8, 8, 8, 1) 90 -> 75 ms; 4, 16 and 32 instances 1.56, 1.22 and 1.28 times
-// faster; 256 instances the same.
-int adaptive_words(int n_inst, int groups, int phase, int cus, int slot_threads)
-{
-    auto cost = [&](int words, double per_site_max, double per_site, int threads) {
-        const double on_cu = (double)(((int64_t)n_inst * words + cus - 1) / cus);
-        return std::max(on_cu * std::max(phase, 256) / 256.0 * per_site,
-                        2.5 * ((phase + threads - 1) / threads) * per_site_max);
-    };
-    int best = 0;
-    double best_cost = cost(groups, 110.0, 110.0, slot_threads);
-    for (int ng = 8; ng >= 2; --ng) {
-        const int nw = (groups + ng - 1) / ng;
-        const int top = (groups + nw - 1) / nw;   // groups of the fullest word
-        if (top < 2) continue;
-        const double c = cost(nw, 60.0 + 50.0 * top, 60.0 + 50.0 * groups / nw,
-                              adaptive_threads((int64_t)n_inst * nw, phase, cus));
-        if (c < best_cost) {
-            best_cost = c;
-            best = nw;
-        }
-    }
-    return best;
-}
-
 // The adaptive stage with up to 32 chains per word (adapt_kernel), for instances without
 // fields.  Returns false, having done nothing, when it does not apply; the caller then
 // runs the chains as APT slots.
@@ -2416,8 +2523,8 @@ bool adaptive_packed(sg_ctx *c, const sg_adaptive_params *p, double *beta_out,
     int planes = 1;
     while ((1 << planes) <= per_thread) ++planes;
     const size_t lds = sizeof(uint32_t) * (size_t)(max_npad + 1);
-    // + the kernel's static LDS: tables, energy counters, reduction scratch
-    const size_t lds_static = sizeof(uint32_t) * (kAdaptTabWords + kAdaptPlanes * nt + nt / 2 + 1 + 64);
+    // + the kernel's static LDS: tables, reduction scratch
+    const size_t lds_static = sizeof(uint32_t) * (kAdaptTabWords + nt / 2 + 1 + 64);
     if (planes > kAdaptPlanes || lds + lds_static > kMaxLds) return false;
     hipStream_t s = c->stream;
     AdaptArgs a{};

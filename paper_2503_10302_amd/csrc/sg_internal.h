@@ -150,6 +150,8 @@ struct AptArgs {
     int32_t boff;              // 1: rec_col holds neighbour byte offsets (kernel variant)
     int32_t threads;           // work-group size: 256, or 512 or 1024 with small
     int32_t small;             // 1: every instance has planes == 2 (kernel variant)
+    int32_t word_ng, word_full, planes;   // apt_word_kernel: quads of the first word_full words of
+                               //    an instance (the others hold one less); counter bits
     int32_t fused_swap;        // 1: first perform the replica exchange described by sw (the
                                //    previous cycle's attempt) for this work-group's slots,
                                //    reading sw.perm_in / sw.E_in and writing sw.perm and E
@@ -208,6 +210,9 @@ hipError_t launch_apt_init(const InstDev *inst_d, const QuadDesc *desc, int n_bl
                            uint8_t *spins, const int32_t *perm, uint32_t key0, uint32_t key1,
                            uint32_t tag, hipStream_t s);
 hipError_t launch_apt_quad(const AptArgs &a, size_t lds_bytes, hipStream_t s);
+// Sweeps of words of up to 32 slots (desc: {instance, word}; rec_col in index form; energies written
+// afresh; threads 512 or 1024).
+hipError_t launch_apt_words(const AptArgs &a, size_t lds_bytes, hipStream_t s);
 hipError_t launch_apt_swap(const SwapArgs &a, hipStream_t s);
 hipError_t launch_sqa_init(const SqaArgs &a, int n_inst, hipStream_t s);
 // DT-SQA kernel with a work-group of `threads` (a multiple of 64 in 128..1024).

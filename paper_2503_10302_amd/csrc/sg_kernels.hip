@@ -1228,12 +1228,12 @@ __device__ void swap_instance(const SwapArgs &A, int inst, int32_t *red)
 }
 
 // The exchange of the previous cycle done at the start of an APT work-group instead of
-// in a launch of its own: the same decisions as swap_instance for the work-group's four
-// logical slots (the work-group of a pair's lower slot counts it), and on quad 0 the
-// running minimum.  The new mapping and energies of the four slots go to lperm / lE
+// in a launch of its own: the same decisions as swap_instance for the work-group's ns
+// logical slots from 4 q on (the work-group of a pair's lower slot counts it), and on quad 0 the
+// running minimum.  The new mapping and energies of the slots go to lperm / lE
 // (LDS) and the mapping to A.perm.
-__device__ void fused_swap_quad(const SwapArgs &A, int slot_off, int inst, int q, int32_t *lperm,
-                                int32_t *lE)
+__device__ __forceinline__ void fused_swap_quad(const SwapArgs &A, int slot_off, int inst, int q, int ns,
+                                                int32_t *lperm, int32_t *lE)
 {
     // the instance's slot range and swap tables follow from its index alone, so these
     // reads need not wait for its descriptor
@@ -1241,7 +1241,7 @@ __device__ void fused_swap_quad(const SwapArgs &A, int slot_off, int inst, int q
     const int tid = threadIdx.x;
     const uint32_t a = A.ctr[2] + (uint32_t)A.cyc_k + 1u;
     const int32_t *pin = A.perm_in + slot_off, *ein = A.E_in + slot_off;
-    if (tid < 4) {
+    if (tid < ns) {
         // every load of the decision is issued before any of it is used: the slot's and
         // its partner's mapping and energy, the pair's table bounds, and the random word
         const int s = 4 * q + tid;
@@ -1452,6 +1452,14 @@ void apt_quad_kernel(AptArgs A)
         uint16_t *queue = (uint16_t *)(vis + ((npad + 31) >> 5) + 1);   // npad
         const int q = D.quad;
         const int slot_off = D.inst * A.nb4;   // == I.slot_off, without waiting for I
+        if (A.n_sweeps == 0 && A.do_icm && !A.fused_swap && A.do_energy == 1) {
+            // cluster moves alone: nothing to do for temperatures without one
+            const int b0 = A.reps == 4 ? q : 2 * q, b1 = A.reps == 4 ? q + 1 : 2 * q + 2;
+            bool any = false;
+            for (int b = b0; b < b1; ++b)
+                any = any || (A.reps >= 2 && b < A.sw.n_beta && A.icm_on[D.inst * A.sw.n_beta + b]);
+            if (!any) return;
+        }
         // The threshold rows are loaded by waves 1..3 while wave 0 makes the exchange, so that
         // the two chains of dependent loads overlap (the exchange ends with a barrier; without
         // it the gather's barrier orders the rows before the sweep).
@@ -1462,7 +1470,7 @@ void apt_quad_kernel(AptArgs A)
         int32_t e_in = 0;   // fused exchange: this slot's energy after it (threads 0..3)
         int32_t pq[4];
         if (A.fused_swap) {
-            fused_swap_quad(A.sw, slot_off, D.inst, q, red + 24, red + 28);
+            fused_swap_quad(A.sw, slot_off, D.inst, q, 4, red + 24, red + 28);
             for (int i = 0; i < 4; ++i) pq[i] = __builtin_amdgcn_readfirstlane(red[24 + i]);
             if (tid < 4) e_in = red[28 + tid];
         } else {
@@ -2396,8 +2404,9 @@ __global__ void best_key_energy_kernel(const uint64_t *key, int n, int64_t *out)
 // (planes c0, c1) and a 16-entry table read (plane c2), relative to lsite, the row moved
 // by the site's field and degree.  Groups run from the highest to the lowest so that the
 // borrow chain leaves chain b at bit b; the table reads of group g - 1 and the threshold
-// reads of group g are issued before group g's Philox block.  NG groups, unrolled.
-template <int NG>
+// reads of group g are issued before group g's Philox block.  NG groups, unrolled.  ROW: words
+// from one chain's threshold row to the next (0: one row for all).
+template <int NG, int ROW>
 __device__ __forceinline__ uint32_t adapt_groups(const uint32_t *lsite, const uint32_t *tab01,
                                                  const uint32_t *tab2, uint32_t e01, uint32_t o01,
                                                  uint32_t c2, uint32_t D, uint32_t C, uint32_t E,
@@ -2410,10 +2419,11 @@ __device__ __forceinline__ uint32_t adapt_groups(const uint32_t *lsite, const ui
 #pragma unroll
     for (int g = NG - 1; g >= 0; --g) {
         const uint32_t idx4 = s0v + s1v;
-        const uint32_t T3 = lds_word(lsite, idx4 >> 24);
-        const uint32_t T2 = lds_word(lsite, (idx4 >> 16) & 0xFFu);
-        const uint32_t T1 = lds_word(lsite, (idx4 >> 8) & 0xFFu);
-        const uint32_t T0 = lds_word(lsite, idx4 & 0xFFu);
+        const uint32_t *row = lsite + 4 * g * ROW;
+        const uint32_t T3 = lds_word(row + 3 * ROW, idx4 >> 24);
+        const uint32_t T2 = lds_word(row + 2 * ROW, (idx4 >> 16) & 0xFFu);
+        const uint32_t T1 = lds_word(row + ROW, (idx4 >> 8) & 0xFFu);
+        const uint32_t T0 = lds_word(row, idx4 & 0xFFu);
         const uint4 Ug = U;
         if (g > 0) {
             s0v = lds_word(tab01, pair_off(e01, o01, g - 1));
@@ -2439,11 +2449,11 @@ __device__ __forceinline__ uint32_t adapt_groups(const uint32_t *lsite, const ui
 
 // One colour phase of the adaptive stage's sweep: the sites of the phase are split over
 // the work-group's threads; each updates all chains of the word at its sites.
-template <int NG, int NT>
-__device__ __forceinline__ void adapt_phase(const AdaptArgs &A, const uint4 *rc, int cnt,
-                                            uint32_t *sp, const uint32_t *tab01,
-                                            const uint32_t *tab2, const uint32_t *lut,
-                                            const uint4 *ug, uint32_t c3, uint32_t vmask)
+template <int NG, int NT, int ROW>
+__device__ __forceinline__ void adapt_phase(const uint4 *rc, int cnt, uint32_t *sp,
+                                            const uint32_t *tab01, const uint32_t *tab2,
+                                            const uint32_t *lut, const uint4 *ug, uint32_t c3,
+                                            uint32_t vmask, int imax, uint32_t key0, uint32_t key1)
 {
     for (int i = threadIdx.x; i < cnt; i += NT) {
         const uint4 r = rc[i];
@@ -2461,18 +2471,122 @@ __device__ __forceinline__ void adapt_phase(const AdaptArgs &A, const uint4 *rc,
         const uint32_t c0 = s1 ^ s2, c1 = k1 ^ k2 ^ cy, c2 = (k1 & k2) | (cy & (k1 ^ k2));
         // the site's part of the table index, h - d + imax, moves the row
         const uint32_t *lsite = lut + ((int32_t)((r.x >> 25) & 63u) - 32 -
-                                       (int32_t)((r.x >> 16) & 7u) + A.imax);
+                                       (int32_t)((r.x >> 16) & 7u) + imax);
         uint32_t e01, o01;
         pair_planes(c0, c1, e01, o01);
         // the site's part of Philox rounds 0 and 1 (word 0 of the counter is j)
         const uint64_t pj = (uint64_t)0xD2511F53u * j;
-        const uint32_t B = (uint32_t)(pj >> 32) ^ c3 ^ A.key1;
+        const uint32_t B = (uint32_t)(pj >> 32) ^ c3 ^ key1;
         const uint64_t pb = (uint64_t)0xCD9E8D57u * B;
-        const uint32_t res = adapt_groups<NG>(lsite, tab01, tab2, e01, o01, c2,
+        const uint32_t res = adapt_groups<NG, ROW>(lsite, tab01, tab2, e01, o01, c2,
                                               (uint32_t)(pb >> 32), (uint32_t)pj, (uint32_t)pb, ug,
-                                              A.key0, A.key1);
+                                              key0, key1);
         sp[j] = res & vmask;
     }
+}
+
+// The spread tables of adapt_groups: bit i of a nibble -> byte i; table index = I + imax = 2 k +
+// (h - d + imax), k = c0 + 2 c1 + 4 c2, stored times 4 (byte offsets into the threshold row).
+__device__ __forceinline__ void adapt_tables(uint32_t *tabs, int tid, int threads)
+{
+    for (int e = tid; e < 272; e += threads) {
+        auto spread = [](uint32_t nib) {
+            return (nib & 1u) | ((nib & 2u) << 7) | ((nib & 4u) << 14) | ((nib & 8u) << 21);
+        };
+        const uint32_t lo = (uint32_t)e & 15u, hi = ((uint32_t)e >> 4) & 15u;
+        tabs[e] = e < 256 ? 8u * spread(lo) + 16u * spread(hi) : 32u * spread(lo);
+    }
+}
+
+// a += b for vertical counters (plane p = bit p of every chain's count), the carry into plane P.
+template <int P>
+__device__ __forceinline__ void vsum(uint32_t (&a)[P + 1], const uint32_t (&b)[P])
+{
+    uint32_t c = 0u;
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        const uint32_t x = a[p], y = b[p];
+        a[p] = x ^ y ^ c;
+        c = (x & y) | (c & (x | y));
+    }
+    a[P] = c;
+}
+
+// Doubles the lanes that vertical counters cover: every lane adds the counters of its partner.
+template <int P, int CTRL>
+__device__ __forceinline__ void vsum_dpp(const uint32_t (&a)[P], uint32_t (&o)[P + 1])
+{
+    uint32_t b[P];
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        o[p] = a[p];
+        b[p] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)a[p], CTRL, 0xF, 0xF, true);
+    }
+    vsum<P>(o, b);
+}
+
+template <int P>
+__device__ __forceinline__ void vsum_xor(const uint32_t (&a)[P], uint32_t (&o)[P + 1], int lanes)
+{
+    uint32_t b[P];
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        o[p] = a[p];
+        b[p] = (uint32_t)__shfl_xor((int)a[p], lanes, 64);
+    }
+    vsum<P>(o, b);
+}
+
+// Unsatisfied bonds of chain tid < 32 of the word over the lattice (0 in other threads).  Each
+// thread counts the +x, +y, +z bonds of its sites in a vertical counter of P bits, the three of a
+// site added first; the counters are then summed over a wave in that form (six additions of
+// counters, for all 32 chains at once) and over the waves through red [NT / 2].  Bits taken one
+// by one from every thread's counters took 700 instructions instead of 250.
+template <int NT, int P>
+__device__ __forceinline__ int32_t unsat_of_chain(const uint4 *recj, const uint32_t *sp, int n, int32_t *red)
+{
+    const int tid = threadIdx.x, lane = tid & 63;
+    uint32_t v[P];
+#pragma unroll
+    for (int p = 0; p < P; ++p) v[p] = 0u;
+    for (int j = tid; j < n; j += NT) {
+        const uint4 r = recj[j];
+        const uint32_t jn = r.x >> 19, wj = sp[j];
+        uint32_t x[3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const uint32_t nb = a == 0 ? (r.y & 0xFFFFu) : (a == 1 ? (r.z & 0xFFFFu) : (r.w & 0xFFFFu));
+            x[a] = nb == (uint32_t)n ? 0u : wj ^ sp[nb] ^ (0u - ((jn >> (2 * a)) & 1u));
+        }
+        const uint32_t s = x[0] ^ x[1] ^ x[2], c = (x[0] & x[1]) | (x[2] & (x[0] | x[1]));
+        const uint32_t d = v[0] & s;
+        v[0] ^= s;
+        uint32_t e = (v[1] & d) | (c & (v[1] | d));
+        v[1] ^= d ^ c;
+#pragma unroll
+        for (int p = 2; p < P; ++p) {
+            const uint32_t f = v[p] & e;
+            v[p] ^= e;
+            e = f;
+        }
+    }
+    uint32_t v1[P + 1], v2[P + 2], v3[P + 3], v4[P + 4], v5[P + 5], v6[P + 6];
+    vsum_dpp<P, 0xB1>(v, v1);           // lanes 2 k, 2 k + 1
+    vsum_dpp<P + 1, 0x4E>(v1, v2);      // quads
+    vsum_dpp<P + 2, 0x141>(v2, v3);     // half rows
+    vsum_dpp<P + 3, 0x140>(v3, v4);     // rows of 16
+    vsum_xor<P + 4>(v4, v5, 16);
+    vsum_xor<P + 5>(v5, v6, 32);
+    int32_t u = 0;
+#pragma unroll
+    for (int p = 0; p < P + 6; ++p) u |= (int32_t)(((v6[p] >> (lane & 31)) & 1u) << p);
+    if (lane < 32) red[(tid >> 6) * 32 + lane] = u;
+    __syncthreads();
+    u = 0;
+    if (tid < 32)
+#pragma unroll
+        for (int q = 0; q < NT / 64; ++q) u += red[q * 32 + tid];
+    return u;
 }
 
 // Work-group -> (instance, chain word) and the word's groups: the first n_full words of an
@@ -2530,9 +2644,8 @@ template <int NG, int NT>
 __global__ __launch_bounds__(NT) void adapt_kernel(AdaptArgs A)
 {
     // Static LDS: pair spread table of planes c0, c1 (256), spread table of c2 (16),
-    // threshold row (<= 64), per-thread counters for the energies, reduction scratch.
+    // threshold row (<= 64), reduction scratch.
     __shared__ uint32_t tabs[kAdaptTabWords];
-    __shared__ uint32_t vc[kAdaptPlanes * NT];
     constexpr int kWaves = NT / 64;
     __shared__ int32_t red[kWaves * 32 + 1];
     // group words of Philox rounds 0-1 (sqa_group_words) by sweep parity and group
@@ -2546,15 +2659,7 @@ __global__ __launch_bounds__(NT) void adapt_kernel(AdaptArgs A)
     uint32_t *gw = A.words + ((int64_t)inst * A.nw + W.w) * A.wstride;
     for (int i = tid; i <= npad; i += NT) sp[i] = i < npad ? gw[i] : 0u;
     uint32_t *tab01 = tabs, *tab2 = tabs + 256, *lut = tabs + 272;
-    for (int e = tid; e < 272; e += NT) {
-        // bit i of a nibble -> byte i; table index = I + imax = 2 k + (h - d + imax), k =
-        // c0 + 2 c1 + 4 c2, stored times 4 (byte offsets into the threshold row)
-        auto spread = [](uint32_t nib) {
-            return (nib & 1u) | ((nib & 2u) << 7) | ((nib & 4u) << 14) | ((nib & 8u) << 21);
-        };
-        const uint32_t lo = (uint32_t)e & 15u, hi = ((uint32_t)e >> 4) & 15u;
-        tabs[e] = e < 256 ? 8u * spread(lo) + 16u * spread(hi) : 32u * spread(lo);
-    }
+    adapt_tables(tabs, tid, NT);
     for (int i = tid; i < A.ni; i += NT) lut[i] = A.lut[(int64_t)inst * A.ni + i];
     // bonds along +x, +y, +z present (J != 0): E = 2 (unsatisfied) - bonds
     if (tid == 0) red[kWaves * 32] = 0;
@@ -2583,51 +2688,18 @@ __global__ __launch_bounds__(NT) void adapt_kernel(AdaptArgs A)
                     sqa_group_words(t + 1u, (uint32_t)(W.first + tid), A.key0, A.key1);
             const uint4 *rc = A.rec_col + I.rec_off + A.inst[inst].col_off[c];
             const int cnt = A.inst[inst].col_cnt[c];
-            if (ng == NG) adapt_phase<NG, NT>(A, rc, cnt, sp, tab01, tab2, lut, ug, c3, vmask);
-            else adapt_phase<NG - 1, NT>(A, rc, cnt, sp, tab01, tab2, lut, ug, c3, vmask);
+            if (ng == NG)
+                adapt_phase<NG, NT, 0>(rc, cnt, sp, tab01, tab2, lut, ug, c3, vmask, A.imax, A.key0, A.key1);
+            else
+                adapt_phase<NG - 1, NT, 0>(rc, cnt, sp, tab01, tab2, lut, ug, c3, vmask, A.imax, A.key0,
+                                           A.key1);
             __syncthreads();
         }
         if (sw >= A.mom_from) {
-            // unsatisfied bonds per chain: each thread adds the +x, +y, +z bonds of its
-            // sites into a vertical counter (plane p = bit p of every chain's count)
-            uint32_t v[kAdaptPlanes];
-#pragma unroll
-            for (int p = 0; p < kAdaptPlanes; ++p) v[p] = 0u;
-            for (int j = tid; j < n; j += NT) {
-                const uint4 r = A.rec_j[I.recj_off + j];
-                const uint32_t jn = r.x >> 19, wj = sp[j];
-                const uint32_t nbf[3] = {r.y & 0xFFFFu, r.z & 0xFFFFu, r.w & 0xFFFFu};
-#pragma unroll
-                for (int a = 0; a < 3; ++a) {
-                    if (nbf[a] == (uint32_t)n) continue;
-                    uint32_t carry = wj ^ sp[nbf[a]] ^ (0u - ((jn >> (2 * a)) & 1u));
-#pragma unroll
-                    for (int p = 0; p < kAdaptPlanes; ++p) {
-                        if (p >= A.planes) break;
-                        const uint32_t cp = v[p] & carry;
-                        v[p] ^= carry;
-                        carry = cp;
-                    }
-                }
-            }
-#pragma unroll
-            for (int p = 0; p < kAdaptPlanes; ++p)
-                if (p < A.planes) vc[p * NT + tid] = v[p];
-            __syncthreads();
-            // chain cc, sources part * 32 .. part * 32 + 31
-            const int cc = tid & 31, part = tid >> 5;
-            int32_t cntu = 0;
-            for (int src = part * 32; src < part * 32 + 32; ++src)
-#pragma unroll
-                for (int p = 0; p < kAdaptPlanes; ++p)
-                    if (p < A.planes) cntu += (int32_t)(((vc[p * NT + src] >> cc) & 1u) << p);
-            cntu += __shfl_xor(cntu, 32, 64);
-            if ((tid & 63) < 32) red[(tid >> 6) * 32 + cc] = cntu;
-            __syncthreads();
+            const uint4 *recj = A.rec_j + I.recj_off;
+            const int32_t u = A.planes <= 5 ? unsat_of_chain<NT, 5>(recj, sp, n, red)
+                                            : unsat_of_chain<NT, kAdaptPlanes>(recj, sp, n, red);
             if (tid < nch) {
-                int32_t u = 0;
-#pragma unroll
-                for (int q = 0; q < kWaves; ++q) u += red[q * 32 + tid];
                 const int64_t e = 2 * (int64_t)u - bonds;
                 S1 += e;
                 S2 += e * e;
@@ -2640,6 +2712,97 @@ __global__ __launch_bounds__(NT) void adapt_kernel(AdaptArgs A)
         int64_t *m = A.mom + ((int64_t)inst * A.n_chains + 4 * W.first + tid) * 2;
         m[0] = S1;
         m[1] = S2;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// APT sweeps with up to 32 slots per word: several sweeps per launch (no cluster moves, no fields).
+// One work-group per (instance, word of up to eight quads): its slots' lattices are gathered from
+// the physical buffers into one word per site (bit b = the word's slot b), swept as in the
+// adaptive stage with a threshold row per slot (rows 16 entries apart, so that a slot's row is an
+// immediate offset of its read), counted for the energies once at the end, and written back.
+// The four-slot tiles of apt_quad_kernel spend 24 vector instructions on a flip, half of them on
+// the site's record, neighbours, signs and energy sums that only four flips share; here 32 flips
+// share them and a flip takes 15.  The exchange before the sweeps is fused as there.
+// ---------------------------------------------------------------------------
+template <int NG, int NT>
+__global__ __launch_bounds__(NT) void apt_word_kernel(AptArgs A)
+{
+    __shared__ uint32_t tabs[256 + 16];
+    __shared__ uint32_t lut[32 * 16];
+    __shared__ int32_t red[NT / 2];
+    __shared__ int32_t slots[64];                        // physical buffers (energies past them)
+    __shared__ __align__(16) uint4 ugrp[2 * 8];          // by sweep parity and group
+    extern __shared__ __align__(16) uint32_t sp[];       // npad + 4 words
+    const QuadDesc D = A.desc[blockIdx.x];
+    if (D.inst < 0) return;
+    const InstDev I = A.inst[D.inst];
+    const int tid = threadIdx.x, n = I.n, npad = I.npad;
+    const int w = D.quad;
+    const int ng = w < A.word_full ? NG : NG - 1;
+    const int q0 = w < A.word_full ? w * NG : A.word_full * NG + (w - A.word_full) * (NG - 1);
+    const int slot_off = D.inst * A.nb4 + 4 * q0;
+    const uint32_t t0 = A.ctr[0] + (uint32_t)(A.cyc_k * A.n_sweeps);
+    const uint32_t c3 = ((uint32_t)D.inst << 4) | A.tag;
+    adapt_tables(tabs, tid, NT);
+    for (int e = tid; e < 64 * ng; e += NT) {
+        const int sl = e >> 4, k = e & 15;
+        lut[e] = k < A.ni ? A.lut[(int64_t)A.slot_lut[slot_off + sl] * A.ni + k] : 0u;
+    }
+    if (tid < ng) ugrp[tid] = sqa_group_words(t0, (uint32_t)(q0 + tid), A.key0, A.key1);
+    if (A.fused_swap) {
+        fused_swap_quad(A.sw, slot_off - 4 * q0, D.inst, q0, 4 * ng, slots, slots + 32);
+    } else {
+        if (tid < 4 * ng) slots[tid] = A.perm[slot_off + tid];
+        __syncthreads();
+    }
+    // four sites of every slot per thread: bytes 0/1 of eight slots to the bits of a byte, then
+    // the bytes of a site from the four accumulators
+    const uint8_t *gs = A.spins + I.spin_off;
+    uint32_t off[4 * NG];   // (an instance's buffers hold less than 2^31 bytes here)
+#pragma unroll
+    for (int i = 0; i < 4 * NG; ++i)
+        off[i] = (uint32_t)__builtin_amdgcn_readfirstlane(slots[i < 4 * ng ? i : 0]) * (uint32_t)npad;
+    for (int g = tid; g < (npad >> 2); g += NT) {
+        uint32_t a[4] = {0u, 0u, 0u, 0u}, o[4];
+#pragma unroll
+        for (int i = 0; i < 4 * NG; ++i)
+            if (i < 4 * ng) a[i >> 3] |= *(const uint32_t *)(gs + (off[i] + 4u * (uint32_t)g)) << (i & 7);
+        transpose_bytes(a[0], a[1], a[2], a[3], o);
+        *(uint4 *)(sp + 4 * g) = make_uint4(o[0], o[1], o[2], o[3]);
+    }
+    if (tid < 4) sp[npad + tid] = 0u;
+    __syncthreads();
+    for (int sw = 0; sw < A.n_sweeps; ++sw) {
+        const uint4 *ug = ugrp + 8 * (sw & 1);
+        for (int c = 0; c < I.n_colours; ++c) {
+            if (c == 0 && sw + 1 < A.n_sweeps && tid < ng)
+                ugrp[8 * ((sw + 1) & 1) + tid] =
+                    sqa_group_words(t0 + (uint32_t)sw + 1u, (uint32_t)(q0 + tid), A.key0, A.key1);
+            const uint4 *rc = A.rec_col + I.rec_off + A.inst[D.inst].col_off[c];
+            const int cnt = A.inst[D.inst].col_cnt[c];
+            if (ng == NG)
+                adapt_phase<NG, NT, 16>(rc, cnt, sp, tabs, tabs + 256, lut, ug, c3, 0xFFFFFFFFu, A.imax,
+                                        A.key0, A.key1);
+            else
+                adapt_phase<NG - 1, NT, 16>(rc, cnt, sp, tabs, tabs + 256, lut, ug, c3, 0xFFFFFFFFu, A.imax,
+                                            A.key0, A.key1);
+            __syncthreads();
+        }
+    }
+    // E = 2 (unsatisfied bonds) - bonds
+    const uint4 *recj = A.rec_j + I.recj_off;
+    const int32_t u = A.planes <= 5 ? unsat_of_chain<NT, 5>(recj, sp, n, red)
+                                    : unsat_of_chain<NT, kAdaptPlanes>(recj, sp, n, red);
+    if (tid < 4 * ng && 4 * q0 + tid < I.n_slots) A.E[slot_off + tid] = 2 * u - I.n_bonds;
+    uint8_t *gw = A.spins + I.spin_off;
+    for (int g = tid; g < (npad >> 2); g += NT) {
+        const uint4 o = *(const uint4 *)(sp + 4 * g);
+        uint32_t a[4];
+        transpose_bytes(o.x, o.y, o.z, o.w, a);
+#pragma unroll
+        for (int i = 0; i < 4 * NG; ++i)
+            if (i < 4 * ng) *(uint32_t *)(gw + (off[i] + 4u * (uint32_t)g)) = (a[i >> 3] >> (i & 7)) & 0x01010101u;
     }
 }
 
@@ -2693,6 +2856,34 @@ hipError_t launch_apt_quad(const AptArgs &a, size_t lds_bytes, hipStream_t s)
                           : launch_apt_quad_w<false, true, false>(a, lds_bytes, s);
     return a.ni <= 16 ? launch_apt_quad_w<true, false, false>(a, lds_bytes, s)
                       : launch_apt_quad_w<false, false, false>(a, lds_bytes, s);
+}
+
+template <int NG>
+hipError_t launch_apt_words_g(const AptArgs &a, size_t lds_bytes, hipStream_t s)
+{
+    const bool big = a.threads == 1024;
+    const void *k = big ? (const void *)apt_word_kernel<NG, 1024> : (const void *)apt_word_kernel<NG, 512>;
+    hipError_t e = allow_lds(k, lds_bytes);
+    if (e != hipSuccess) return e;
+    if (big)
+        hipLaunchKernelGGL((apt_word_kernel<NG, 1024>), dim3(a.n_blocks), dim3(1024), lds_bytes, s, a);
+    else
+        hipLaunchKernelGGL((apt_word_kernel<NG, 512>), dim3(a.n_blocks), dim3(512), lds_bytes, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_apt_words(const AptArgs &a, size_t lds_bytes, hipStream_t s)
+{
+    switch (a.word_ng) {
+    case 2: return launch_apt_words_g<2>(a, lds_bytes, s);
+    case 3: return launch_apt_words_g<3>(a, lds_bytes, s);
+    case 4: return launch_apt_words_g<4>(a, lds_bytes, s);
+    case 5: return launch_apt_words_g<5>(a, lds_bytes, s);
+    case 6: return launch_apt_words_g<6>(a, lds_bytes, s);
+    case 7: return launch_apt_words_g<7>(a, lds_bytes, s);
+    case 8: return launch_apt_words_g<8>(a, lds_bytes, s);
+    }
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_apt_swap(const SwapArgs &a, hipStream_t s)

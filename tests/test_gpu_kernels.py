@@ -152,3 +152,33 @@ def test_spins_in_and_out(mode, shapes):
         bad[last, ..., n:] = 7     # bytes past an instance's sites are not looked at
         ctx.set_spins(bad)
         assert np.array_equal(ctx.spins(), s)
+
+
+@pytest.mark.parametrize("shape,n_inst,n_beta,reps,S,cutoff", [
+    ((3, 4, 2), 520, 8, 1, 2, float("inf")), ((4, 3, 3), 520, 11, 1, 3, float("inf")),
+    ((2, 3, 4), 520, 4, 4, 2, float("inf")), ((3, 4, 2), 520, 10, 2, 5, 1.0),
+    ((3, 3, 2), 520, 12, 2, 6, 0.5), ((4, 2, 2), 520, 7, 4, 5, 1.0), ((3, 4, 2), 520, 15, 2, 2, float("inf")),
+    ((2, 2, 3), 300, 25, 4, 2, float("inf")), ((12, 12, 12), 12, 25, 4, 2, float("inf")),
+    ((5, 7, 3), 520, 16, 2, 5, 1.0)])
+def test_sweeps_in_words(shape, n_inst, n_beta, reps, S, cutoff):
+    """Several sweeps per cycle in words of 2 to 8 quads of slots (the last quad not full, words with
+    one quad less beside them, 512 and 1024 threads), cluster moves in launches of their own: a graph
+    of cycles, single ones and a sweep call."""
+    insts = [(ej_couplings(shape, 7, 800 + i)[0], 7, None) for i in range(n_inst)]
+    beta = geometric_ladder(n_beta, 0.2, 3.0)
+    cycles = 33 if np.prod(shape) < 200 else 2
+    ctx = sg.apt(insts, beta, SEED, reps_per_beta=reps)
+    trace = ctx.run_apt(cycles, S, cutoff, record_every=1)
+    ctx.sweep(3)
+    spins, E, counts = ctx.spins(), ctx.energy(), ctx.swap_counts()
+    for i in range(0, n_inst, max(1, n_inst // 24)):
+        lat = oracle.Lattice(*insts[i])
+        sp = oracle.apt_init(lat, i, n_beta * reps, SEED)
+        ctr, oE = np.zeros(3, np.uint32), np.zeros(n_beta * reps, np.int64)
+        best = np.array([np.iinfo(np.int64).max], np.int64)
+        rc, otr, oacc = oracle.apt_run(lat, i, beta, reps, SEED, cycles, S, cutoff, 1, ctr, sp, oE, best)
+        assert rc == 0 and np.array_equal(trace[i], otr) and np.array_equal(counts[i], oacc), f"instance {i}"
+        for k in range(3):
+            oracle.apt_sweep(lat, i, np.repeat(beta, reps), SEED, cycles * S + k, sp)
+        assert np.array_equal(spins[i], sp), f"spins, instance {i}"
+        assert E[i].tolist() == [oracle.energy(lat, v) for v in sp], f"energies, instance {i}"
