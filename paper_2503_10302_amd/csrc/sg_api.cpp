@@ -337,7 +337,7 @@ struct sg_ctx {
     DevBuf<int32_t> d_perm, d_E, d_slot_lut, d_tab_off, d_tab_len, d_icm_info;
     DevBuf<int32_t> d_perm2, d_E2;   // second mapping / energy buffers of the cycle graph
     DevBuf<uint32_t> d_lut, d_tab;
-    DevBuf<uint8_t> d_icm_on;
+    DevBuf<uint32_t> d_icm_on;
     DevBuf<int64_t> d_best, d_acc_count, d_mom, d_trace;
     DevBuf<int32_t> d_acc_out;
     DevBuf<QuadDesc> d_desc;
@@ -919,7 +919,7 @@ void create_apt(sg_ctx *c, const sg_config *cfg, const int8_t *const *colour = n
     c->d_acc_count.alloc((size_t)c->n_inst * (c->n_beta - 1) * c->reps, "swap counts");
     c->d_acc_out.alloc((size_t)c->n_inst * (c->n_beta - 1) * c->reps, "swap flags");
     c->d_icm_info.alloc((size_t)c->n_inst * c->n_beta * std::max(1, c->reps / 2) * 4, "icm info");
-    c->d_icm_on.alloc((size_t)c->n_inst * c->n_beta, "icm flags");
+    c->d_icm_on.alloc((size_t)c->n_inst * c->n_quads, "icm flags");
     c->d_ctr.alloc(8, "counters");
     std::vector<QuadDesc> desc = make_quad_descs(c->lat, c->n_quads, c->beta, c->n_beta, c->reps, 0);
     c->n_blocks = (int)desc.size();
@@ -955,12 +955,17 @@ void create_apt(sg_ctx *c, const sg_config *cfg, const int8_t *const *colour = n
     hip_check(launch_apt_quad(a, c->quad_lds, s), "initial energies");
 }
 
-// ICM applies at (instance i, temperature b) when beta[i][b] >= cutoff[i].
+// ICM applies at (instance i, temperature b) when beta[i][b] >= cutoff[i]; one word per quad, a bit
+// for each of its temperatures.
 void upload_icm_flags(sg_ctx *c, const std::vector<double> &cutoff)
 {
     if (c->icm_cutoff_loaded == cutoff) return;
-    std::vector<uint8_t> on((size_t)c->n_inst * c->n_beta);
-    for (size_t i = 0; i < on.size(); ++i) on[i] = c->beta[i] >= cutoff[i / c->n_beta] ? 1 : 0;
+    std::vector<uint32_t> on((size_t)c->n_inst * c->n_quads, 0u);
+    const int per = c->reps == 2 ? 2 : 1;   // temperatures per quad (one label: no pairs)
+    for (int i = 0; i < c->n_inst && c->reps >= 2; ++i)
+        for (int b = 0; b < c->n_beta; ++b)
+            if (c->beta[(size_t)i * c->n_beta + b] >= cutoff[(size_t)i])
+                on[(size_t)i * c->n_quads + b / per] |= 1u << (b % per);
     c->d_icm_on.upload(on.data(), on.size(), c->stream, "icm flags");
     hip_check(hipStreamSynchronize(c->stream), "icm flags");
     c->icm_cutoff_loaded = cutoff;

@@ -126,7 +126,8 @@ struct AptArgs {
     const int32_t *perm;       // logical slot -> physical buffer (per instance)
     const uint32_t *lut;       // heat-bath thresholds, NI per table
     const int32_t *slot_lut;   // logical slot -> table index
-    const uint8_t *icm_on;     // per (instance, beta index): ICM applies
+    const uint32_t *icm_on;    // per (instance, quad): bit k: ICM applies at the quad's k-th
+                               //    temperature (two labels: two of them, four: one)
     int32_t *E;                // energies per logical slot
     int64_t *mom;              // per logical slot {sum E, sum E^2} (adaptive stage)
     int32_t *icm_info;         // per (instance, beta, pair) {m, seed, size, branch}

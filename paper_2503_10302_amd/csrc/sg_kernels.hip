@@ -132,17 +132,19 @@ __device__ __forceinline__ uint32_t aligned_count(const uint32_t *sp, const uint
     return k;
 }
 
-// Sum over the 64 lanes of a wave (all lanes active): DPP exchanges inside each row of 16
-// lanes (pairs, quads, half rows, rows: no LDS round trips), then the four row sums read
-// from lanes 0, 16, 32 and 48.  The result is wave-uniform.
+// Sum over the 64 lanes of a wave (all lanes active), by lane moves of the vector unit (no LDS
+// round trips): inside each row of 16 lanes (pairs, quads, half rows, rows), then lane 15 of rows
+// 0 and 2 into the next row and lane 31 into the upper half; lane 63 holds the total.  The
+// result is wave-uniform.
 __device__ __forceinline__ int32_t wave_sum(int32_t v)
 {
     v += __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, false);    // quad_perm [1,0,3,2]
     v += __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, false);    // quad_perm [2,3,0,1]
     v += __builtin_amdgcn_update_dpp(0, v, 0x141, 0xF, 0xF, false);   // row_half_mirror
     v += __builtin_amdgcn_update_dpp(0, v, 0x140, 0xF, 0xF, false);   // row_mirror
-    return __builtin_amdgcn_readlane(v, 0) + __builtin_amdgcn_readlane(v, 16) +
-           __builtin_amdgcn_readlane(v, 32) + __builtin_amdgcn_readlane(v, 48);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);   // row_bcast15 into rows 1, 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);   // row_bcast31 into rows 2, 3
+    return __builtin_amdgcn_readlane(v, 63);
 }
 
 __device__ __forceinline__ int32_t wave_min(int32_t v)
@@ -1006,16 +1008,23 @@ __device__ __forceinline__ void cluster_wave(const uint4 *t, int lx, int ly, int
     }
 }
 
+template <int NT>
+constexpr int kSideWave = NT > 256 ? 4 : 3;
+
 // Thread (z, y) = (tid / 16, tid mod 16) of the first four waves holds row y of plane z for the
 // overlap, the sums over the cluster's boundary and the flips.  LDS: Qr, Vr, Sr [ly lz] each;
-// red[16..28], sums [NT / 16].  e4: this thread's energy changes of the four slots so far; the
-// return value is slot tid's total over the work-group, the move included, in threads 0..3.
+// red[16..31], sums [NT / 16].  e4: this thread's energy changes of the four slots so far; the
+// return value is slot i's total over the work-group, the move included, in lane i < 4 of wave
+// kSideWave.  That wave, which has no part of the search and few rows, also makes the random words
+// and the records, beside wave 0's chain.  (Totals fit 16 bits: an energy lies in +-3 n without
+// fields, n <= 4096; sums of changes may wrap on the way.)
 template <int NT>
 __device__ int32_t icm_pairs_wave(uint32_t *sp, const uint4 *rowP, int n, int lx, int ly, int lz, int np,
-                               uint32_t pa, uint32_t pb, uint32_t pidx0, uint32_t pidx1, uint32_t call,
-                               uint32_t c3p, uint32_t key0, uint32_t key1, uint32_t *Qr, int32_t *red,
+                                  uint32_t pa, uint32_t pb, uint32_t pidx0, uint32_t pidx1, uint32_t call,
+                                  uint32_t c3p, uint32_t key0, uint32_t key1, uint32_t *Qr, int32_t *red,
                                   int32_t *sums, int32_t *info0, int32_t *info1, int32_t e4[4])
 {
+    constexpr int kSide = kSideWave<NT>;
     uint32_t *Vr = Qr + ly * lz, *Sr = Vr + ly * lz;   // cluster; spins of each pair's first replica
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));   // (what follows from it is not kept from or for other parts)
@@ -1024,9 +1033,8 @@ __device__ int32_t icm_pairs_wave(uint32_t *sp, const uint4 *rowP, int n, int lx
     const bool own = y < ly && z < lz;
     const int r = z * ly + y;
     const int K = (lz + 3) >> 2;
-    // wave 0: the bond masks of its rows, and both pairs' random words (lane 1: pair 1)
+    // wave 0: the bond masks of its rows; the side wave: both pairs' random words (lane 1: pair 1)
     uint4 t[4];
-    uint4 uw = make_uint4(0u, 0u, 0u, 0u);
     if (wv == 0) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
@@ -1034,7 +1042,12 @@ __device__ int32_t icm_pairs_wave(uint32_t *sp, const uint4 *rowP, int n, int lx
             const int zz = (lane >> 4) * K + k;
             if (k < K && y < ly && zz < lz) t[k] = rowP[zz * ly + y];
         }
-        uw = philox10(lane == 1 ? pidx1 : pidx0, call, 0u, c3p, key0, key1);
+    } else if (wv == kSide) {
+        const uint4 uw = philox10(lane == 1 ? pidx1 : pidx0, call, 0u, c3p, key0, key1);
+        if (lane < 2) {
+            red[28 + lane] = (int32_t)(uw.y >> 31);
+            red[30 + lane] = (int32_t)uw.x;
+        }
     }
     if (own) {
         const uint2 f = fold_row16(sp + r * lx, lx);
@@ -1048,18 +1061,18 @@ __device__ int32_t icm_pairs_wave(uint32_t *sp, const uint4 *rowP, int n, int lx
         Qr[r] = q & all2;
         Sr[r] = s & all2;
     }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int32_t v = wave_sum(e4[i]);
-        if (lane == 0) sums[4 * wv + i] = v;
-        e4[i] = 0;
+    {
+        const int32_t e01 = wave_sum(e4[0] + (int32_t)((uint32_t)e4[1] << 16));
+        const int32_t e23 = wave_sum(e4[2] + (int32_t)((uint32_t)e4[3] << 16));
+        if (lane == 0) {
+            sums[2 * wv] = e01;
+            sums[2 * wv + 1] = e23;
+        }
+        e4[0] = e4[1] = e4[2] = e4[3] = 0;
     }
     __syncthreads();
     if (wv == 0) {
-        const uint32_t w0 = (uint32_t)__builtin_amdgcn_readlane((int)uw.x, 0);
-        const uint32_t w1 = (uint32_t)__builtin_amdgcn_readlane((int)uw.x, 1);
-        if (lane == 0) red[19] = (int32_t)(uw.y >> 31);
-        if (lane == 1) red[28] = (int32_t)(uw.y >> 31);
+        const uint32_t w0 = (uint32_t)red[30], w1 = (uint32_t)red[31];
         if (K == 4) cluster_wave<4>(t, lx, ly, lz, w0, w1, Qr, Vr, red);
         else if (K == 3) cluster_wave<3>(t, lx, ly, lz, w0, w1, Qr, Vr, red);
         else if (K == 2) cluster_wave<2>(t, lx, ly, lz, w0, w1, Qr, Vr, red);
@@ -1106,30 +1119,32 @@ __device__ int32_t icm_pairs_wave(uint32_t *sp, const uint4 *rowP, int n, int lx
     const int32_t z0 = sz & 0xFFFF, z1 = (int32_t)((uint32_t)sz >> 16);
     const int32_t d0 = (int32_t)(int16_t)db, d1 = (db - d0) >> 16;
     const bool big0 = 2 * z0 > n, big1 = 2 * z1 > n;
-    const int32_t br0 = red[19], br1 = red[28];
+    const int32_t br0 = red[28], br1 = red[29];
     const uint32_t mA0 = 1u << (8 * (pa & 3u)), mB0 = 1u << (8 * (pb & 3u));
     const uint32_t mA1 = 1u << (8 * ((pa >> 8) & 3u)), mB1 = 1u << (8 * ((pb >> 8) & 3u));
     int32_t v = 0;
-    if (tid < 4) {
+    if (wv == kSide && lane < 4) {
         // isoenergetic move (crossing bonds change sign, the partner's energy by the opposite
         // amount); a cluster of more than half the lattice flips one whole replica instead
 #pragma unroll
-        for (int w = 0; w < NT / 64; ++w) v += sums[4 * w + tid];
+        for (int w = 0; w < NT / 64; ++w) v += sums[2 * w + (lane >> 1)];
+        const int32_t low = (int32_t)(int16_t)v;
+        v = lane & 1 ? (int32_t)(int16_t)((uint32_t)(v - low) >> 16) : low;
         const int32_t c0 = m0 > 0 && !big0 ? 2 * d0 : 0, c1 = m1 > 0 && !big1 ? 2 * d1 : 0;
-        if (tid == (int)(pa & 3u)) v += c0;
-        if (tid == (int)(pb & 3u)) v -= c0;
+        if (lane == (int)(pa & 3u)) v += c0;
+        if (lane == (int)(pb & 3u)) v -= c0;
         if (np > 1) {
-            if (tid == (int)((pa >> 8) & 3u)) v += c1;
-            if (tid == (int)((pb >> 8) & 3u)) v -= c1;
+            if (lane == (int)((pa >> 8) & 3u)) v += c1;
+            if (lane == (int)((pb >> 8) & 3u)) v -= c1;
         }
-        int32_t *o = tid == 0 ? info0 : info1;
-        if (tid < np) {
-            const int32_t mp = tid ? m1 : m0;
-            const bool big = tid ? big1 : big0;
+        int32_t *o = lane == 0 ? info0 : info1;
+        if (lane < np) {
+            const int32_t mp = lane ? m1 : m0;
+            const bool big = lane ? big1 : big0;
             o[0] = mp;
-            o[1] = mp > 0 ? red[16 + tid] : -1;
-            o[2] = mp > 0 ? (tid ? z1 : z0) : 0;
-            o[3] = mp > 0 && big ? 1 + (tid ? br1 : br0) : 0;
+            o[1] = mp > 0 ? red[16 + lane] : -1;
+            o[2] = mp > 0 ? (lane ? z1 : z0) : 0;
+            o[3] = mp > 0 && big ? 1 + (lane ? br1 : br0) : 0;
         }
     }
     if (own) {
@@ -1452,14 +1467,10 @@ void apt_quad_kernel(AptArgs A)
         uint16_t *queue = (uint16_t *)(vis + ((npad + 31) >> 5) + 1);   // npad
         const int q = D.quad;
         const int slot_off = D.inst * A.nb4;   // == I.slot_off, without waiting for I
-        if (A.n_sweeps == 0 && A.do_icm && !A.fused_swap && A.do_energy == 1) {
-            // cluster moves alone: nothing to do for temperatures without one
-            const int b0 = A.reps == 4 ? q : 2 * q, b1 = A.reps == 4 ? q + 1 : 2 * q + 2;
-            bool any = false;
-            for (int b = b0; b < b1; ++b)
-                any = any || (A.reps >= 2 && b < A.sw.n_beta && A.icm_on[D.inst * A.sw.n_beta + b]);
-            if (!any) return;
-        }
+        // the tile's temperatures with a cluster move (loaded here, far ahead of their use)
+        const uint32_t icm_bits = A.do_icm ? A.icm_on[(slot_off >> 2) + q] : 0u;
+        // cluster moves alone: nothing to do without one
+        if (A.n_sweeps == 0 && A.do_icm && !A.fused_swap && A.do_energy == 1 && icm_bits == 0u) return;
         // The threshold rows are loaded by waves 1..3 while wave 0 makes the exchange, so that
         // the two chains of dependent loads overlap (the exchange ends with a barrier; without
         // it the gather's barrier orders the rows before the sweep).
@@ -1467,12 +1478,12 @@ void apt_quad_kernel(AptArgs A)
             const int i = e / ni;
             lut[e] = A.lut[(int64_t)A.slot_lut[slot_off + 4 * q + i] * ni + (e - i * ni)];
         }
-        int32_t e_in = 0;   // fused exchange: this slot's energy after it (threads 0..3)
+        int32_t e_in = 0;   // fused exchange: the energy of slot tid mod 4 after it
         int32_t pq[4];
         if (A.fused_swap) {
             fused_swap_quad(A.sw, slot_off, D.inst, q, 4, red + 24, red + 28);
             for (int i = 0; i < 4; ++i) pq[i] = __builtin_amdgcn_readfirstlane(red[24 + i]);
-            if (tid < 4) e_in = red[28 + tid];
+            e_in = red[28 + (tid & 3)];
         } else {
             for (int i = 0; i < 4; ++i) pq[i] = A.perm[slot_off + 4 * q + i];
         }
@@ -1519,7 +1530,7 @@ void apt_quad_kernel(AptArgs A)
         uint32_t V02 = 0u, V13 = 0u, C4 = 0u;
         const uint32_t rev4 = 2u * (uint32_t)A.imax * 0x01010101u;
         bool full_energy = A.do_energy == 2;
-        bool summed = false;   // e_sum of thread i < 4 already holds slot i's total change
+        bool summed = false;   // e_sum already holds slot i's total change (icm_pairs_wave)
         int32_t e_sum = 0;
         // threshold offsets: table of slot b at b * ni; with ni <= 16 the four byte offsets
         // of one site fit one word (index bytes + table starts, times 4)
@@ -1568,9 +1579,8 @@ void apt_quad_kernel(AptArgs A)
             }
         }
 
-        if (A.do_icm && A.reps >= 2) {
+        if (icm_bits != 0u) {
             const uint32_t a = A.ctr[1] + (uint32_t)A.cyc_k + 1u;
-            const int n_beta = I.n_slots / A.reps;
             const int npair = A.reps / 2;
             const uint4 *recj = A.rec_j + I.recj_off;
             // up to two pairs in this tile: bytes (pa, pb) and their record / random-word indices
@@ -1579,7 +1589,7 @@ void apt_quad_kernel(AptArgs A)
             if (A.reps == 2) {
                 for (int half = 0; half < 2; ++half) {
                     const int b = 2 * q + half;
-                    if (b >= n_beta || !A.icm_on[D.inst * n_beta + b]) continue;
+                    if (!((icm_bits >> half) & 1u)) continue;
                     pa |= (uint32_t)(2 * half) << (8 * np);
                     pb |= (uint32_t)(2 * half + 1) << (8 * np);
                     if (np) pidx1 = b; else pidx0 = b;
@@ -1587,7 +1597,7 @@ void apt_quad_kernel(AptArgs A)
                 }
             } else if (A.reps == 4) {
                 const int b = q;
-                if (b < n_beta && A.icm_on[D.inst * n_beta + b]) {
+                {
                     const uint4 wp = philox10((uint32_t)b, a, 0u,
                                               ((uint32_t)D.inst << 4) | TAG_ICM_PAIR, A.key0, A.key1);
                     const uint32_t pairing = (uint32_t)(((uint64_t)wp.x * 3u) >> 32);
@@ -1665,8 +1675,9 @@ void apt_quad_kernel(AptArgs A)
             }
         } else if (A.do_energy) {
             if (!summed) e_sum = block_sum4_last<NT>(dE, sums);
-            if (tid < 4) {
-                const int s = 4 * q + tid;
+            const int es = summed ? tid - 64 * kSideWave<NT> : tid;   // the thread's slot
+            if (es >= 0 && es < 4) {
+                const int s = 4 * q + es;
                 if (s < I.n_slots) {
                     if (A.fused_swap) A.E[I.slot_off + s] = e_in + e_sum;
                     else A.E[I.slot_off + s] += e_sum;
