@@ -324,6 +324,9 @@ struct sg_ctx {
     DevBuf<uint4> d_rec, d_recj;
     DevBuf<uint4> d_recb;      // APT: d_rec with byte offsets (empty when a lattice is too large)
     DevBuf<uint32_t> d_ctr;      // {sweeps/steps, icm calls, swap attempts, cycles, done}
+    // APT sweeps, ICM calls and swap attempts of single calls that d_ctr does not count yet: they go
+    // to the kernels as arguments, so that such a call needs no launch to advance the counters
+    uint32_t ctr_add[3] = {0, 0, 0};
     Timer timer;
     // events around every main kernel launch (DT-SQA kernel, APT cycle graph)
     std::vector<std::pair<hipEvent_t, hipEvent_t>> kev;
@@ -1010,6 +1013,8 @@ AptArgs apt_args(sg_ctx *c, int n_sweeps, int do_icm)
     a.nb4 = 4 * c->n_quads;
     a.fused_swap = 0;
     a.sw.n_beta = c->n_beta;
+    a.add_sweeps = c->ctr_add[0];
+    a.add_icm = c->ctr_add[1];
     a.waves = c->apt_waves;
     return a;
 }
@@ -1078,7 +1083,17 @@ SwapArgs swap_args(sg_ctx *c, int32_t *acc_out, int64_t *trace, int trace_cap, i
     a.reps = c->reps;
     a.n_inst = c->n_inst;
     a.cyc_k = 0;
+    a.add_swaps = c->ctr_add[2];
     return a;
+}
+
+// Brings d_ctr up to date (before launches that are captured or advance it themselves).
+void flush_counters(sg_ctx *c)
+{
+    uint32_t *p = c->ctr_add;
+    if (!(p[0] | p[1] | p[2])) return;
+    hip_check(launch_advance(c->d_ctr.p, p[0], p[1], p[2], 0u, c->stream), "counters");
+    p[0] = p[1] = p[2] = 0;
 }
 
 void require(sg_ctx *c, int mode)
@@ -1424,14 +1439,18 @@ hipError_t apt_on_groups(sg_ctx *c, F body)
 
 std::string apt_tune_key(const sg_ctx *c, int S, bool icm, int pairs)
 {
-    std::string k = "apt2/" + std::to_string(c->n_inst) + "/" + std::to_string(c->n_beta) + "/" +
+    std::string k = "apt3/" + std::to_string(c->n_inst) + "/" + std::to_string(c->n_beta) + "/" +
                     std::to_string(c->reps) + "/" + std::to_string(c->imax) + "/" + std::to_string(S) +
                     "/" + std::to_string((int)icm) + "/" + std::to_string(pairs);
     for (const InstDev &I : c->idev)
         k += ":" + std::to_string(I.n) + "," + std::to_string(I.n_colours) + "," +
              std::to_string(I.row_off >= 0) + std::to_string(I.planes);
-    k += "/";   // temperatures with cluster moves (their share of the cost)
-    for (const double &cut : c->icm_cutoff_loaded) k += std::to_string(cut) + ",";
+    // the share of temperatures with cluster moves, in sixteenths (per-instance cutoffs of another
+    // batch of the same shape make the same work: timing the candidates anew for them would cost
+    // more than most runs)
+    size_t on = 0;
+    for (size_t i = 0; i < c->beta.size(); ++i) on += c->beta[i] >= c->icm_cutoff_loaded[i / c->n_beta];
+    k += "/" + std::to_string((16 * on + c->beta.size() / 2) / c->beta.size());
     return k;
 }
 
@@ -1688,7 +1707,7 @@ sg_status sg_sweep(sg_ctx *c, int32_t n_sweeps)
                       ? launch_apt_words(word_args(c, a), c->word_lds, c->stream)
                       : launch_apt_quad(a, c->quad_lds, c->stream),
                   "sweep");
-        hip_check(launch_advance(c->d_ctr.p, (uint32_t)n_sweeps, 0u, 0u, 0u, c->stream), "sweep");
+        c->ctr_add[0] += (uint32_t)n_sweeps;
     });
 }
 
@@ -1702,13 +1721,14 @@ void icm_call(sg_ctx *c, const std::vector<double> &cut, int icm_pairs, int32_t 
     if (icm_applies(c, cut) && any_field(c))
         fail(SG_EUNSUPPORTED, "ICM with non-zero fields is not supported");
     upload_icm_flags(c, cut);
-    hip_check(launch_fill_u32((uint32_t *)c->d_icm_info.p, 0xFFFFFFFFu, (int64_t)c->d_icm_info.n,
-                              c->stream),
-              "icm");
+    if (info_host)
+        hip_check(launch_fill_u32((uint32_t *)c->d_icm_info.p, 0xFFFFFFFFu, (int64_t)c->d_icm_info.n,
+                                  c->stream),
+                  "icm");
     AptArgs a = apt_args(c, 0, 1);
     a.icm_pairs = icm_pairs;
     hip_check(launch_apt_quad(a, c->quad_lds, c->stream), "icm");
-    hip_check(launch_advance(c->d_ctr.p, 0u, 1u, 0u, 0u, c->stream), "icm");
+    ++c->ctr_add[1];
     if (info_host) {
         c->d_icm_info.download(info_host, c->d_icm_info.n, c->stream, "icm info");
         hip_check(hipStreamSynchronize(c->stream), "icm");
@@ -1773,7 +1793,7 @@ sg_status sg_swap(sg_ctx *c, int32_t *accepted_host)
         require(c, SG_APT);
         SwapArgs a = swap_args(c, accepted_host ? c->d_acc_out.p : nullptr, nullptr, 0, 0);
         hip_check(launch_apt_swap(a, c->stream), "swap");
-        hip_check(launch_advance(c->d_ctr.p, 0u, 0u, 1u, 0u, c->stream), "swap");
+        ++c->ctr_add[2];
         if (accepted_host) {
             c->d_acc_out.download(accepted_host, (size_t)c->n_inst * (c->n_beta - 1) * c->reps,
                                   c->stream, "swap");
@@ -1810,6 +1830,7 @@ void run_apt(sg_ctx *c, int64_t n_cycles, int32_t sweeps_per_swap, const std::ve
         const bool icm = icm_applies(c, cut);
         if (icm && any_field(c)) fail(SG_EUNSUPPORTED, "ICM with non-zero fields is not supported");
         if (n_cycles == 0) return;
+        flush_counters(c);
         upload_icm_flags(c, icm ? cut : std::vector<double>((size_t)c->n_inst,
                                                               std::numeric_limits<double>::infinity()));
         // Sweeps in words leave the configurations their cluster moves alone (nothing to choose
@@ -1838,15 +1859,11 @@ void run_apt(sg_ctx *c, int64_t n_cycles, int32_t sweeps_per_swap, const std::ve
         // and energies from one buffer pair and writes them to the other; a last
         // exchange launch after cycle K - 1 brings them back to the first pair.
         const int K = 32;
-        if (!c->gexec || c->g_sweeps != sweeps_per_swap || c->g_icm != (int)icm || c->g_record != rec ||
-            c->g_trace != trace || c->g_trace_cap != cap || c->g_pairs != icm_pairs) {
-            if (c->gexec) (void)hipGraphExecDestroy(c->gexec);
-            c->gexec = nullptr;
-            hipGraph_t g = nullptr;
-            hip_check(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal), "capture");
-            hipError_t e = hipSuccess;
-            int32_t *pa = c->d_perm.p, *pb = c->d_perm2.p, *ea = c->d_E.p, *eb = c->d_E2.p;
-            // cycle k's arguments: the exchange of cycle k - 1 first
+        int32_t *pa = c->d_perm.p, *pb = c->d_perm2.p, *ea = c->d_E.p, *eb = c->d_E2.p;
+        // n cycles (at most K) one after another, the exchange of each but the last at the start of
+        // the next one's replica kernel, then the last exchange and the counters
+        auto cycles = [&](int n) {
+            // cycle k's arguments
             auto cycle = [&](int k) {
                 AptArgs fa = qa;
                 fa.cyc_k = k;
@@ -1863,12 +1880,13 @@ void run_apt(sg_ctx *c, int64_t n_cycles, int32_t sweeps_per_swap, const std::ve
                 }
                 return fa;
             };
+            hipError_t e = hipSuccess;
             if (words)
-                for (int k = 0; k < K && e == hipSuccess; ++k) e = launch_word_cycle(c, cycle(k), icm);
+                for (int k = 0; k < n && e == hipSuccess; ++k) e = launch_word_cycle(c, cycle(k), icm);
             else
                 e = apt_on_groups(c, [&](hipStream_t gs, const QuadDesc *desc, int nb, size_t lds) {
                     hipError_t r = hipSuccess;
-                    for (int k = 0; k < K && r == hipSuccess; ++k) {
+                    for (int k = 0; k < n && r == hipSuccess; ++k) {
                         AptArgs fa = cycle(k);
                         fa.desc = desc;
                         fa.n_blocks = nb;
@@ -1876,13 +1894,22 @@ void run_apt(sg_ctx *c, int64_t n_cycles, int32_t sweeps_per_swap, const std::ve
                     }
                     return r;
                 });
-            static_assert(K % 2 == 0, "the last replica kernel must write the second buffers");
             SwapArgs last = sa;
-            last.cyc_k = K - 1;
-            last.perm_in = pb;
-            last.E_in = eb;
+            last.cyc_k = n - 1;
+            last.perm_in = n & 1 ? pa : pb;
+            last.E_in = n & 1 ? ea : eb;
             if (e == hipSuccess) e = launch_apt_swap(last, c->stream);
-            if (e == hipSuccess) e = launch_advance(c->d_ctr.p, K * S, K, K, K, c->stream);
+            const uint32_t m = (uint32_t)n;
+            if (e == hipSuccess) e = launch_advance(c->d_ctr.p, m * S, m, m, m, c->stream);
+            return e;
+        };
+        if (n_cycles >= K && (!c->gexec || c->g_sweeps != sweeps_per_swap || c->g_icm != (int)icm || c->g_record != rec ||
+            c->g_trace != trace || c->g_trace_cap != cap || c->g_pairs != icm_pairs)) {
+            if (c->gexec) (void)hipGraphExecDestroy(c->gexec);
+            c->gexec = nullptr;
+            hipGraph_t g = nullptr;
+            hip_check(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal), "capture");
+            const hipError_t e = cycles(K);
             hipError_t e2 = hipStreamEndCapture(c->stream, &g);
             hip_check(e, "capture launch");
             hip_check(e2, "end capture");
@@ -1902,14 +1929,7 @@ void run_apt(sg_ctx *c, int64_t n_cycles, int32_t sweeps_per_swap, const std::ve
             hip_check(hipGraphLaunch(c->gexec, c->stream), "graph launch");
             kernel_event(c, false);
         }
-        qa.cyc_k = 0;
-        sa.cyc_k = 0;
-        for (; done < n_cycles; ++done) {
-            hip_check(words ? launch_word_cycle(c, qa, icm) : launch_apt_quad(qa, c->quad_lds, c->stream),
-                      "cycle");
-            hip_check(launch_apt_swap(sa, c->stream), "cycle");
-            hip_check(launch_advance(c->d_ctr.p, S, 1u, 1u, 1u, c->stream), "cycle");
-        }
+        if (done < n_cycles) hip_check(cycles((int)(n_cycles - done)), "cycle");
         if (best_trace) {
             std::vector<int64_t> t((size_t)c->n_inst * cap);
             c->d_trace.download(t.data(), t.size(), c->stream, "trace");
@@ -2359,9 +2379,7 @@ sg_status sg_get_counters(sg_ctx *c, uint32_t *out3)
         c->d_ctr.download(v, 8, c->stream, "counters");
         hip_check(hipStreamSynchronize(c->stream), "counters");
         if (c->mode == SG_SQA) v[0] = c->sqa_steps;
-        out3[0] = v[0];
-        out3[1] = v[1];
-        out3[2] = v[2];
+        for (int k = 0; k < 3; ++k) out3[k] = v[k] + c->ctr_add[k];
     });
 }
 
@@ -2401,6 +2419,7 @@ sg_status sg_get_state(sg_ctx *c, void *blob, size_t *len)
         spins_to_host(c, 0, (int64_t)c->n_inst * (c->mode == SG_APT ? c->n_slots : c->R), c->n_max,
                       (int8_t *)(b + off));
         if (c->mode == SG_SQA) ctr[0] = c->sqa_steps;
+        for (int k = 0; k < 3; ++k) ctr[k] += c->ctr_add[k];
         std::memcpy(b + 24, ctr, 3 * sizeof *ctr);
         *len = need;
     });
@@ -2429,6 +2448,7 @@ sg_status sg_set_state(sg_ctx *c, const void *blob, size_t len)
         }
         uint32_t v[8] = {ctr[0], ctr[1], ctr[2], 0u, 0u, 0u, 0u, 0u};
         c->d_ctr.upload(v, 8, c->stream, "state");
+        c->ctr_add[0] = c->ctr_add[1] = c->ctr_add[2] = 0;
         if (c->mode == SG_SQA) c->sqa_steps = ctr[0];
         hip_check(hipStreamSynchronize(c->stream), "state");
     });

@@ -111,6 +111,7 @@ struct SwapArgs {
     int32_t reps;
     int32_t n_inst;
     int32_t cyc_k;             // cycle offset of this launch inside a captured graph
+    uint32_t add_swaps;        // attempts not yet in ctr[2]
 };
 
 struct AptArgs {
@@ -147,6 +148,7 @@ struct AptArgs {
     int32_t cyc_k;             // cycle offset of this launch inside a captured graph: the
                                // kernel uses sweep counter ctr[0] + cyc_k * n_sweeps and ICM
                                // call ctr[1] + cyc_k + 1; counters advance only between graphs
+    uint32_t add_sweeps, add_icm;   // sweeps and ICM calls not yet in ctr[0], ctr[1]
     int32_t waves;             // kernel variant: at least 8 or 7 (also for 0) waves per SIMD
     int32_t boff;              // 1: rec_col holds neighbour byte offsets (kernel variant)
     int32_t threads;           // work-group size: 256, or 512 or 1024 with small

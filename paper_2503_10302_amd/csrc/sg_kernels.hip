@@ -1196,7 +1196,7 @@ __device__ void swap_instance(const SwapArgs &A, int inst, int32_t *red)
     const InstDev &I = A.inst[inst];
     const int R = A.reps, nb = A.n_beta;
     const int npt = (nb - 1) * R;
-    const uint32_t a = A.ctr[2] + (uint32_t)A.cyc_k + 1u;
+    const uint32_t a = A.ctr[2] + A.add_swaps + (uint32_t)A.cyc_k + 1u;
     const int32_t *pin = A.perm_in + I.slot_off, *ein = A.E_in + I.slot_off;
     int32_t *perm = A.perm + I.slot_off;
     int32_t *E = A.E + I.slot_off;
@@ -1254,7 +1254,7 @@ __device__ __forceinline__ void fused_swap_quad(const SwapArgs &A, int slot_off,
     // reads need not wait for its descriptor
     const int n_slots = A.n_beta * A.reps, swap_off = inst * (A.n_beta - 1);
     const int tid = threadIdx.x;
-    const uint32_t a = A.ctr[2] + (uint32_t)A.cyc_k + 1u;
+    const uint32_t a = A.ctr[2] + A.add_swaps + (uint32_t)A.cyc_k + 1u;
     const int32_t *pin = A.perm_in + slot_off, *ein = A.E_in + slot_off;
     if (tid < ns) {
         // every load of the decision is issued before any of it is used: the slot's and
@@ -1518,7 +1518,7 @@ void apt_quad_kernel(AptArgs A)
         if (tid < 4) sp[npad + tid] = 0u;
         __syncthreads();
 
-        const uint32_t t0 = A.ctr[0] + (uint32_t)(A.cyc_k * A.n_sweeps);
+        const uint32_t t0 = A.ctr[0] + A.add_sweeps + (uint32_t)(A.cyc_k * A.n_sweeps);
         const uint32_t c3 = ((uint32_t)D.inst << 4) | A.tag;
         // this thread's share of each slot's energy change in this launch
         int32_t dE[4] = {0, 0, 0, 0};
@@ -1580,7 +1580,7 @@ void apt_quad_kernel(AptArgs A)
         }
 
         if (icm_bits != 0u) {
-            const uint32_t a = A.ctr[1] + (uint32_t)A.cyc_k + 1u;
+            const uint32_t a = A.ctr[1] + A.add_icm + (uint32_t)A.cyc_k + 1u;
             const int npair = A.reps / 2;
             const uint4 *recj = A.rec_j + I.recj_off;
             // up to two pairs in this tile: bytes (pa, pb) and their record / random-word indices
@@ -2753,7 +2753,7 @@ __global__ __launch_bounds__(NT) void apt_word_kernel(AptArgs A)
     const int ng = w < A.word_full ? NG : NG - 1;
     const int q0 = w < A.word_full ? w * NG : A.word_full * NG + (w - A.word_full) * (NG - 1);
     const int slot_off = D.inst * A.nb4 + 4 * q0;
-    const uint32_t t0 = A.ctr[0] + (uint32_t)(A.cyc_k * A.n_sweeps);
+    const uint32_t t0 = A.ctr[0] + A.add_sweeps + (uint32_t)(A.cyc_k * A.n_sweeps);
     const uint32_t c3 = ((uint32_t)D.inst << 4) | A.tag;
     adapt_tables(tabs, tid, NT);
     for (int e = tid; e < 64 * ng; e += NT) {

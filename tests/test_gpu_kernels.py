@@ -182,3 +182,53 @@ def test_sweeps_in_words(shape, n_inst, n_beta, reps, S, cutoff):
             oracle.apt_sweep(lat, i, np.repeat(beta, reps), SEED, cycles * S + k, sp)
         assert np.array_equal(spins[i], sp), f"spins, instance {i}"
         assert E[i].tolist() == [oracle.energy(lat, v) for v in sp], f"energies, instance {i}"
+
+
+@pytest.mark.parametrize("code", [0, 14])
+def test_calls_and_short_runs_interleaved(code):
+    """Single calls (whose steps the device counters learn of later) between runs of every kind of
+    length, in one and two launch groups, with a checkpoint taken in between."""
+    insts = [(ej_couplings(s, 7, 900 + i)[0], 7, None) for i, s in enumerate([(5, 4, 3), (4, 4, 4), (3, 3, 3)])]
+    beta, reps = geometric_ladder(6, 0.3, 2.5), 2
+    ctx = sg.apt(insts, beta, SEED, reps_per_beta=reps)
+    ctx.set_launch_config(code)
+    lats = [oracle.Lattice(*x) for x in insts]
+    sps = [oracle.apt_init(lat, i, 12, SEED) for i, lat in enumerate(lats)]
+    ctr = np.zeros((3, 3), np.uint32)
+    Es = [np.array([oracle.energy(lat, v) for v in sp], np.int64) for lat, sp in zip(lats, sps)]
+    best = [np.array([np.iinfo(np.int64).max], np.int64) for _ in lats]
+
+    def check(what):
+        g, E, b = ctx.spins(), ctx.energy(), ctx.best()
+        assert ctx.counters().tolist() == ctr[0].tolist(), what
+        for i, lat in enumerate(lats):
+            assert np.array_equal(g[i, :, :lat.n], sps[i]), f"{what}, spins {i}"
+            assert E[i].tolist() == [oracle.energy(lat, v) for v in sps[i]], f"{what}, energies {i}"
+            assert ctr[0, 2] == 0 or b[i] == best[i][0], f"{what}, minimum {i}"
+
+    for step, n in enumerate((1, 2, 3, 31, 33, 5, 64, 34)):
+        ctx.sweep(2)
+        ctx.icm(0.8)
+        acc = ctx.swap()
+        trace = ctx.run_apt(n, 1, 0.8, record_every=1)
+        for i, lat in enumerate(lats):
+            for k in range(2):
+                oracle.apt_sweep(lat, i, np.repeat(beta, reps), SEED, int(ctr[i, 0]) + k, sps[i])
+            oracle.apt_icm(lat, i, beta, reps, 0.8, SEED, int(ctr[i, 1]) + 1, sps[i])
+            Es[i][:] = [oracle.energy(lat, v) for v in sps[i]]
+            oacc = oracle.apt_swap(i, beta, reps, SEED, int(ctr[i, 2]) + 1, sps[i], Es[i])
+            assert np.array_equal(acc[i], oacc)
+            best[i][0] = min(best[i][0], Es[i].min())
+            ctr[i] += np.array([2, 1, 1], np.uint32)
+            rc, otr, _ = oracle.apt_run(lat, i, beta, reps, SEED, n, 1, 0.8, 1, ctr[i], sps[i], Es[i], best[i])
+            assert rc == 0 and np.array_equal(trace[i], otr), f"trace of {n} cycles, instance {i}"
+        check(f"after {n} cycles")
+        if step == 3:
+            ctx.sweep(1)
+            blob = ctx.get_state()
+            ctx.sweep(3)
+            ctx.set_state(blob)
+            for i, lat in enumerate(lats):
+                oracle.apt_sweep(lat, i, np.repeat(beta, reps), SEED, int(ctr[i, 0]), sps[i])
+                ctr[i, 0] += 1
+            check("after the checkpoint")
