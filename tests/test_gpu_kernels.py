@@ -113,6 +113,19 @@ def test_sqa_group_counts(M, h_max):
         assert E[i].min() == oE
 
 
+@pytest.mark.parametrize("steps", [128, 129, 289])
+def test_sqa_schedule_in_launches(steps):
+    """A schedule whose launches (32, 256 and remaining steps) take their own threshold tables."""
+    J, h = ej_couplings((3, 2, 2), 7, 520, h_max=1)
+    gam = np.linspace(3.0, 0.1, steps)
+    ctx = sg.sqa([(J, 7, h)], 6, 2, 3.0, SEED)
+    bE, _ = ctx.sqa_anneal(gam)
+    lat = oracle.Lattice(J, 7, h)
+    sp = oracle.sqa_init(lat, 0, 6, 2, SEED)
+    oE, _, _ = oracle.sqa_anneal(lat, 0, 6, 2, 3.0, gam, SEED, 0, sp)
+    assert np.array_equal(ctx.spins()[0], sp) and bE[0] == oE
+
+
 @pytest.mark.parametrize("mode", ["apt", "sqa"])
 @pytest.mark.parametrize("shapes", [[(1, 1, 1)], [(3, 1, 1), (5, 7, 3)], [(15, 15, 15), (4, 4, 4), (11, 9, 13)]])
 def test_spins_in_and_out(mode, shapes):
