@@ -1471,6 +1471,12 @@ void apt_quad_kernel(AptArgs A)
         const uint32_t icm_bits = A.do_icm ? A.icm_on[(slot_off >> 2) + q] : 0u;
         // cluster moves alone: nothing to do without one
         if (A.n_sweeps == 0 && A.do_icm && !A.fused_swap && A.do_energy == 1 && icm_bits == 0u) return;
+        // A tile that ends with a cluster move sweeps first: resident work-groups run in step, and
+        // with the same priority for all of them every search, one wave of dependent steps, would run
+        // after every sweep instead of beside the other tiles' sweeps.  64 L = 15 instances of 32
+        // temperatures x 4 replicas: 45 -> 40 us a cycle (40 -> 38 with two launch groups); 256 mixed
+        // ones: within 1 %.  (Held through the search, it takes issue slots from the mixed sweeps: +2 %.)
+        if (icm_bits) __builtin_amdgcn_s_setprio(2);
         // The threshold rows are loaded by waves 1..3 while wave 0 makes the exchange, so that
         // the two chains of dependent loads overlap (the exchange ends with a barrier; without
         // it the gather's barrier orders the rows before the sweep).
@@ -1580,6 +1586,7 @@ void apt_quad_kernel(AptArgs A)
         }
 
         if (icm_bits != 0u) {
+            __builtin_amdgcn_s_setprio(0);
             const uint32_t a = A.ctr[1] + A.add_icm + (uint32_t)A.cyc_k + 1u;
             const int npair = A.reps / 2;
             const uint4 *recj = A.rec_j + I.recj_off;
