@@ -1437,9 +1437,46 @@ hipError_t apt_on_groups(sg_ctx *c, F body)
     return eb != hipSuccess ? eb : ej;
 }
 
+// Cycle k's arguments in a chain of launches: the exchange of cycle k - 1 runs at the start of cycle
+// k's replica kernel, which reads the mapping and energies from one buffer pair and writes them to
+// the other.
+AptArgs chain_cycle(const sg_ctx *c, const AptArgs &qa, const SwapArgs &sa, int k)
+{
+    AptArgs fa = qa;
+    fa.cyc_k = k;
+    if (k > 0) {
+        int32_t *pa = c->d_perm.p, *pb = c->d_perm2.p, *ea = c->d_E.p, *eb = c->d_E2.p;
+        const bool odd = (k & 1) != 0;
+        fa.fused_swap = 1;
+        fa.sw = sa;
+        fa.sw.cyc_k = k - 1;
+        fa.sw.perm_in = odd ? pa : pb;
+        fa.sw.E_in = odd ? ea : eb;
+        fa.sw.perm = odd ? pb : pa;
+        fa.sw.E = fa.E = odd ? eb : ea;
+        fa.perm = fa.sw.perm;
+    }
+    return fa;
+}
+
+// n cycles in tiles, the exchange of each but the last at the start of the next one's launch.
+hipError_t launch_chain(sg_ctx *c, const AptArgs &qa, const SwapArgs &sa, int n)
+{
+    return apt_on_groups(c, [&](hipStream_t gs, const QuadDesc *desc, int nb, size_t lds) {
+        hipError_t r = hipSuccess;
+        for (int k = 0; k < n && r == hipSuccess; ++k) {
+            AptArgs fa = chain_cycle(c, qa, sa, k);
+            fa.desc = desc;
+            fa.n_blocks = nb;
+            r = launch_apt_quad(fa, lds, gs);
+        }
+        return r;
+    });
+}
+
 std::string apt_tune_key(const sg_ctx *c, int S, bool icm, int pairs)
 {
-    std::string k = "apt3/" + std::to_string(c->n_inst) + "/" + std::to_string(c->n_beta) + "/" +
+    std::string k = "apt4/" + std::to_string(c->n_inst) + "/" + std::to_string(c->n_beta) + "/" +
                     std::to_string(c->reps) + "/" + std::to_string(c->imax) + "/" + std::to_string(S) +
                     "/" + std::to_string((int)icm) + "/" + std::to_string(pairs);
     for (const InstDev &I : c->idev)
@@ -1456,10 +1493,13 @@ std::string apt_tune_key(const sg_ctx *c, int S, bool icm, int pairs)
 
 std::map<std::string, int> g_apt_tune_cache;   // guarded by g_tune_mu
 
-// Candidates: the six work-group orders x {7, 8} waves per SIMD and the three two-group
-// splits, each timed over 32 replica-kernel launches of the run's shape (sweeps, cluster
-// moves), best of five; the state is saved before and restored after, so the context is
-// unchanged.  The pick is cached per workload shape for the process and on disk.
+// Candidates: the six work-group orders x {7, 8} waves per SIMD, each timed over 32 replica-kernel
+// launches of the run's shape (sweeps, cluster moves), best of five; then the best of them against
+// the three two-group splits, each as a graph of 32 cycles (the form a run launches: outside a graph
+// the two streams' launches can be held up by the host or by a shared hardware queue, and on some
+// machines a split that runs 256 mixed instances in 4.4 ms lost to an order that takes 4.9).  The
+// state is saved before and restored after, so the context is unchanged.  The pick is cached per
+// workload shape for the process and on disk.
 void apt_autotune(sg_ctx *c, int S, bool icm, int pairs)
 {
     const std::string key = apt_tune_key(c, S, icm, pairs);
@@ -1500,26 +1540,52 @@ void apt_autotune(sg_ctx *c, int S, bool icm, int pairs)
         hipError_t err = hipSuccess;
         try {
             for (int rep = 0; rep < 5 && err == hipSuccess; ++rep)
-                for (int code = 1; code <= kAptConfigs && err == hipSuccess; ++code) {
+                for (int code = 1; code <= 2 * kAptOrders && err == hipSuccess; ++code) {
                     apply_apt_config(c, code);
                     AptArgs a = apt_args(c, S, icm ? 1 : 0);
                     a.icm_pairs = pairs;
                     err = hipEventRecord(e0, st);
-                    if (err == hipSuccess)
-                        err = apt_on_groups(c, [&](hipStream_t gs, const QuadDesc *desc, int nb, size_t lds) {
-                            AptArgs b = a;
-                            b.desc = desc;
-                            b.n_blocks = nb;
-                            hipError_t r = hipSuccess;
-                            for (int k = 0; k < 32 && r == hipSuccess; ++k) r = launch_apt_quad(b, lds, gs);
-                            return r;
-                        });
+                    for (int k = 0; k < 32 && err == hipSuccess; ++k) err = launch_apt_quad(a, c->quad_lds, st);
                     if (err == hipSuccess) err = hipEventRecord(e1, st);
                     if (err == hipSuccess) err = hipEventSynchronize(e1);
                     float ms = 0.f;
                     if (err == hipSuccess) err = hipEventElapsedTime(&ms, e0, e1);
                     if (err == hipSuccess) best_ms[code] = std::min(best_ms[code], ms);
                 }
+            pick = 1;
+            for (int code = 2; code <= 2 * kAptOrders; ++code)
+                if (best_ms[code] < best_ms[pick]) pick = code;
+            // (launches without sweeps are made in one group)
+            if (c->n_inst > 1 && S > 0 && err == hipSuccess) {
+                best_ms[pick] = std::numeric_limits<float>::infinity();
+                for (int code : {pick, 2 * kAptOrders + 1, 2 * kAptOrders + 2, 2 * kAptOrders + 3}) {
+                    apply_apt_config(c, code);
+                    AptArgs a = apt_args(c, S, icm ? 1 : 0);
+                    a.icm_pairs = pairs;
+                    hipGraph_t g = nullptr;
+                    hipGraphExec_t x = nullptr;
+                    err = hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal);
+                    if (err != hipSuccess) break;
+                    err = launch_chain(c, a, swap_args(c, nullptr, nullptr, 0, 0), 32);
+                    const hipError_t end = hipStreamEndCapture(st, &g);
+                    if (err == hipSuccess) err = end;
+                    if (err == hipSuccess) err = hipGraphInstantiate(&x, g, nullptr, nullptr, 0);
+                    if (g) (void)hipGraphDestroy(g);
+                    for (int rep = 0; rep < 4 && err == hipSuccess; ++rep) {
+                        err = hipEventRecord(e0, st);
+                        if (err == hipSuccess) err = hipGraphLaunch(x, st);
+                        if (err == hipSuccess) err = hipEventRecord(e1, st);
+                        if (err == hipSuccess) err = hipEventSynchronize(e1);
+                        float ms = 0.f;
+                        if (err == hipSuccess) err = hipEventElapsedTime(&ms, e0, e1);
+                        if (err == hipSuccess) best_ms[code] = std::min(best_ms[code], ms);
+                    }
+                    if (x) (void)hipGraphExecDestroy(x);
+                    if (err != hipSuccess) break;
+                }
+                for (int code = 2 * kAptOrders + 1; code <= kAptConfigs; ++code)
+                    if (best_ms[code] < best_ms[pick]) pick = code;
+            }
         } catch (...) {
             (void)hipEventDestroy(e0);
             (void)hipEventDestroy(e1);
@@ -1537,9 +1603,6 @@ void apt_autotune(sg_ctx *c, int S, bool icm, int pairs)
         restore(c->d_mom, s_mom);
         restore(c->d_ctr, s_ctr);
         hip_check(hipStreamSynchronize(st), "autotune restore");
-        pick = 1;
-        for (int code = 2; code <= kAptConfigs; ++code)
-            if (best_ms[code] < best_ms[pick]) pick = code;
         tune_disk_store(key, pick);
     }
     {
@@ -1854,46 +1917,20 @@ void run_apt(sg_ctx *c, int64_t n_cycles, int32_t sweeps_per_swap, const std::ve
         // Replay a captured graph of K cycles.  Inside the graph cycle k reads
         // its step numbers as (counters + k * per-cycle increments); one
         // one-thread kernel at the end advances the counters by K cycles, so
-        // the same graph is valid on every replay.  The exchange of cycle k - 1
-        // runs at the start of cycle k's replica kernel, which reads the mapping
-        // and energies from one buffer pair and writes them to the other; a last
-        // exchange launch after cycle K - 1 brings them back to the first pair.
+        // the same graph is valid on every replay.  The exchanges are fused
+        // (chain_cycle); a last exchange launch after cycle K - 1 brings mapping
+        // and energies back to the first buffer pair.
         const int K = 32;
         int32_t *pa = c->d_perm.p, *pb = c->d_perm2.p, *ea = c->d_E.p, *eb = c->d_E2.p;
         // n cycles (at most K) one after another, the exchange of each but the last at the start of
         // the next one's replica kernel, then the last exchange and the counters
         auto cycles = [&](int n) {
-            // cycle k's arguments
-            auto cycle = [&](int k) {
-                AptArgs fa = qa;
-                fa.cyc_k = k;
-                if (k > 0) {
-                    const bool odd = (k & 1) != 0;
-                    fa.fused_swap = 1;
-                    fa.sw = sa;
-                    fa.sw.cyc_k = k - 1;
-                    fa.sw.perm_in = odd ? pa : pb;
-                    fa.sw.E_in = odd ? ea : eb;
-                    fa.sw.perm = odd ? pb : pa;
-                    fa.sw.E = fa.E = odd ? eb : ea;
-                    fa.perm = fa.sw.perm;
-                }
-                return fa;
-            };
             hipError_t e = hipSuccess;
             if (words)
-                for (int k = 0; k < n && e == hipSuccess; ++k) e = launch_word_cycle(c, cycle(k), icm);
+                for (int k = 0; k < n && e == hipSuccess; ++k)
+                    e = launch_word_cycle(c, chain_cycle(c, qa, sa, k), icm);
             else
-                e = apt_on_groups(c, [&](hipStream_t gs, const QuadDesc *desc, int nb, size_t lds) {
-                    hipError_t r = hipSuccess;
-                    for (int k = 0; k < n && r == hipSuccess; ++k) {
-                        AptArgs fa = cycle(k);
-                        fa.desc = desc;
-                        fa.n_blocks = nb;
-                        r = launch_apt_quad(fa, lds, gs);
-                    }
-                    return r;
-                });
+                e = launch_chain(c, qa, sa, n);
             SwapArgs last = sa;
             last.cyc_k = n - 1;
             last.perm_in = n & 1 ? pa : pb;
