@@ -2311,31 +2311,38 @@ __global__ __launch_bounds__(256) void apt_spins_out_kernel(const uint8_t *spins
 
 // DT-SQA spins of the replicas (all instances' in turn) row0 + blockIdx.y as +1/-1 bytes, M rows
 // of `stride` per replica: slice k = 2 h + p is bit h of word p.  A thread holds the words of four
-// sites for all slices, so every word is read once (132 MB of spins: 110 -> 40 us, against a
-// byte per thread and a read of the words for every slice).
+// sites for `per` slices, all of them where the rows fill the chip, so that every word is read once
+// (132 MB of spins: 110 -> 40 us, against a byte per thread and a read of the words for every slice).
 __global__ __launch_bounds__(256) void sqa_spins_out_kernel(const uint32_t *words, const InstDev *inst,
-                                                            int R, int M, int64_t row0, int stride,
-                                                            int8_t *out)
+                                                            int R, int M, int per, int64_t row0,
+                                                            int stride, int8_t *out)
 {
+    const int k0 = per * blockIdx.z, k1 = min(M, k0 + per);
     const int64_t row = row0 + blockIdx.y;
     const int i = (int)(row / R), r = (int)(row - (int64_t)i * R);
     const InstDev I = inst[i];
     const uint32_t *g = words + I.spin_off + (int64_t)r * I.npad * 2;
     int8_t *dst = out + (int64_t)blockIdx.y * M * stride;
     for (int j = 4 * (blockIdx.x * 256 + threadIdx.x); j < stride; j += 1024 * gridDim.x) {
-        uint32_t w[2][4];
+        uint32_t w0[4], w1[4];
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
             const uint2 v = j < I.npad ? *(const uint2 *)(g + 2 * (j + t)) : make_uint2(0u, 0u);
-            w[0][t] = v.x;
-            w[1][t] = v.y;
+            w0[t] = v.x >> (k0 >> 1);
+            w1[t] = v.y >> (k0 >> 1);
         }
-        for (int k = 0; k < M; ++k) {
-            const int h = k >> 1;
-            uint32_t bits = 0u;
+        for (int k = k0; k < k1; k += 2) {   // (k0 is even)
+            uint32_t b0 = 0u, b1 = 0u;
 #pragma unroll
-            for (int t = 0; t < 4; ++t) bits |= (((k & 1 ? w[1][t] : w[0][t]) >> h) & 1u) << (8 * t);
-            store4(dst + (int64_t)k * stride + j, signed_bytes(bits, I.n - j), stride - j);
+            for (int t = 0; t < 4; ++t) {
+                b0 |= (w0[t] & 1u) << (8 * t);
+                b1 |= (w1[t] & 1u) << (8 * t);
+                w0[t] >>= 1;
+                w1[t] >>= 1;
+            }
+            int8_t *p = dst + (int64_t)k * stride + j;
+            store4(p, signed_bytes(b0, I.n - j), stride - j);
+            if (k + 1 < k1) store4(p + stride, signed_bytes(b1, I.n - j), stride - j);
         }
     }
 }
@@ -2992,8 +2999,14 @@ hipError_t launch_sqa_spins_out(const uint32_t *words, const InstDev *inst, int 
                                 int64_t rows, int stride, int8_t *out, hipStream_t s)
 {
     return over_rows(rows, [&](int64_t q, int n) {
-        hipLaunchKernelGGL(sqa_spins_out_kernel, dim3((stride + 1023) / 1024, n), dim3(256), 0, s, words, inst,
-                           R, M, row0 + q, stride, out + q * M * stride);
+        // a few hundred rows would leave the chip idle behind each thread's loop over the slices: then
+        // the slices are split, to about eight work-groups per CU (228 replicas of L = 7, M = 16, call
+        // and wait: 27.8 -> 14.0 us, most of it from words that the compiler had put into LDS to
+        // index them by the slice's parity)
+        const int x = (stride + 1023) / 1024, parts = std::max(1, std::min(M, 2048 / (x * n)));
+        const int per = 2 * ((M + 2 * parts - 1) / (2 * parts));
+        hipLaunchKernelGGL(sqa_spins_out_kernel, dim3(x, n, (M + per - 1) / per), dim3(256), 0, s, words, inst,
+                           R, M, per, row0 + q, stride, out + q * M * stride);
     });
 }
 
