@@ -325,8 +325,12 @@ struct sg_ctx {
     DevBuf<uint4> d_recb;      // APT: d_rec with byte offsets (empty when a lattice is too large)
     DevBuf<uint32_t> d_ctr;      // {sweeps/steps, icm calls, swap attempts, cycles, done}
     // APT sweeps, ICM calls and swap attempts of single calls that d_ctr does not count yet: they go
-    // to the kernels as arguments, so that such a call needs no launch to advance the counters
+    // to the kernels as arguments, so that such a call needs no launch to advance the counters.
+    // A caller's graph of such calls is replayed with the arguments it was recorded with: from the
+    // first recorded call on (ctr_fixed) ctr_add keeps its values for good and every call's steps
+    // are counted on the device, in the graph as outside.
     uint32_t ctr_add[3] = {0, 0, 0};
+    bool ctr_fixed = false;
     Timer timer;
     // events around every main kernel launch (DT-SQA kernel, APT cycle graph)
     std::vector<std::pair<hipEvent_t, hipEvent_t>> kev;
@@ -368,6 +372,7 @@ struct sg_ctx {
     // graph cache for APT cycles
     hipGraphExec_t gexec = nullptr;
     int g_sweeps = -1, g_icm = -1, g_record = -1, g_cycles = 0, g_pairs = -1;
+    uint32_t g_ctr_add[3] = {0, 0, 0};
     int64_t *g_trace = nullptr;
     int g_trace_cap = 0;
 
@@ -780,6 +785,21 @@ void plan_words(sg_ctx *c)
     c->word_lds = lds;
 }
 
+// The task list of the words: the largest instances first, an instance's words on one XCD
+// (work-groups go to the eight XCDs in turn).
+std::vector<QuadDesc> word_tasks(const sg_ctx *c)
+{
+    std::vector<int> idx((size_t)c->n_inst);
+    for (int i = 0; i < c->n_inst; ++i) idx[(size_t)i] = i;
+    std::stable_sort(idx.begin(), idx.end(),
+                     [&](int a, int b) { return c->lat[(size_t)a].n > c->lat[(size_t)b].n; });
+    std::vector<QuadDesc> d;
+    for (int i = 0; i < c->n_inst; i += 8)
+        for (int w = 0; w < c->word_nw; ++w)
+            for (int k = i; k < std::min(i + 8, c->n_inst); ++k) d.push_back({idx[(size_t)k], w});
+    return d;
+}
+
 // --------------------------------------------------------------------- APT
 void create_apt(sg_ctx *c, const sg_config *cfg, const int8_t *const *colour = nullptr)
 {
@@ -929,6 +949,8 @@ void create_apt(sg_ctx *c, const sg_config *cfg, const int8_t *const *colour = n
     c->d_desc.upload(desc, s, "tasks");
     c->quad_threads = quad_threads(c);
     plan_words(c);
+    const std::vector<QuadDesc> word_desc = word_tasks(c);
+    if (!word_desc.empty()) c->d_word_desc.upload(word_desc, s, "tasks");
     c->quad_lds = 0;
     for (auto &I : c->idev) {
         const size_t need = apt_lds_bytes(I, c->ni);
@@ -1033,23 +1055,6 @@ AptArgs word_args(sg_ctx *c, AptArgs a)
     return a;
 }
 
-// The task list of the words, made on their first use: the largest instances first, an instance's
-// words on one XCD (work-groups go to the eight XCDs in turn).
-void make_word_tasks(sg_ctx *c)
-{
-    if (c->d_word_desc.p) return;
-    std::vector<int> idx((size_t)c->n_inst);
-    for (int i = 0; i < c->n_inst; ++i) idx[(size_t)i] = i;
-    std::stable_sort(idx.begin(), idx.end(),
-                     [&](int a, int b) { return c->lat[(size_t)a].n > c->lat[(size_t)b].n; });
-    std::vector<QuadDesc> d;
-    for (int i = 0; i < c->n_inst; i += 8)
-        for (int w = 0; w < c->word_nw; ++w)
-            for (int k = i; k < std::min(i + 8, c->n_inst); ++k) d.push_back({idx[(size_t)k], w});
-    c->d_word_desc.upload(d, c->stream, "tasks");
-    hip_check(hipStreamSynchronize(c->stream), "tasks");   // the list ends here
-}
-
 // Whether a cycle of n_sweeps sweeps runs them in words.  A launch in words costs about 13 us
 // beside its sweeps against 3 us in tiles, a sweep 6.8 against 13.1 us (128 L = 12 instances): 1.11,
 // 1.27 and 1.33 times faster at 2, 3 and 10 sweeps.  Cluster moves then take a launch of their own:
@@ -1087,11 +1092,32 @@ SwapArgs swap_args(sg_ctx *c, int32_t *acc_out, int64_t *trace, int trace_cap, i
     return a;
 }
 
-// Brings d_ctr up to date (before launches that are captured or advance it themselves).
+// At the start of a call that counts steps: ctr_add stays as it is once the caller records.
+void counters_for_call(sg_ctx *c)
+{
+    if (c->ctr_fixed) return;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    hip_check(hipStreamIsCapturing(c->stream, &st), "stream");
+    c->ctr_fixed = st != hipStreamCaptureStatusNone;
+}
+
+// Counts the steps of a single call whose kernels have been launched.
+void count_steps(sg_ctx *c, uint32_t sweeps, uint32_t icms, uint32_t swaps)
+{
+    if (c->ctr_fixed) {
+        hip_check(launch_advance(c->d_ctr.p, sweeps, icms, swaps, 0u, c->stream), "counters");
+        return;
+    }
+    c->ctr_add[0] += sweeps;
+    c->ctr_add[1] += icms;
+    c->ctr_add[2] += swaps;
+}
+
+// Brings d_ctr up to date where it may be (before launches that advance it themselves).
 void flush_counters(sg_ctx *c)
 {
     uint32_t *p = c->ctr_add;
-    if (!(p[0] | p[1] | p[2])) return;
+    if (c->ctr_fixed || !(p[0] | p[1] | p[2])) return;
     hip_check(launch_advance(c->d_ctr.p, p[0], p[1], p[2], 0u, c->stream), "counters");
     p[0] = p[1] = p[2] = 0;
 }
@@ -1764,13 +1790,13 @@ sg_status sg_sweep(sg_ctx *c, int32_t n_sweeps)
         require(c, SG_APT);
         if (n_sweeps < 0) fail(SG_EINVAL, "n_sweeps must be >= 0");
         if (n_sweeps == 0) return;
+        counters_for_call(c);
         const AptArgs a = apt_args(c, n_sweeps, 0);
-        if (sweep_in_words(c, n_sweeps, false)) make_word_tasks(c);
         hip_check(sweep_in_words(c, n_sweeps, false)
                       ? launch_apt_words(word_args(c, a), c->word_lds, c->stream)
                       : launch_apt_quad(a, c->quad_lds, c->stream),
                   "sweep");
-        c->ctr_add[0] += (uint32_t)n_sweeps;
+        count_steps(c, (uint32_t)n_sweeps, 0u, 0u);
     });
 }
 
@@ -1783,6 +1809,7 @@ void icm_call(sg_ctx *c, const std::vector<double> &cut, int icm_pairs, int32_t 
     if (icm_pairs != 1 && icm_pairs != 2) fail(SG_EINVAL, "icm_pairs must be 1 or 2");
     if (icm_applies(c, cut) && any_field(c))
         fail(SG_EUNSUPPORTED, "ICM with non-zero fields is not supported");
+    counters_for_call(c);
     upload_icm_flags(c, cut);
     if (info_host)
         hip_check(launch_fill_u32((uint32_t *)c->d_icm_info.p, 0xFFFFFFFFu, (int64_t)c->d_icm_info.n,
@@ -1791,7 +1818,7 @@ void icm_call(sg_ctx *c, const std::vector<double> &cut, int icm_pairs, int32_t 
     AptArgs a = apt_args(c, 0, 1);
     a.icm_pairs = icm_pairs;
     hip_check(launch_apt_quad(a, c->quad_lds, c->stream), "icm");
-    ++c->ctr_add[1];
+    count_steps(c, 0u, 1u, 0u);
     if (info_host) {
         c->d_icm_info.download(info_host, c->d_icm_info.n, c->stream, "icm info");
         hip_check(hipStreamSynchronize(c->stream), "icm");
@@ -1854,9 +1881,10 @@ sg_status sg_swap(sg_ctx *c, int32_t *accepted_host)
 {
     return guarded(c, [&] {
         require(c, SG_APT);
+        counters_for_call(c);
         SwapArgs a = swap_args(c, accepted_host ? c->d_acc_out.p : nullptr, nullptr, 0, 0);
         hip_check(launch_apt_swap(a, c->stream), "swap");
-        ++c->ctr_add[2];
+        count_steps(c, 0u, 0u, 1u);
         if (accepted_host) {
             c->d_acc_out.download(accepted_host, (size_t)c->n_inst * (c->n_beta - 1) * c->reps,
                                   c->stream, "swap");
@@ -1893,13 +1921,13 @@ void run_apt(sg_ctx *c, int64_t n_cycles, int32_t sweeps_per_swap, const std::ve
         const bool icm = icm_applies(c, cut);
         if (icm && any_field(c)) fail(SG_EUNSUPPORTED, "ICM with non-zero fields is not supported");
         if (n_cycles == 0) return;
+        counters_for_call(c);
         flush_counters(c);
         upload_icm_flags(c, icm ? cut : std::vector<double>((size_t)c->n_inst,
                                                               std::numeric_limits<double>::infinity()));
         // Sweeps in words leave the configurations their cluster moves alone (nothing to choose
         // without any).
         const bool words = sweep_in_words(c, sweeps_per_swap, icm);
-        if (words) make_word_tasks(c);
         if (c->apt_config == 0 && words && !icm) c->apt_config = 1;
         if (c->apt_config == 0) apt_autotune(c, words ? 0 : sweeps_per_swap, icm, icm_pairs);
         else apply_apt_config(c, c->apt_config);
@@ -1941,7 +1969,8 @@ void run_apt(sg_ctx *c, int64_t n_cycles, int32_t sweeps_per_swap, const std::ve
             return e;
         };
         if (n_cycles >= K && (!c->gexec || c->g_sweeps != sweeps_per_swap || c->g_icm != (int)icm || c->g_record != rec ||
-            c->g_trace != trace || c->g_trace_cap != cap || c->g_pairs != icm_pairs)) {
+            c->g_trace != trace || c->g_trace_cap != cap || c->g_pairs != icm_pairs ||
+            !std::equal(c->ctr_add, c->ctr_add + 3, c->g_ctr_add))) {
             if (c->gexec) (void)hipGraphExecDestroy(c->gexec);
             c->gexec = nullptr;
             hipGraph_t g = nullptr;
@@ -1959,6 +1988,7 @@ void run_apt(sg_ctx *c, int64_t n_cycles, int32_t sweeps_per_swap, const std::ve
             c->g_trace = trace;
             c->g_trace_cap = cap;
             c->g_pairs = icm_pairs;
+            std::copy(c->ctr_add, c->ctr_add + 3, c->g_ctr_add);
         }
         int64_t done = 0;
         for (; done + K <= n_cycles; done += K) {
@@ -2489,9 +2519,10 @@ sg_status sg_set_state(sg_ctx *c, const void *blob, size_t len)
             c->d_best.upload((const int64_t *)best, (size_t)c->n_inst, c->stream, "state");
             c->d_acc_count.upload((const int64_t *)acc, na, c->stream, "state");
         }
-        uint32_t v[8] = {ctr[0], ctr[1], ctr[2], 0u, 0u, 0u, 0u, 0u};
+        if (!c->ctr_fixed) c->ctr_add[0] = c->ctr_add[1] = c->ctr_add[2] = 0;
+        uint32_t v[8] = {};
+        for (int k = 0; k < 3; ++k) v[k] = ctr[k] - c->ctr_add[k];
         c->d_ctr.upload(v, 8, c->stream, "state");
-        c->ctr_add[0] = c->ctr_add[1] = c->ctr_add[2] = 0;
         if (c->mode == SG_SQA) c->sqa_steps = ctr[0];
         hip_check(hipStreamSynchronize(c->stream), "state");
     });

@@ -245,3 +245,95 @@ def test_calls_and_short_runs_interleaved(code):
                 oracle.apt_sweep(lat, i, np.repeat(beta, reps), SEED, int(ctr[i, 0]), sps[i])
                 ctr[i, 0] += 1
             check("after the checkpoint")
+
+
+def _hip():
+    """The HIP runtime that libsg itself uses."""
+    import ctypes
+    sg.load()
+    return ctypes.CDLL(next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line))
+
+
+@pytest.mark.parametrize("shapes,n_beta,reps,sweeps", [([(5, 4, 3), (4, 4, 4)], 6, 2, 1),
+                                                       ([(12, 12, 12)] * 12, 25, 4, 12)])
+def test_captured_calls_replay_with_new_random_numbers(monkeypatch, shapes, n_beta, reps, sweeps):
+    """Sweeps, cluster moves and an exchange, recorded by the caller into a graph on the stream it
+    gave the context (the sweeps in tiles and in words), then replayed between calls of its own:
+    every replay takes the next step numbers."""
+    import ctypes as C
+    hip = _hip()
+    stream = C.c_void_p()
+    assert hip.hipStreamCreateWithFlags(C.byref(stream), 1) == 0
+    config = sg._Config
+    monkeypatch.setattr(sg, "_Config", lambda *a: config(*a[:-1], stream))
+    insts = [(ej_couplings(s, 7, 950 + i)[0], 7, None) for i, s in enumerate(shapes)]
+    beta = geometric_ladder(n_beta, 0.3, 2.5)
+    cut = float(beta[-2])
+
+    def steps(c):
+        c.sweep(sweeps)
+        c.icm(cut)
+        c.swap(want_flags=False)
+
+    twin = sg.apt(insts, beta, SEED + 1, reps_per_beta=reps)
+    steps(twin)   # the kernels are loaded
+    twin.close()
+    ctx = sg.apt(insts, beta, SEED, reps_per_beta=reps)
+    ctx.set_launch_config(1)
+    ctx.icm(cut)  # the flags of this cutoff are on the device
+    ctx.swap()
+    graph, replay = C.c_void_p(), C.c_void_p()
+    assert hip.hipStreamBeginCapture(stream, 1) == 0
+    steps(ctx)
+    assert hip.hipStreamEndCapture(stream, C.byref(graph)) == 0
+    assert hip.hipGraphInstantiate(C.byref(replay), graph, None, None, C.c_size_t(0)) == 0
+
+    pick = sorted({0, len(insts) - 1})
+    lats = {i: oracle.Lattice(*insts[i]) for i in pick}
+    sps = {i: oracle.apt_init(lats[i], i, n_beta * reps, SEED) for i in pick}
+    ctr = [0, 0, 0]
+
+    def oracle_icm():
+        for i in pick:
+            oracle.apt_icm(lats[i], i, beta, reps, cut, SEED, ctr[1] + 1, sps[i])
+        ctr[1] += 1
+
+    def oracle_swap():
+        for i in pick:
+            E = np.array([oracle.energy(lats[i], v) for v in sps[i]], np.int64)
+            oracle.apt_swap(i, beta, reps, SEED, ctr[2] + 1, sps[i], E)
+        ctr[2] += 1
+
+    def oracle_sweeps(n):
+        for i in pick:
+            for k in range(n):
+                oracle.apt_sweep(lats[i], i, np.repeat(beta, reps), SEED, ctr[0] + k, sps[i])
+        ctr[0] += n
+
+    oracle_icm()
+    oracle_swap()
+    for k in range(3):
+        assert hip.hipGraphLaunch(replay, stream) == 0
+        oracle_sweeps(sweeps)
+        oracle_icm()
+        oracle_swap()
+        assert ctx.counters().tolist() == ctr, f"replay {k}"
+        spins, E = ctx.spins(), ctx.energy()
+        for i in pick:
+            assert np.array_equal(spins[i, :, :lats[i].n], sps[i]), f"replay {k}, spins {i}"
+            assert E[i].tolist() == [oracle.energy(lats[i], v) for v in sps[i]], f"replay {k}, energies {i}"
+        # calls, a run (graph and single cycles) and a checkpoint of the caller's own between the replays
+        ctx.sweep(1)
+        oracle_sweeps(1)
+        ctx.run_apt(33, 1, cut)
+        for _ in range(33):
+            oracle_sweeps(1)
+            oracle_icm()
+            oracle_swap()
+        blob = ctx.get_state()
+        ctx.sweep(3)
+        ctx.swap()
+        ctx.set_state(blob)
+    assert hip.hipGraphExecDestroy(replay) == 0 and hip.hipGraphDestroy(graph) == 0
+    ctx.close()
+    assert hip.hipStreamDestroy(stream) == 0
