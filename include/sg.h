@@ -229,10 +229,12 @@ sg_status sg_sqa_anneal_dev(sg_ctx *ctx, const double *gamma, int32_t n_steps, i
  * stream the library creates (joined back before the call's later work): the largest
  * instances up to 65, 75 or 85 % of all sites, and the rest (one group if that leaves the
  * second empty).  The first sg_run_apt / sg_run_apt_ex of a context whose code is unset (0)
- * times all fifteen on its own shape (sweeps per swap, cluster moves) and keeps the fastest,
- * leaving the context's state as it was; other calls use code 1 until then.  Launches of several
- * sweeps may run in a kernel of their own, to which no code applies: a first run whose cycles are
- * such launches alone (no cluster moves) sets code 1.
+ * times them on its own shape (sweeps per swap, cluster moves) and keeps the fastest: codes 1..12
+ * as 32 plain launches, then the best of them and the three splits as graphs of 32 cycles.  The
+ * context's state is left as it was; other calls use code 1 until then.  Launches of several
+ * sweeps may run in a kernel of their own, to which no code applies.  Runs of such launches leave
+ * the code unset; their cluster moves, if any, take the fastest of codes 1..12 for a launch without
+ * sweeps, or the code that is set.
  * Both tuners cache their pick per workload shape for the process and in the file named by
  * the environment variable SG_TUNE_CACHE (default ~/.cache/libsg_tune.txt; best effort).
  * get: 0 while unset.  set: 0 re-enables the autotuner; any other value outside the allowed

@@ -366,6 +366,7 @@ struct sg_ctx {
     hipStream_t stream2 = nullptr;
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
     int apt_config = 0;        // launch configuration asked for: 0 = the autotuner's on the next run
+    int apt_config_moves = 0;  // the autotuner's pick for launches of cluster moves alone (0: none yet)
     int apt_config_used = 1;   // configuration of d_desc / apt_waves (1: order 0, 7 waves)
     int apt_waves = 7;
     std::vector<double> icm_cutoff_loaded;   // per instance, as last uploaded into d_icm_on
@@ -1526,7 +1527,7 @@ std::map<std::string, int> g_apt_tune_cache;   // guarded by g_tune_mu
 // machines a split that runs 256 mixed instances in 4.4 ms lost to an order that takes 4.9).  The
 // state is saved before and restored after, so the context is unchanged.  The pick is cached per
 // workload shape for the process and on disk.
-void apt_autotune(sg_ctx *c, int S, bool icm, int pairs)
+int apt_autotune(sg_ctx *c, int S, bool icm, int pairs)
 {
     const std::string key = apt_tune_key(c, S, icm, pairs);
     int pick = 0;
@@ -1635,8 +1636,8 @@ void apt_autotune(sg_ctx *c, int S, bool icm, int pairs)
         std::lock_guard<std::mutex> lk(g_tune_mu);
         g_apt_tune_cache[key] = pick;
     }
-    c->apt_config = pick;
     apply_apt_config(c, pick);
+    return pick;
 }
 
 // Event pair bracketing one main-kernel launch when kernel timing is on.
@@ -1925,12 +1926,14 @@ void run_apt(sg_ctx *c, int64_t n_cycles, int32_t sweeps_per_swap, const std::ve
         flush_counters(c);
         upload_icm_flags(c, icm ? cut : std::vector<double>((size_t)c->n_inst,
                                                               std::numeric_limits<double>::infinity()));
-        // Sweeps in words leave the configurations their cluster moves alone (nothing to choose
-        // without any).
+        // Sweeps in words leave the configurations their cluster moves alone, which keep a pick of
+        // their own: the context's is for runs whose sweeps are in tiles.
         const bool words = sweep_in_words(c, sweeps_per_swap, icm);
-        if (c->apt_config == 0 && words && !icm) c->apt_config = 1;
-        if (c->apt_config == 0) apt_autotune(c, words ? 0 : sweeps_per_swap, icm, icm_pairs);
-        else apply_apt_config(c, c->apt_config);
+        if (!words || icm) {
+            int &code = words && c->apt_config == 0 ? c->apt_config_moves : c->apt_config;
+            if (code == 0) code = apt_autotune(c, words ? 0 : sweeps_per_swap, icm, icm_pairs);
+            else apply_apt_config(c, code);
+        }
         const int cap = best_trace ? (int)(n_cycles / record_every) : 0;
         if (best_trace) {
             if ((size_t)c->n_inst * cap > c->d_trace.n) c->d_trace.alloc((size_t)c->n_inst * cap, "trace");
@@ -2104,6 +2107,7 @@ sg_status sg_set_launch_config(sg_ctx *c, int32_t config)
             if (config < 0 || config > kAptConfigs)
                 fail(SG_EINVAL, "APT launch configuration must be 0..%d", kAptConfigs);
             c->apt_config = config;
+            c->apt_config_moves = 0;
             if (config) apply_apt_config(c, config);
         }
     });

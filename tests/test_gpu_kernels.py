@@ -337,3 +337,26 @@ def test_captured_calls_replay_with_new_random_numbers(monkeypatch, shapes, n_be
     assert hip.hipGraphExecDestroy(replay) == 0 and hip.hipGraphDestroy(graph) == 0
     ctx.close()
     assert hip.hipStreamDestroy(stream) == 0
+
+
+def test_runs_in_words_leave_the_launch_configuration_unset():
+    """A first run whose sweeps are in words, without and with cluster moves, leaves the choice to the
+    first run in tiles, which tunes its own shape; a code that is set stays."""
+    insts = [(ej_couplings((8, 8, 8), 7, 970 + i)[0], 7, None) for i in range(64)]
+    beta = geometric_ladder(64, 0.2, 3.0)
+    ctx = sg.apt(insts, beta, SEED, reps_per_beta=4)
+    for cutoff in (float("inf"), 1.0):
+        ctx.run_apt(34, 12, cutoff)
+        assert ctx.launch_config() == 0
+    ctx.run_apt(2, 1, 1.0)
+    assert 1 <= ctx.launch_config() <= 15
+    ctx.set_launch_config(13)
+    ctx.run_apt(2, 12, 1.0)
+    assert ctx.launch_config() == 13
+    lat, sp = oracle.Lattice(*insts[63]), oracle.apt_init(oracle.Lattice(*insts[63]), 63, 256, SEED)
+    ctr, E = np.zeros(3, np.uint32), np.zeros(256, np.int64)
+    best = np.array([np.iinfo(np.int64).max], np.int64)
+    for cycles, sweeps, cutoff in ((34, 12, float("inf")), (34, 12, 1.0), (2, 1, 1.0), (2, 12, 1.0)):
+        rc, _, _ = oracle.apt_run(lat, 63, beta, 4, SEED, cycles, sweeps, cutoff, 1, ctr, sp, E, best)
+        assert rc == 0
+    assert np.array_equal(ctx.spins()[63], sp) and ctx.energy()[63].tolist() == E.tolist()
