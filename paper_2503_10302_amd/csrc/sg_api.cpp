@@ -353,6 +353,7 @@ struct sg_ctx {
     int quad_threads = kQuadThreads;   // work-group size of the replica kernel
     // sweeps in words of up to 32 slots (apt_word_kernel): words per instance, 0: never
     int word_nw = 0, word_threads = 0, word_planes = 0;
+    int word_from[2] = {0, 0};   // fewest sweeps that pay for it, without and with cluster moves
     size_t word_lds = 0;
     DevBuf<QuadDesc> d_word_desc;
     int n_blocks = 0;
@@ -756,9 +757,44 @@ int adaptive_words(int n_inst, int groups, int phase, int cus, int slot_threads)
     return best;
 }
 
+// Predicted time in microseconds of one sweep with per_inst work-groups of `threads` per instance.
+// Two things bound it: the vector instructions that the fullest CU issues (`site` per site of a
+// wave, on average over the words, and 27 per four waves and phase), and the largest instance's chain
+// of dependent phases (`longest` instructions per pass of a thread and 55 around the passes, each
+// `stall` times as long as its issue), once per round of work-groups that fit a CU together.
+double sweep_us(const sg_ctx *c, int per_inst, double site, double longest, double stall, int threads, int cus)
+{
+    double issue = 0.0, most = 0.0, chain = 0.0;
+    for (const InstDev &I : c->idev) {
+        double one = 0.0, dep = 0.0;
+        for (int k = 0; k < I.n_colours; ++k) {
+            one += (I.col_cnt[k] + 63) / 64 * 0.25 * site + 27.0 * threads / 256;
+            dep += (I.col_cnt[k] + threads - 1) / threads * longest + 55.0;
+        }
+        issue += per_inst * one;
+        most = std::max(most, one);
+        chain = std::max(chain, dep);
+    }
+    const int64_t wgs = (int64_t)c->n_inst * per_inst, on_cu = (wgs + cus - 1) / cus;
+    issue = std::max(issue * (double)on_cu / (double)wgs, most);
+    chain *= stall * (double)std::max<int64_t>(1, (on_cu * (threads / 64) + 31) / 32);
+    const double i2 = issue * issue, c2 = chain * chain;
+    return std::sqrt(std::sqrt(i2 * i2 + c2 * c2)) * 4.0 / 2400.0;   // 4 cycles each at 2.4 GHz
+}
+
 // The sweeps of apt_word_kernel for this context: words per instance by the rule of the adaptive
-// stage (which few work-groups or phases of few sites turn down: a four-slot tile then has more
-// parallel work) and the kernel's LDS.
+// stage, the kernel's LDS, and the fewest sweeps of a launch that pay for it.  Beside its sweeps a
+// launch in words takes some 1 to 20 us more than one in tiles (tables, rows of 32 slots, energies
+// counted afresh; more for larger lattices), and cluster moves then need a launch of their own.  The
+// constants, here and in sweep_us (tiles: 103 instructions a site; words: 50 and 62 per group of
+// four slots), are fitted to both kernels' times on 49 batches of 8 to 400 instances of L = 4..31,
+// mixed sizes among them, with 8 to 40 temperatures of 1 to 4 labels: of their 250 launches of 2 to
+// 12 sweeps none is more than 4 % slower in words than in tiles, and two that words would run
+// more than 3 % faster stay in tiles.  us per cycle, words against tiles: 128 L = 12 instances of 32 x 2
+// slots, words from 2 sweeps on, 26 against 31 at 2, 79 against 112 at 10 (with moves from 5 on, 57
+// against 62); 32 of L = 15, from 4, 20.3 against 19.1 at 2, 57 against 65 at 10; 64 of L = 8,
+// from 14, 12.2 against 10.3 at 2; 100 of L = 5, never, 33.7 against 27.7 at 10; 256 of L = 6..15
+// with moves, from 6, 101 against 95 at 5, 168 against 170 at 10.
 void plan_words(sg_ctx *c)
 {
     c->word_nw = 0;
@@ -780,6 +816,14 @@ void plan_words(sg_ctx *c)
     const size_t lds = sizeof(uint32_t) * (size_t)(npad + 4);
     const size_t lds_static = sizeof(uint32_t) * (272 + 512 + nt / 2 + 64 + 64);
     if (planes > kAdaptPlanes || lds + lds_static > kMaxLds) return;
+    const int top = (c->n_quads + nw - 1) / nw;   // groups of the fullest word
+    const double gain =
+        sweep_us(c, c->n_quads, 103.0, 103.0, 2.5, c->quad_threads, cus) -
+        sweep_us(c, nw, 50.0 + 62.0 * c->n_quads / nw, 50.0 + 62.0 * top, 1.85, nt, cus);
+    const double extra[2] = {1.2 + 0.0007 * c->n_max, 5.0 + std::min(8.0, 0.003 * c->n_max)};
+    if (gain * 1e6 < extra[1]) return;
+    c->word_from[0] = std::max(2, (int)(extra[0] / gain) + 1);
+    c->word_from[1] = std::max(5, (int)(extra[1] / gain) + 1);
     c->word_nw = nw;
     c->word_threads = nt;
     c->word_planes = planes;
@@ -1056,13 +1100,10 @@ AptArgs word_args(sg_ctx *c, AptArgs a)
     return a;
 }
 
-// Whether a cycle of n_sweeps sweeps runs them in words.  A launch in words costs about 13 us
-// beside its sweeps against 3 us in tiles, a sweep 6.8 against 13.1 us (128 L = 12 instances): 1.11,
-// 1.27 and 1.33 times faster at 2, 3 and 10 sweeps.  Cluster moves then take a launch of their own:
-// at 4 sweeps 1.18 times faster on that batch, 0.99 on 256 instances of L = 6..15.
+// Whether a cycle of n_sweeps sweeps runs them in words (plan_words).
 bool sweep_in_words(const sg_ctx *c, int n_sweeps, bool icm)
 {
-    return c->word_nw > 0 && n_sweeps >= (icm ? 5 : 2);
+    return c->word_nw > 0 && n_sweeps >= c->word_from[icm ? 1 : 0];
 }
 
 SwapArgs swap_args(sg_ctx *c, int32_t *acc_out, int64_t *trace, int trace_cap, int record_every)

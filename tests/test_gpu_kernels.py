@@ -360,3 +360,77 @@ def test_runs_in_words_leave_the_launch_configuration_unset():
         rc, _, _ = oracle.apt_run(lat, 63, beta, 4, SEED, cycles, sweeps, cutoff, 1, ctr, sp, E, best)
         assert rc == 0
     assert np.array_equal(ctx.spins()[63], sp) and ctx.energy()[63].tolist() == E.tolist()
+
+
+@pytest.mark.parametrize("shapes,n_inst,n_beta,reps,sweeps,cutoff,words", [
+    ([(8, 8, 8)], 64, 32, 2, 2, float("inf"), False), ([(5, 5, 5)], 100, 32, 2, 10, float("inf"), False),
+    ([(15, 15, 15)], 32, 32, 2, 2, float("inf"), False), ([(15, 15, 15), (6, 6, 6)], 40, 20, 2, 10, float("inf"), False),
+    ([(12, 12, 12)], 64, 32, 2, 5, 1.0, False), ([(5, 5, 5)], 100, 32, 2, 10, 1.0, False),
+    ([(12, 12, 12)], 128, 32, 2, 2, float("inf"), True), ([(15, 15, 15)], 32, 32, 2, 10, float("inf"), True),
+    ([(12, 12, 12)], 128, 32, 2, 10, 1.0, True), ([(20, 20, 20)], 8, 32, 2, 2, float("inf"), True)])
+def test_sweeps_run_in_words_where_they_pay(shapes, n_inst, n_beta, reps, sweeps, cutoff, words):
+    """The choice between words and tiles on batches on both sides of the line, each with its measured
+    winner.  (Only a run in tiles settles the launch configuration.)"""
+    insts = [(ej_couplings(shapes[i % len(shapes)], 7, 1000 + i)[0], 7, None) for i in range(n_inst)]
+    ctx = sg.apt(insts, geometric_ladder(n_beta, 0.2, 3.0), SEED, reps_per_beta=reps)
+    ctx.run_apt(2, sweeps, cutoff)
+    assert (ctx.launch_config() == 0) == words
+
+
+_MIXED_WORDS = [(5, 4, 3), (4, 4, 4), (3, 5, 2), (6, 3, 4), (1, 1, 3), (7, 6, 5), (2, 2, 2), (9, 4, 2)]
+_MIXED_AXES = [7, 7, 5, 7, 0, 3, 7, 6]   # periodic axes of each
+
+
+@pytest.mark.parametrize("shapes,n_inst,n_beta,reps,S,cutoff", [
+    ([(8, 8, 8)], 64, 32, 2, 20, float("inf")), ([(12, 12, 12)], 12, 25, 4, 6, float("inf")),
+    ([(3, 4, 2)], 1500, 11, 1, 3, float("inf")), ([(4, 3, 3)], 1500, 16, 1, 4, float("inf")),
+    ([(2, 3, 4)], 1500, 20, 1, 2, float("inf")), ([(3, 4, 2)], 1500, 12, 2, 5, 1.0),
+    ([(3, 3, 2)], 1500, 14, 2, 5, 0.5), ([(4, 2, 2)], 1500, 8, 4, 5, 1.0), ([(3, 4, 2)], 1500, 9, 4, 2, float("inf")),
+    ([(2, 2, 3)], 1500, 13, 4, 5, 1.0), (_MIXED_WORDS, 800, 15, 4, 5, 1.0), ([(18, 18, 18)], 130, 8, 4, 2, float("inf")),
+    ([(22, 21, 23)], 4, 8, 2, 2, float("inf"))])
+def test_words_of_every_size(shapes, n_inst, n_beta, reps, S, cutoff):
+    """Batches whose sweeps run in words: 2 to 8 groups of four slots in the fuller words, words with one
+    group less beside them, 512 and 1024 threads; mixed sizes with open axes and missing bonds; and the
+    wide bond counters of lattices with more than ten sites per thread."""
+    insts = []
+    for i in range(n_inst):
+        k = i % len(shapes)
+        per = _MIXED_AXES[k] if len(shapes) > 1 else 7
+        diluted = len(shapes) > 1 and (i // len(shapes)) % 2
+        J = diluted_couplings(shapes[k], per, 1100 + i, 0.25) if diluted else ej_couplings(shapes[k], per, 1100 + i)[0]
+        insts.append((J, per, None))
+    beta = geometric_ladder(n_beta, 0.2, 3.0)
+    n = max(int(np.prod(s)) for s in shapes)
+    cycles = 33 if n <= 512 else 2
+    ctx = sg.apt(insts, beta, SEED, reps_per_beta=reps)
+    trace = ctx.run_apt(cycles, S, cutoff, record_every=1)
+    assert ctx.launch_config() == 0   # no run in tiles
+    ctx.sweep(S)
+    spins, E, counts = ctx.spins(), ctx.energy(), ctx.swap_counts()
+    if len(shapes) > 1:
+        pick = list(range(16)) + [n_inst - 1]
+    else:
+        pick = range(0, n_inst, max(1, n_inst // (12 if n < 100 else 2)))
+    for i in pick:
+        lat = oracle.Lattice(*insts[i])
+        sp = oracle.apt_init(lat, i, n_beta * reps, SEED)
+        ctr, oE = np.zeros(3, np.uint32), np.zeros(n_beta * reps, np.int64)
+        best = np.array([np.iinfo(np.int64).max], np.int64)
+        rc, otr, oacc = oracle.apt_run(lat, i, beta, reps, SEED, cycles, S, cutoff, 1, ctr, sp, oE, best)
+        assert rc == 0 and np.array_equal(trace[i], otr) and np.array_equal(counts[i], oacc), f"instance {i}"
+        for k in range(S):
+            oracle.apt_sweep(lat, i, np.repeat(beta, reps), SEED, cycles * S + k, sp)
+        assert np.array_equal(spins[i, :, :lat.n], sp), f"spins, instance {i}"
+        assert E[i].tolist() == [oracle.energy(lat, v) for v in sp], f"energies, instance {i}"
+
+
+@pytest.mark.parametrize("shape,n_inst,n_chains", [((18, 18, 18), 270, 8), ((22, 22, 22), 3, 16)])
+def test_adaptive_words_of_large_lattices(shape, n_inst, n_chains):
+    """The adaptive kernel's wide bond counters (more than ten sites per thread), with 512 and 1024
+    threads."""
+    insts = [(ej_couplings(shape, 7, 1200 + i)[0], 7, None) for i in range(n_inst)]
+    kw = dict(beta0=0.4, alpha=1.25, tol=0.01, n_chains=n_chains, sweeps=4, tail=3, max_steps=2)
+    got = sg.adaptive_ladder(insts, 21, **kw)
+    for i in {0, n_inst - 1}:
+        beta, sigma = oracle.adaptive_ladder(oracle.Lattice(*insts[i]), i, 21, **kw)[:2]
+        assert np.array_equal(got[i][0], beta) and np.array_equal(got[i][1], sigma), f"instance {i}"
