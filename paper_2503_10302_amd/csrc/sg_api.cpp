@@ -1607,8 +1607,10 @@ int apt_autotune(sg_ctx *c, int S, bool icm, int pairs)
         std::vector<float> best_ms(kAptConfigs + 1, std::numeric_limits<float>::infinity());
         hipError_t err = hipSuccess;
         try {
+            // (larger work-groups have one register budget: codes 7..12 are codes 1..6 there)
+            const int plain = c->quad_threads == kQuadThreads ? 2 * kAptOrders : kAptOrders;
             for (int rep = 0; rep < 5 && err == hipSuccess; ++rep)
-                for (int code = 1; code <= 2 * kAptOrders && err == hipSuccess; ++code) {
+                for (int code = 1; code <= plain && err == hipSuccess; ++code) {
                     apply_apt_config(c, code);
                     AptArgs a = apt_args(c, S, icm ? 1 : 0);
                     a.icm_pairs = pairs;
@@ -1621,7 +1623,7 @@ int apt_autotune(sg_ctx *c, int S, bool icm, int pairs)
                     if (err == hipSuccess) best_ms[code] = std::min(best_ms[code], ms);
                 }
             pick = 1;
-            for (int code = 2; code <= 2 * kAptOrders; ++code)
+            for (int code = 2; code <= plain; ++code)
                 if (best_ms[code] < best_ms[pick]) pick = code;
             // (launches without sweeps are made in one group)
             if (c->n_inst > 1 && S > 0 && err == hipSuccess) {

@@ -434,3 +434,13 @@ def test_adaptive_words_of_large_lattices(shape, n_inst, n_chains):
     for i in {0, n_inst - 1}:
         beta, sigma = oracle.adaptive_ladder(oracle.Lattice(*insts[i]), i, 21, **kw)[:2]
         assert np.array_equal(got[i][0], beta) and np.array_equal(got[i][1], sigma), f"instance {i}"
+
+
+def test_tuner_leaves_out_codes_that_are_the_same_kernel(tmp_path, monkeypatch):
+    """Contexts whose work-groups have 512 or 1024 threads: codes 7..12 are codes 1..6."""
+    monkeypatch.setenv("SG_TUNE_CACHE", str(tmp_path / "tune.txt"))
+    for n_inst in range(1, 9):
+        insts = [(ej_couplings((12, 12, 12), 7, 1300 + i)[0], 7, None) for i in range(n_inst)]
+        ctx = sg.apt(insts, geometric_ladder(16, 0.2, 3.0), SEED, reps_per_beta=2)
+        ctx.run_apt(2, 1, 1.0)
+        assert ctx.launch_config() not in range(7, 13)
