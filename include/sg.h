@@ -206,8 +206,9 @@ sg_status sg_threshold_swap(double beta_lo, double beta_hi, int64_t d, uint32_t 
  * [n_inst]; best_E_dev int64 [n_inst], best_state_dev int8 [n_inst][n_max]).  The work is
  * queued on the context's stream and nothing is copied to the host: the results are there once
  * that stream reaches them (create the context on the consumer's stream, or call
- * sg_synchronize).  sg_sqa_anneal_dev still waits for the stream between 256-step chunks of a
- * longer schedule, whose threshold tables it rebuilds on the host.  The caller provides buffers
+ * sg_synchronize).  sg_sqa_anneal_dev still waits for the stream between the launches of a
+ * schedule of more than 256 steps, whose threshold tables it rebuilds on the host (at most 256
+ * steps a launch; the first of a state of at most 64 MB takes 32).  The caller provides buffers
  * of the sizes above; a pointer that is not device memory of the context's device gives
  * SG_EINVAL before any work is queued. */
 sg_status sg_energy_dev(sg_ctx *ctx, int64_t *E_dev);

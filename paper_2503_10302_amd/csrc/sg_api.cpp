@@ -2170,16 +2170,18 @@ void run_sqa_anneal(sg_ctx *c, const double *gamma, int32_t n_steps)
         if (!(gamma[t] > 0.0) || !std::isfinite(gamma[t])) fail(SG_EINVAL, "gamma must be > 0");
     // thresholds for every step, FP64 -> uint32 (Supplementary Eq. S.3)
     // The host fills a launch's table while the launch before it runs; nothing runs beside the
-    // first, so a long anneal starts with a short one (about 0.5 us of host time a step against
-    // some 20 us for one more launch and copy;
-    // 600 steps of 64 L = 10 replicas, M = 32: 3.47 -> 3.41 ms, 160 steps of 2 x 32: 1.06 -> 1.02).
+    // first, so an anneal of several launches starts with a short one: about 0.5 us of host time for
+    // each of some 200 steps against 20 us for one more launch and copy and the state's way through
+    // memory once more.  600 steps of 64 L = 10 replicas, M = 32: 3.47 -> 3.41 ms; states of more than
+    // 64 MB (some 30 us) start with a whole launch, and 256 steps or fewer are one, without a wait.
     const int chunk = 256, short_chunk = 32;
+    const bool start_short = n_steps > chunk && c->d_sqa.n * sizeof(uint32_t) <= (size_t)64 << 20;
     int done = 0;
     std::vector<uint32_t> lut;
     if (c->d_sqa_lut.n < (size_t)std::min(chunk, n_steps) * c->nl)
         c->d_sqa_lut.alloc((size_t)std::min(chunk, n_steps) * c->nl, "sqa thresholds");
     while (done < n_steps) {
-        const int ns = std::min(done == 0 && n_steps > 4 * short_chunk ? short_chunk : chunk, n_steps - done);
+        const int ns = std::min(done == 0 && start_short ? short_chunk : chunk, n_steps - done);
         lut.assign((size_t)ns * c->nl, 0u);
         for (int t = 0; t < ns; ++t) {
             const double K = trotter_K(c->sqa_beta, c->M, gamma[done + t]);

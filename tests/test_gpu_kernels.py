@@ -444,3 +444,17 @@ def test_tuner_leaves_out_codes_that_are_the_same_kernel(tmp_path, monkeypatch):
         ctx = sg.apt(insts, geometric_ladder(16, 0.2, 3.0), SEED, reps_per_beta=2)
         ctx.run_apt(2, 1, 1.0)
         assert ctx.launch_config() not in range(7, 13)
+
+
+@pytest.mark.parametrize("shape,M,R,steps,launches", [((4, 3, 2), 6, 2, 129, 1), ((4, 3, 2), 6, 2, 256, 1),
+                                                      ((4, 3, 2), 6, 2, 257, 2), ((4, 3, 2), 6, 2, 289, 3),
+                                                      ((15, 15, 15), 4, 2500, 289, 2)])
+def test_sqa_launches_of_a_schedule(shape, M, R, steps, launches):
+    """A schedule of up to 256 steps is one launch (nothing to wait for); a longer one starts with a
+    short launch unless its state is large (here 2500 x 27 KB)."""
+    J, _ = ej_couplings(shape, 7, 521)
+    ctx = sg.sqa([(J, 7, None)], M, R, 3.0, SEED)
+    ctx.sqa_anneal(np.full(2, 1.0))   # the work-group size is settled
+    ctx.kernel_timing(True)
+    ctx.sqa_anneal(np.linspace(3.0, 0.1, steps))
+    assert ctx.kernel_time()[1] == launches
