@@ -2237,25 +2237,96 @@ void spins_out(sg_ctx *c, int64_t row0, int64_t rows, int stride, int8_t *out)
 // Rows of spins cross to the host through a staging buffer on the device, at most 32 MB at a
 // time (or one row; less where the device has no room for that), kept with the context.  The bytes are made and read by the GPU: four L = 15
 // instances with 64 replicas of 32 slices (28 MB of spins) leave in 1.7 ms; a loop over them on
-// the host took 36 ms.
+// the host took 36 ms.  0 when there is no room for a single row.
 int64_t stage_rows(sg_ctx *c, int64_t rows, int64_t row_bytes)
 {
     int64_t n = std::min(rows, std::max<int64_t>(1, (32 << 20) / row_bytes));
     while (c->d_stage.n < (size_t)(n * row_bytes)) {
         try {
             c->d_stage.alloc((size_t)(n * row_bytes), "spin staging");
-        } catch (const Failure &) {
-            if (n == 1) throw;
+        } catch (const Failure &e) {
+            if (e.code != SG_ENOMEM) throw;
+            if (n == 1) return 0;
             n = (n + 1) / 2;
         }
     }
     return n;
 }
 
+// A replica row in the device's form, on its way without a staging buffer (the device is full): a row
+// at a time is packed or unpacked here.
+struct RawRow {
+    const InstDev *I;
+    uint8_t *dev;
+    std::vector<uint8_t> buf;
+};
+
+// Row `row` of all (APT: perm[] names its buffer, logical slot s in buffer s when it is empty).
+void raw_row(sg_ctx *c, int64_t row, const std::vector<int32_t> &perm, RawRow &r)
+{
+    const int per = c->mode == SG_APT ? c->n_slots : c->R, nb4 = 4 * c->n_quads;
+    const int i = (int)(row / per), k = (int)(row - (int64_t)i * per);
+    r.I = &c->idev[(size_t)i];
+    if (c->mode == SG_APT) {
+        const int64_t b = perm.empty() ? k : perm[(size_t)i * nb4 + k];
+        r.dev = c->d_spins.p + r.I->spin_off + b * r.I->npad;
+        r.buf.assign((size_t)r.I->npad, 0);
+    } else {
+        r.dev = (uint8_t *)(c->d_sqa.p + r.I->spin_off + (int64_t)k * r.I->npad * 2);
+        r.buf.assign((size_t)r.I->npad * 8, 0);
+    }
+}
+
+void rows_to_host(sg_ctx *c, int64_t row0, int64_t rows, int stride, int8_t *out)
+{
+    const int slices = c->mode == SG_APT ? 1 : c->M;
+    std::vector<int32_t> perm;
+    if (c->mode == SG_APT) {
+        perm.resize(c->d_perm.n);
+        c->d_perm.download(perm.data(), perm.size(), c->stream, "spins");
+        hip_check(hipStreamSynchronize(c->stream), "spins");
+    }
+    RawRow r;
+    for (int64_t q = 0; q < rows; ++q) {
+        raw_row(c, row0 + q, perm, r);
+        hip_check(hipMemcpyAsync(r.buf.data(), r.dev, r.buf.size(), hipMemcpyDeviceToHost, c->stream), "spins");
+        hip_check(hipStreamSynchronize(c->stream), "spins");
+        const uint32_t *w = (const uint32_t *)r.buf.data();
+        for (int k = 0; k < slices; ++k) {
+            int8_t *dst = out + (q * slices + k) * stride;
+            std::memset(dst, 0, (size_t)stride);
+            for (int j = 0; j < r.I->n; ++j) {
+                const uint32_t up = c->mode == SG_APT ? r.buf[(size_t)j] : w[2 * j + (k & 1)] >> (k >> 1);
+                dst[j] = up & 1u ? 1 : -1;
+            }
+        }
+    }
+}
+
+void rows_from_host(sg_ctx *c, int64_t rows, const int8_t *in)
+{
+    const int slices = c->mode == SG_APT ? 1 : c->M;
+    RawRow r;
+    for (int64_t q = 0; q < rows; ++q) {
+        raw_row(c, q, {}, r);
+        uint32_t *w = (uint32_t *)r.buf.data();
+        for (int k = 0; k < slices; ++k) {
+            const int8_t *v = in + (q * slices + k) * c->n_max;
+            for (int j = 0; j < r.I->n; ++j) {
+                if (c->mode == SG_APT) r.buf[(size_t)j] = v[j] > 0 ? 1 : 0;
+                else w[2 * j + (k & 1)] |= (v[j] > 0 ? 1u : 0u) << (k >> 1);
+            }
+        }
+        hip_check(hipMemcpyAsync(r.dev, r.buf.data(), r.buf.size(), hipMemcpyHostToDevice, c->stream), "spins");
+        hip_check(hipStreamSynchronize(c->stream), "spins");
+    }
+}
+
 void spins_to_host(sg_ctx *c, int64_t row0, int64_t rows, int stride, int8_t *out)
 {
     const int64_t row_bytes = (int64_t)stride * (c->mode == SG_APT ? 1 : c->M);
     const int64_t n = stage_rows(c, rows, row_bytes);
+    if (n == 0) return rows_to_host(c, row0, rows, stride, out);
     for (int64_t q = 0; q < rows; q += n) {
         const int64_t m = std::min(n, rows - q);
         spins_out(c, row0 + q, m, stride, c->d_stage.p);
@@ -2270,7 +2341,7 @@ void put_spins(sg_ctx *c, const int8_t *in)
     // The new state is built beside the present one and checked on the way; it takes its place
     // only when every site's byte was +1 or -1.  A small state (up to 256 KB of spins: the
     // check takes less than the buffer and the trip of the flag), or one that finds no room on
-    // the device, is checked here first and goes in at once.
+    // the device, is checked here first and goes in at once (row by row without a staging buffer).
     const bool apt = c->mode == SG_APT;
     hipStream_t s = c->stream;
     const int64_t rows = (int64_t)c->n_inst * (apt ? c->n_slots : c->R);
@@ -2280,7 +2351,7 @@ void put_spins(sg_ctx *c, const int8_t *in)
     const size_t words = apt ? c->d_spins.n / 4 : c->d_sqa.n;   // (replica buffers of 16 k bytes)
     uint32_t *state = apt ? (uint32_t *)c->d_spins.p : c->d_sqa.p, *to = state;
     int32_t *bad = (int32_t *)(c->d_ctr.p + 7);   // (a spare counter)
-    if (rows * row_bytes > 1 << 18) {
+    if (n > 0 && rows * row_bytes > 1 << 18) {
         try {
             next.alloc(words, "spins");
             to = next.p;
@@ -2302,7 +2373,8 @@ void put_spins(sg_ctx *c, const int8_t *in)
     // every site of every row is written; an APT ladder that does not fill its last tile
     // leaves buffers that no slot names
     if (apt && c->n_slots != 4 * c->n_quads) hip_check(launch_fill_u32(to, 0u, (int64_t)words, s), "spins");
-    for (int64_t q = 0; q < rows; q += n) {
+    if (n == 0) rows_from_host(c, rows, in);
+    for (int64_t q = 0; n > 0 && q < rows; q += n) {
         const int64_t m = std::min(n, rows - q);
         c->d_stage.upload(in + q * row_bytes, (size_t)(m * row_bytes), s, "spins");
         hip_check(apt ? launch_apt_spins_in((uint8_t *)to, c->d_inst.p, c->n_slots, q, m, c->n_max,
@@ -2451,6 +2523,7 @@ sg_status sg_sqa_trotter_agreement(sg_ctx *c, int32_t *agree_host)
         // counts of whole replicas through the staging buffer
         const int64_t rows = (int64_t)c->n_inst * c->R;
         const int64_t n = stage_rows(c, rows, 4 * c->M);
+        if (n == 0) fail(SG_ENOMEM, "correlation: out of device memory");
         SqaArgs a = sqa_args(c);
         for (int64_t q = 0; q < rows; q += n) {
             const int64_t m = std::min(n, rows - q);
