@@ -109,15 +109,29 @@ void features_of(const sg_lattice &L, double *f)
 
 namespace {
 
+// Device memory for `want` units of `floats` each, or for as many as there is room for (half as
+// many at each try, at least one).
+float *dalloc_upto(int &want, size_t floats)
+{
+    while (true) {
+        try {
+            return dalloc<float>((size_t)want * floats);
+        } catch (const Err &e) {
+            if (e.code != SG_ENOMEM || want == 1) throw;
+            want = (want + 1) / 2;
+        }
+    }
+}
+
 // Room for a batch's records (the stream is idle when it grows).
 void mlp_reserve(MlpWork &w, int batch)
 {
-    const int want = std::min(batch, kMlpChunk);
+    int want = std::min(batch, kMlpChunk);
     if (w.chunk >= want) return;
     if (w.rec) (void)hipFree(w.rec);
     w.rec = nullptr;
     w.chunk = 0;
-    w.rec = dalloc<float>((size_t)want * kMlpRecFloats);
+    w.rec = dalloc_upto(want, kMlpRecFloats);
     w.chunk = want;
 }
 
@@ -295,11 +309,11 @@ sg_status sg_mlp_train(sg_mlp *m, const float *x, const float *y, int32_t n, int
         const int grp = std::min(kMlpGroups, std::min(batch, n));
         // losses stay on the device for a run of epochs (64 MB of them at most, or one epoch)
         const int64_t per_epoch = (int64_t)nb * grp;
-        const int run = (int)std::max<int64_t>(1, std::min<int64_t>(epochs, (16 << 20) / per_epoch));
+        int run = (int)std::max<int64_t>(1, std::min<int64_t>(epochs, (16 << 20) / per_epoch));
         dx = dalloc<float>((size_t)n * 4);
         dy = dalloc<float>((size_t)n * 33);
         didx = dalloc<int>((size_t)2 * n);
-        dloss = dalloc<float>((size_t)run * per_epoch);
+        dloss = dalloc_upto(run, (size_t)per_epoch);
         for (hipEvent_t &e : ev) chk(hipEventCreateWithFlags(&e, hipEventDisableTiming));
         mlp_reserve(m->work, std::min(batch, n));
         chk(hipMemcpyAsync(dx, x, sizeof(float) * 4 * (size_t)n, hipMemcpyHostToDevice, m->stream));

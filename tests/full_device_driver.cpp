@@ -14,6 +14,7 @@
 
 static size_t room = (size_t)1 << 40;
 static int32_t *apt_perm;      // slot -> buffer of the last APT context made
+static int mlp_chunk, mlp_calls;
 
 extern "C" {
 hipError_t hipMalloc(void **p, size_t n)
@@ -57,6 +58,21 @@ hipError_t launch_apt_init(const InstDev *, const QuadDesc *, int, uint8_t *, co
 }
 hipError_t launch_apt_quad(const AptArgs &, size_t, hipStream_t) { return hipSuccess; }
 hipError_t launch_sqa_init(const SqaArgs &, int, hipStream_t) { return hipSuccess; }
+hipError_t mlp_scratch(float **p)
+{
+    static float a[4];
+    *p = a;
+    return hipSuccess;
+}
+hipError_t launch_mlp_grad(float *, const float *, const float *, const int *, int batch, const MlpWork &w, float *loss,
+                           float *, const MlpAdam *, hipStream_t)
+{
+    mlp_chunk = w.chunk;
+    ++mlp_calls;
+    std::memset(w.rec, 0, sizeof(float) * kMlpRecFloats * (size_t)w.chunk);
+    for (int q = 0; q < (batch < kMlpGroups ? batch : kMlpGroups); ++q) loss[q] = 33.f;
+    return hipSuccess;
+}
 }  // namespace sg
 
 #define CHECK(x)                                                       \
@@ -133,4 +149,26 @@ static int spins(int mode)
     return 0;
 }
 
-int main() { return spins(SG_APT) || spins(SG_SQA); }
+// Gradient and training with room for few records and for the losses of one epoch at a time.
+static int training()
+{
+    room = (size_t)1 << 40;
+    sg_mlp *m = nullptr;
+    CHECK(sg_mlp_create(nullptr, 1, nullptr, &m) == SG_OK);
+    const int n = 9000;
+    std::vector<float> x(4 * n, 1.f), y(33 * n, 1.f), g(SG_MLP_NPARAM);
+    room = 33 * 4 * n;   // the targets: the largest array of the caller's data
+    float loss = 0.f;
+    CHECK(sg_mlp_loss_grad(m, x.data(), y.data(), n, &loss, g.data()) == SG_OK);
+    CHECK(mlp_chunk >= 512 && (size_t)mlp_chunk * sg::kMlpRecFloats * 4 <= room);
+    mlp_calls = 0;
+    const int epochs = 80;
+    std::vector<float> per(epochs, 0.f);
+    CHECK(sg_mlp_train(m, x.data(), y.data(), n, 1, epochs, 1e-3f, per.data()) == SG_OK);
+    CHECK(mlp_calls == epochs * n);
+    for (float v : per) CHECK(v == 1.f);
+    sg_mlp_destroy(m);
+    return 0;
+}
+
+int main() { return spins(SG_APT) || spins(SG_SQA) || training(); }

@@ -2,7 +2,7 @@
 
 The library's host sources are linked against tests/full_device_driver.cpp, a HIP runtime whose
 device memory is host memory and whose hipMalloc can fail: spins are read and written without the
-staging buffer."""
+staging buffer, training takes records in smaller chunks and losses in shorter runs of epochs."""
 import os
 import shutil
 import subprocess
