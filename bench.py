@@ -57,13 +57,13 @@ def alg_ops_per_flip(groups):
 
 # HBM traffic of one DT-SQA launch (R = 1024) from two rocprofv3 counter runs, FETCH_SIZE then
 # WRITE_SIZE (KiB per dispatch), each scaled by what the same counter reads for a plain 256 MiB
-# copy (fetch x 2.0, write x 1.0), for the anneals measured (20 steps, one launch: the default
-# benchmark command; 200 steps, the mean of its launches of 32 and 168).  Reported only while the DT-SQA kernel source is the one
-# measured.
+# copy (fetch x 2.0, write x 1.0), for the anneals measured (20 steps, the default benchmark
+# command, and 200 steps; one launch each).  Reported only while the DT-SQA kernel source is the
+# one measured.
 SQA_TRAFFIC = {"kernel_src_sha256_16": "9e46e42715920861", "R": 1024, "fetch_scale": 2.0,
                "write_scale": 1.0,
                "by_steps": {20: {"fetch_kib": 452607.625, "write_kib": 873472.0},
-                            200: {"fetch_kib": 449287.281, "write_kib": 868864.0}}}
+                            200: {"fetch_kib": 452723.2, "write_kib": 873472.0}}}
 
 
 def sqa_kernel_source_hash():
