@@ -115,7 +115,8 @@ const char *sg_last_error(const sg_ctx *ctx);
  * sg_sweep, and sg_icm and sg_swap without their nullable outputs, only queue launches on the
  * context's stream: a caller may record them into a graph of its own (sg_icm at the cutoff of the
  * call before it), and every replay takes the next step numbers.  Such a graph holds until the
- * context's launch configuration changes (sg_set_launch_config, the autotuner of a first run). */
+ * context's launch configuration changes (sg_set_launch_config, the autotuner of a first run) or
+ * a call uses another ICM cutoff. */
 sg_status sg_sweep(sg_ctx *ctx, int32_t n_sweeps);
 
 /* APT: one ICMop per replica pair at every inverse temperature >= beta_cutoff
